@@ -195,7 +195,7 @@ struct Layout {
     // state
     // (the gradient records st_g2 come last: an inference render needs only
     // infer_bytes of the state)
-    size_t st_status, st_pair_base, st_views, st_recs, st_ckeys, st_cvals, st_cranges, st_thist, st_T, st_nc, st_C,
+    size_t st_status, st_pair_base, st_views, st_recs, st_coarse, st_cranges, st_thist, st_T, st_nc, st_C,
         st_tcost, infer_bytes, st_g2, st_tids, state_bytes;
     // scratch, forward use
     size_t sc_dkeys, sc_dvals, sc_dkeys2, sc_dvals2, sc_cnt, sc_rect, sc_offsets, sc_partials, sc_eff, sc_ceff,
@@ -216,6 +216,16 @@ struct Layout {
     int64_t entries(const Pass& P) const {
         const int nv = P.v1 - P.v0;
         return shared ? (int64_t)nv * n4 + (int64_t)n_groups * n3 : (int64_t)nv * N;
+    }
+    // The pass's ranked binning, when every grid's bits fit LDS and its
+    // histograms (2 bytes per block and super-tile) the scratch that the sort
+    // would use; false: emit and sort.
+    bool ranked(const Pass& P, BinPlan* plan) const {
+        int most = 0;
+        for (int v = P.v0; v < P.v1; ++v) most = std::max(most, vg[v].sx * vg[v].sy);
+        if (entries(P) == 0 || ccap == 0 || most > kBinSupers) return false;
+        *plan = bin_plan(segs(P), shared ? n_groups : 0, most);
+        return plan->bytes <= sc_totals - sc_pkeys;
     }
 };
 
@@ -324,8 +334,8 @@ Layout make_layout(int N, int n3, const h4d_view* views, int V, const h4d_config
     L.st_pair_base = s.take(8 * (V_ + 1));
     L.st_views = s.take(sizeof(ViewParams) * V_);
     L.st_recs = s.take(sizeof(Rec) * n * V_);
-    L.st_ckeys = s.take(4 * (size_t)L.ccap);
-    L.st_cvals = s.take(4 * (size_t)L.ccap);
+    L.st_coarse = s.take(4 * (size_t)L.ccap);
+    s.take(4 * (size_t)L.ccap);  // (8 bytes per entry)
     L.st_cranges = s.take(16 * (size_t)L.total_supers);
     L.st_thist = s.take(4 * (size_t)kCostBuckets * V_);  // one per pass (at most V); cleared with the ranges
     // the per-pixel arrays and everything after them start on a 2 MiB
@@ -564,7 +574,7 @@ unsigned long long* stat_counters(h4d_ctx* c, void* state, const Layout& L) {
 // The call's sorted coarse lists in its state.
 CoarseLists coarse_lists(const Layout& L, const void* state) {
     void* s = const_cast<void*>(state);
-    return CoarseLists{at<uint32_t>(s, L.st_ckeys), at<uint32_t>(s, L.st_cvals), at<int64_t>(s, L.st_cranges)};
+    return CoarseLists{at<uint2>(s, L.st_coarse), at<int64_t>(s, L.st_cranges)};
 }
 
 // Binning and sorting of one pass whose records and depth keys are in place
@@ -624,6 +634,13 @@ bool bin_pass(h4d_ctx* c, const Layout& L, const Pass& P, int tile, int cull, vo
     CullShape* shapes = cull ? at<CullShape>(scratch, L.sc_shape) : nullptr;
     uint32_t* spans = cull ? at<uint32_t>(scratch, L.sc_spans) : nullptr;
     unsigned long long* partials = at<unsigned long long>(scratch, L.sc_partials);
+    BinPlan plan;
+    if (L.ranked(P, &plan)) {
+        launch_bin_ranked(plan, at<char>(scratch, L.sc_pkeys), dv, N, sg, recs, vp, P.v0, P.v1, tile, rect, shapes,
+                          spans, L.ccap, cbase, status, eff_c, at<uint2>(state, L.st_coarse),
+                          at<int64_t>(state, L.st_cranges), st);
+        return true;
+    }
     launch_coarse_count(dv, n, N, sg, recs, vp, P.v0, tile, S, cnt, rect, shapes, spans, partials, st);
     uint32_t* runs = at<uint32_t>(scratch, L.sc_runs);
     launch_coarse_offsets(cnt, n, partials, L.ccap, S, cbase, P.v0, P.v1, status, eff_c, offsets, runs,
@@ -642,8 +659,7 @@ bool bin_pass(h4d_ctx* c, const Layout& L, const Pass& P, int tile, int cull, vo
     const int bits = bits_for(P.supers);
     const int passes = n_passes_for(bits, kMaxRadixBits);
     int64_t* cranges = at<int64_t>(state, L.st_cranges) + 2 * (size_t)L.vg[P.v0].super_base;
-    uint32_t* ckeys = at<uint32_t>(state, L.st_ckeys);
-    uint32_t* cvals = at<uint32_t>(state, L.st_cvals);
+    uint2* coarse = at<uint2>(state, L.st_coarse);
     const unsigned long long* out0 = cbase + P.v0;
     uint32_t* kin = pk;
     uint32_t* vin = pv;
@@ -653,12 +669,12 @@ bool bin_pass(h4d_ctx* c, const Layout& L, const Pass& P, int tile, int cull, vo
     for (int p = 0; p < passes; ++p) {
         const int nb = coarse_pass_bits(bits, p, shift);
         const bool last = p == passes - 1;
-        uint32_t* kout = last ? ckeys : (kin == pk ? pk2 : pk);
-        uint32_t* vout = last ? cvals : (vin == pv ? pv2 : pv);
+        uint32_t* kout = last ? nullptr : (kin == pk ? pk2 : pk);
+        uint32_t* vout = last ? nullptr : (vin == pv ? pv2 : pv);
         if (!launch_radix_pass(kin, vin, kout, vout, p == 0 ? eff_c : ceff, 0, L.ccap, shift, nb, hist,
                                L.hist_words, totals, L.totals_words, last ? out0 : nullptr, st, 1, 0,
                                passes == 1 ? cranges : nullptr, P.supers, kSortItems, last ? dv : nullptr,
-                               (drop && p == 0) ? 1 : 0, (drop && p == 0) ? ceff : nullptr))
+                               (drop && p == 0) ? 1 : 0, (drop && p == 0) ? ceff : nullptr, last ? coarse : nullptr))
             return false;
         kin = kout;
         vin = vout;
@@ -666,7 +682,7 @@ bool bin_pass(h4d_ctx* c, const Layout& L, const Pass& P, int tile, int cull, vo
     }
     if (passes > 1) {
         launch_fill_u64(reinterpret_cast<unsigned long long*>(cranges), 2 * (size_t)P.supers, 0ull, st);
-        launch_ranges(ckeys, 0xFFFFu, ceff, out0, cranges, st);
+        launch_ranges(coarse, 0xFFFFu, ceff, out0, cranges, st);
     }
     return true;
 }

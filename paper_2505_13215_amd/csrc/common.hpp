@@ -71,8 +71,7 @@ __device__ __forceinline__ int find_view_of_tile(const ViewParams* views, int v0
 // Sorted coarse lists of a call (binning's output, read by the blending
 // kernels): per super-tile, its (Gaussian, super-tile) entries in depth order.
 struct CoarseLists {
-    const uint32_t* keys;   // super-tile id (pass-relative) | tile mask << 16
-    const uint32_t* vals;   // splat id (relative to the record's view)
+    const uint2* entries;   // .x: super-tile id | tile mask << 16, .y: splat id (relative to the record's view)
     const int64_t* ranges;  // [start, end) per global super-tile id
 };
 

@@ -82,13 +82,15 @@ bool radix_pass_fits(uint64_t capacity, int n_seg, int nbits, int items, size_t 
 // the values written out are val_map[value].  skip_empty: keys whose upper 16
 // bits are zero are dropped (the output holds the others, in order, from
 // position 0); out_count (may be null) receives the number of keys written.
+// pairs_out (may be null): takes (key, value) pairs instead of keys_out and
+// vals_out.
 bool launch_radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* keys_out, uint32_t* vals_out,
                        const unsigned long long* dcount, uint64_t hcount, uint64_t capacity, int shift, int nbits,
                        uint32_t* hist, size_t hist_words, uint32_t* totals, size_t totals_words,
                        const unsigned long long* out_offset, hipStream_t st, int n_seg = 1, uint64_t seg_stride = 0,
                        int64_t* digit_ranges = nullptr, int n_digit_ranges = 0, int items = kSortItems,
                        const uint32_t* val_map = nullptr, int skip_empty = 0,
-                       unsigned long long* out_count = nullptr);
+                       unsigned long long* out_count = nullptr, uint2* pairs_out = nullptr);
 int scan_blocks(int n);
 // out[j] = sum_{i<j} in[idx[i]] (idx may be null), out[n] = total; 64-bit.
 // With run_start, run_start[r] (r < run_cap) receives the index i whose range
@@ -137,10 +139,29 @@ void launch_coarse_emit(const unsigned long long* offsets, const uint32_t* run_s
                         const uint64_t* rect_sorted, const CullShape* shapes, const uint32_t* spans,
                         const ViewParams* views, int v0, int tile, int S, uint64_t capacity,
                         const unsigned long long* eff_count, uint32_t* keys, uint32_t* vals, hipStream_t st);
-// ranges of the sorted keys keys[*base ..) (compared under key_mask):
-// ranges[2k], ranges[2k+1] = [first, last+1), counted from keys (base may be
+// Ranked binning: launch_coarse_count to the sorted lists and their ranges
+// without a sort, for passes whose views (and static groups) have at most
+// kBinSupers super-tiles each.  work: bin_plan(..).bytes bytes, any content.
+// entries: the call's list entries; ranges: the call's (indexed by global
+// super-tile id), cleared beforehand: written only when the pass fits ccap
+// (the check and its outputs as launch_coarse_offsets).
+constexpr int kBinSupers = 2048;  // a block's bits take 32 bytes of LDS per super-tile
+constexpr int kBinBlock = 256;    // splats per block
+constexpr int kBinChunk = 64;     // blocks per chunk of the histograms' scan
+struct BinPlan {
+    int n_seg = 0, words = 0;
+    int64_t blocks = 0, chunks = 0;
+    size_t bytes = 0, hist = 0, partials = 0, chunk_sums = 0, chunk_entries = 0, lists = 0, seg_entries = 0;
+};
+BinPlan bin_plan(const SegLayout& sg, int n_groups, int max_supers);
+void launch_bin_ranked(const BinPlan& p, void* work, const uint32_t* sorted_gid, int N, SegLayout sg, const Rec* recs,
+                       const ViewParams* views, int v0, int v1, int tile, uint64_t* rect_sorted, CullShape* shapes,
+                       uint32_t* spans, uint64_t ccap, unsigned long long* cbase, Status* status,
+                       unsigned long long* eff_count, uint2* entries, int64_t* ranges, hipStream_t st);
+// ranges of the sorted entries entries[*base ..) (keys compared under key_mask):
+// ranges[2k], ranges[2k+1] = [first, last+1), counted from entries (base may be
 // null: 0)
-void launch_ranges(const uint32_t* keys, uint32_t key_mask, const unsigned long long* eff_count,
+void launch_ranges(const uint2* entries, uint32_t key_mask, const unsigned long long* eff_count,
                    const unsigned long long* base, int64_t* ranges, hipStream_t st);
 // Backward prologue: zeroes g2[0, n_g2) if *dirty != 0 or force, and orders the
 // tiles of every pass by decreasing tcost: one workgroup per pass from the

@@ -63,8 +63,9 @@ __device__ inline int walk_fill(const CoarseLists& L, uint32_t bit, WalkRun& r, 
         for (int w = 0; w < 4; ++w) {
             const int64_t k = p0 + w * 64 + lane;
             const bool in = w < nw && k < r.end;
-            kk[w] = in ? L.keys[k] : 0u;  // (a key of 0 has no tile bit)
-            vv[w] = in ? L.vals[k] : 0u;
+            const uint2 e = in ? L.entries[k] : make_uint2(0u, 0u);  // (a key of 0 has no tile bit)
+            kk[w] = e.x;
+            vv[w] = e.y;
         }
 #pragma unroll
         for (int w = 0; w < 4; ++w)
@@ -105,7 +106,7 @@ __device__ __forceinline__ unsigned long long walk_xor(unsigned long long v, int
 __device__ inline uint64_t walk_count(const CoarseLists& L, uint32_t bit, WalkRun r) {
     uint64_t c = 0;
     for (int64_t p = r.pos + __lane_id(); __ballot(p < r.end) != 0ull; p += 64) {
-        const bool keep = p < r.end && ((L.keys[p] >> bit) & 1u) != 0u;
+        const bool keep = p < r.end && ((L.entries[p].x >> bit) & 1u) != 0u;
         c += (uint64_t)__popcll(__ballot(keep));
     }
     return c;
