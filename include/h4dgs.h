@@ -145,7 +145,10 @@ const char *h4dgs_version(void);
  * and of `scratch` (free between calls) for n3 + n4 Gaussians, the given host
  * array of n_views views and the configuration.  Pure host arithmetic.  An
  * inference render needs only a leading part of the state (no gradient
- * records: N x n_views x 64 bytes less). */
+ * records: N x n_views x 64 bytes less).  Calls of at most 2048 tiles of 16 x
+ * 16 pixels include 29 KiB per tile for the adjoint's checkpoints, without which
+ * (a smaller state) they run slower; render_bwd takes the state_bytes of its
+ * render_fwd. */
 h4d_status h4dgs_workspace_size(h4d_ctx *ctx, int32_t n3, int32_t n4, const h4d_view *views, int32_t n_views,
                                 const h4d_config *cfg, size_t *state_bytes, size_t *scratch_bytes);
 

@@ -196,7 +196,8 @@ struct Layout {
     // (the gradient records st_g2 come last: an inference render needs only
     // infer_bytes of the state)
     size_t st_status, st_pair_base, st_views, st_recs, st_coarse, st_cranges, st_thist, st_T, st_nc, st_C,
-        st_tcost, infer_bytes, st_g2, st_tids, state_bytes;
+        st_tcost, infer_bytes, st_g2, st_tids, st_chk, min_state_bytes, state_bytes;
+    bool quad = false;  // the call's tiles are few enough for the quadrant kernels' checkpoints
     // scratch, forward use
     size_t sc_dkeys, sc_dvals, sc_dkeys2, sc_dvals2, sc_cnt, sc_rect, sc_offsets, sc_partials, sc_eff, sc_ceff,
         sc_pkeys, sc_pvals, sc_pkeys2, sc_pvals2, sc_hist, sc_totals, sc_shape, sc_spans, sc_runs, sc_wcnt, sc_woff, sc_wpart,
@@ -349,6 +350,15 @@ Layout make_layout(int N, int n3, const h4d_view* views, int V, const h4d_config
     L.infer_bytes = s.off;
     L.st_g2 = s.take(4 * (size_t)kG2Stride * n * V_);
     L.st_tids = s.take(4 * (size_t)kTileIds * (size_t)tb);
+    L.min_state_bytes = s.off;
+    // few tiles: longer list heads (in place of those) and the checkpoints, which
+    // a caller's smaller state goes without
+    L.quad = cfg->tile == 16 && tb <= kQuadTiles;
+    if (L.quad) {
+        s.off = L.st_tids;
+        s.take(4 * (size_t)kQuadIds * (size_t)tb);
+        L.st_chk = s.take(16 * (size_t)(kQuadSegs - 1) * 256 * (size_t)tb);
+    }
     L.state_bytes = s.off;
     Carve f;
     L.sc_dkeys = f.take(4 * np);
@@ -699,9 +709,9 @@ void write_tile_lists(const Layout& L, int tile, void* state, void* scratch, uin
 
 // Blending of one pass whose coarse lists are in place.
 // keep: write the adjoint's per-pixel and per-tile state (false for an
-// inference render)
+// inference render); quad: the state has room for the checkpoints
 void blend_pass(h4d_ctx* c, const Layout& L, int k, int tile, int chunk, void* state, const PtrTable& images,
-                hipStream_t st, bool keep) {
+                hipStream_t st, bool keep, bool quad) {
     const Pass P = L.pass(k);
     StageScope sc(c, st, H4D_STAGE_BLEND_FWD);
     KernelMark km(c, H4D_STAGE_BLEND_FWD, P.tiles > 0);
@@ -710,7 +720,9 @@ void blend_pass(h4d_ctx* c, const Layout& L, int k, int tile, int chunk, void* s
                          keep ? at<float>(state, L.st_T) : nullptr, keep ? at<uint32_t>(state, L.st_nc) : nullptr,
                          keep ? at<float>(state, L.st_C) : nullptr, keep ? at<uint32_t>(state, L.st_tcost) : nullptr,
                          keep ? at<uint32_t>(state, L.st_thist) + (size_t)kCostBuckets * k : nullptr,
-                         keep ? at<uint32_t>(state, L.st_tids) : nullptr, keep ? stat_counters(c, state, L) : nullptr,
+                         keep ? at<uint32_t>(state, L.st_tids) : nullptr, quad ? kQuadIds : kTileIds,
+                         keep && quad ? at<float4>(state, L.st_chk) : nullptr, at<Status>(state, L.st_status),
+                         keep ? stat_counters(c, state, L) : nullptr,
                          st, km.a, km.b);
 }
 
@@ -790,7 +802,8 @@ static h4d_status render_forward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d*
     const int N = g3->n + g4->n;
     const Layout L = make_layout(N, g3->n, views, n_views, cfg);
     if ((s = check_layout(ctx, L, cfg)) != H4D_OK) return s;
-    const size_t need = keep ? L.state_bytes : L.infer_bytes;
+    const size_t need = keep ? L.min_state_bytes : L.infer_bytes;
+    const bool quad = L.quad && state_bytes >= L.state_bytes;
     if (!state || state_bytes < need)
         return fail(ctx, H4D_ERR_INVALID_ARG, "state too small (%zu < %zu)", state_bytes, need);
     if (!scratch || scratch_bytes < L.fwd_bytes)
@@ -816,7 +829,7 @@ static h4d_status render_forward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d*
         }
         if (!bin_pass(ctx, L, P, cfg->tile, cfg->cull, state, scratch, st, keep))
             return fail(ctx, H4D_ERR_UNSUPPORTED, "internal: a radix pass did not fit its buffers");
-        blend_pass(ctx, L, k, cfg->tile, cfg->chunk, state, tab, st, keep);
+        blend_pass(ctx, L, k, cfg->tile, cfg->chunk, state, tab, st, keep, quad);
     }
     return hip_check(ctx, keep ? "render_fwd" : "render_infer");
 }
@@ -892,8 +905,9 @@ static h4d_status render_backward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d
     const int N = g3->n + g4->n;
     const Layout L = make_layout(N, g3->n, views, n_views, cfg);
     if ((s = check_layout(ctx, L, cfg)) != H4D_OK) return s;
-    if (!state || state_bytes < L.state_bytes)
-        return fail(ctx, H4D_ERR_INVALID_ARG, "state too small (%zu < %zu)", state_bytes, L.state_bytes);
+    if (!state || state_bytes < L.min_state_bytes)
+        return fail(ctx, H4D_ERR_INVALID_ARG, "state too small (%zu < %zu)", state_bytes, L.min_state_bytes);
+    const bool quad = L.quad && state_bytes >= L.state_bytes;  // (as the forward on this state)
     if (!scratch || scratch_bytes < L.bwd_bytes)
         return fail(ctx, H4D_ERR_INVALID_ARG, "scratch too small (%zu < %zu)", scratch_bytes, L.bwd_bytes);
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -931,7 +945,9 @@ static h4d_status render_backward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d
             launch_composite_bwd(cfg->tile, cfg->chunk, at<Rec>(stt, L.st_recs), N, coarse_lists(L, stt),
                                  L.shared, static_rows, vp, P.v0, P.v1, P.tiles, border + pt.tile0[k], tab,
                                  at<float>(stt, L.st_T),
-                                 at<uint32_t>(stt, L.st_nc), at<float>(stt, L.st_C), at<uint32_t>(stt, L.st_tids), g2,
+                                 at<uint32_t>(stt, L.st_nc), at<float>(stt, L.st_C), at<uint32_t>(stt, L.st_tcost),
+                                 at<uint32_t>(stt, L.st_tids), quad ? kQuadIds : kTileIds,
+                                 quad ? at<float4>(stt, L.st_chk) : nullptr, status, g2,
                                  stat_counters(ctx, stt, L),
                                  st, km.a, km.b);
         }
@@ -1007,7 +1023,7 @@ h4d_status h4dgs_rasterize_splats(h4d_ctx* ctx, int32_t n, const float* u, const
     if ((s = check_views(ctx, &view, 1)) != H4D_OK) return s;
     const Layout L = make_layout(n, 0, &view, 1, cfg);
     if ((s = check_layout(ctx, L, cfg)) != H4D_OK) return s;
-    if (!state || state_bytes < L.state_bytes) return fail(ctx, H4D_ERR_INVALID_ARG, "state too small");
+    if (!state || state_bytes < L.min_state_bytes) return fail(ctx, H4D_ERR_INVALID_ARG, "state too small");
     if (!scratch || scratch_bytes < L.fwd_bytes) return fail(ctx, H4D_ERR_INVALID_ARG, "scratch too small");
     if (!plan_fits(L)) return fail(ctx, H4D_ERR_UNSUPPORTED, "internal: radix buffers of the layout too small");
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -1022,7 +1038,7 @@ h4d_status h4dgs_rasterize_splats(h4d_ctx* ctx, int32_t n, const float* u, const
     tab.p[0] = image;
     if (!bin_pass(ctx, L, L.pass(0), cfg->tile, cfg->cull, state, scratch, st, true))
         return fail(ctx, H4D_ERR_UNSUPPORTED, "internal: a radix pass did not fit its buffers");
-    blend_pass(ctx, L, 0, cfg->tile, cfg->chunk, state, tab, st, true);
+    blend_pass(ctx, L, 0, cfg->tile, cfg->chunk, state, tab, st, true, L.quad && state_bytes >= L.state_bytes);
     const size_t hw = (size_t)width * height;
     if (T_final) (void)hipMemcpyAsync(T_final, at<float>(state, L.st_T), 4 * hw, hipMemcpyDeviceToDevice, st);
     if (sorted_ids && ranges)
@@ -1042,7 +1058,7 @@ h4d_status h4dgs_tile_lists(h4d_ctx* ctx, int32_t n3, int32_t n4, const h4d_view
     if ((s = check_pass_size(ctx, cfg, (int64_t)n3 + n4, n_views)) != H4D_OK) return s;
     const Layout L = make_layout(n3 + n4, n3, views, n_views, cfg);
     if ((s = check_layout(ctx, L, cfg)) != H4D_OK) return s;
-    if (!state || state_bytes < L.state_bytes) return fail(ctx, H4D_ERR_INVALID_ARG, "state too small");
+    if (!state || state_bytes < L.min_state_bytes) return fail(ctx, H4D_ERR_INVALID_ARG, "state too small");
     if (!scratch || scratch_bytes < L.fwd_bytes) return fail(ctx, H4D_ERR_INVALID_ARG, "scratch too small");
     if (!ids || !ranges) return fail(ctx, H4D_ERR_INVALID_ARG, "ids / ranges is null");
     write_tile_lists(L, cfg->tile, const_cast<void*>(state), scratch, ids, ids_capacity, ranges,

@@ -79,6 +79,12 @@ struct CoarseLists {
 // static flag) for the adjoint, which re-walks only tiles whose last
 // contributor lies beyond them.
 constexpr int kTileIds = 256;
+// Calls of at most kQuadTiles 16 x 16 tiles blend quadrant by quadrant
+// (composite.hip) and keep kQuadIds entries and every pixel's state at the
+// starts of kQuadSegs segments of 64 entries.
+constexpr int kQuadTiles = 2048;
+constexpr int kQuadSegs = 8;
+constexpr int kQuadIds = 64 * kQuadSegs;
 
 // Layout of a pass's depth-ordered entries: na segments of la entries (the
 // views v0 .. v0 + na - 1, all their Gaussians, or only the 4D ones when the
@@ -128,7 +134,9 @@ struct Status {
     // counters of the counting variants (h4dgs_stats): blend evaluations and
     // blends of the forward and the adjoint, tile-list entries, traversed
     // entries (each tile's last contributor) and on-screen records
-    unsigned long long pad[13];
+    unsigned long long pad[12];
+    // nonzero once a forward has left the quadrant kernels' checkpoints
+    unsigned long long checkpoints;
     // nonzero once a backward has accumulated into the screen-space gradient
     // records (which the forward leaves zeroed): a further backward clears them
     unsigned long long g2_dirty;

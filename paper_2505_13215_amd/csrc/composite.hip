@@ -22,6 +22,7 @@
 #include <hip/hip_ext.h>
 #include <type_traits>
 #include "common.hpp"
+#include "cull.hpp"
 #include "launch.hpp"
 #include "walk.hpp"
 
@@ -244,7 +245,7 @@ __global__ void __launch_bounds__((ShapeF<B, SPLIT>::NT), (FwdWaves<B, SPLIT, ME
     const Rec* __restrict__ recs, int N, CoarseLists lists, const ViewParams* __restrict__ views, int v0, int v1,
     const uint32_t* __restrict__ order, PtrTable images, float* __restrict__ Tfin, uint32_t* __restrict__ ncontrib,
     float* __restrict__ Cout, uint32_t* __restrict__ tcost, uint32_t* __restrict__ thist, uint32_t* __restrict__ tids,
-    unsigned long long* counters) {
+    int tile_ids, unsigned long long* counters) {
     constexpr int NT = ShapeF<B, SPLIT>::NT, PPL = ShapeF<B, SPLIT>::PPL;
     // two waves per tile: wave 0 walks the next chunk's entries while wave 1
     // stages the current chunk's records (the ids double-buffered); one wave
@@ -315,7 +316,7 @@ __global__ void __launch_bounds__((ShapeF<B, SPLIT>::NT), (FwdWaves<B, SPLIT, ME
                 const uint32_t raw = s_ids[cur][k];
                 stage_splat(walk.record(raw), raw & ~kFromStatic, ty * B, ty * B + B - 1, s_sp[k]);
                 // the list's head, kept for the adjoint
-                if (tids && rel0 + (uint32_t)k < (uint32_t)kTileIds) tids[(size_t)gt * kTileIds + rel0 + k] = raw;
+                if (tids && rel0 + (uint32_t)k < (uint32_t)tile_ids) tids[(size_t)gt * tile_ids + rel0 + k] = raw;
             }
         }
         __syncthreads();
@@ -432,6 +433,219 @@ __global__ void __launch_bounds__((ShapeF<B, SPLIT>::NT), (FwdWaves<B, SPLIT, ME
     }
 }
 
+// ---------------------------------------------------------------------------
+// Quadrant kernels: launches of few 16 x 16 tiles.
+// ---------------------------------------------------------------------------
+// With few tiles a launch lasts as long as one tile's list takes, and most of
+// the chip is idle.  A tile then takes five waves: each of four blends one 8 x 8
+// quadrant, one pixel per lane, and only the splats that can reach it (the
+// ellipse test of the tile lists at 8 pixels; a pair that it drops would not
+// blend, so every pixel's blends are the same); the fifth walks the list and
+// stages the next chunk's records (and walks one chunk further) while the
+// others blend.  Pixel arithmetic is eval_col / eval_pix / next_T in list order
+// as in the other kernels: images are bit-identical.  A tile's wave issues
+// fewer than one instruction in four cycles when it is alone on its SIMD, so
+// the time is the list's length times the instructions per step; forward of
+// 2,000 Gaussians at 128 x 96 (48 tiles) 0.070 -> 0.024 ms, 20k at 333 x 250 (336
+// tiles) 0.133 -> 0.045 ms, 100k at 640 x 480 (1200) 0.085 -> 0.060 ms, 50k at
+// 800 x 600 (1900) 0.083 -> 0.077 ms; at 1000 x 750 (2961) 0.088 -> 0.103 ms, where
+// the chip is full and two pixels per lane share more work: kQuadTiles lies
+// between.
+constexpr int kQuadChunk = 64;                 // one list entry per lane of the staging wave
+constexpr int kQuadThreads = 5 * 64;
+// The adjoint takes four waves per segment (one pixel per lane, culled by
+// quadrant) up to this many tiles, one (four pixels per lane) beyond: 336 tiles
+// 0.040 against 0.052 ms, 1200 tiles 0.074-0.085 against 0.075-0.080 ms, 1900 tiles
+// 0.112 against 0.094 ms (before segments 0.215, 0.133-0.140 and 0.121 ms).
+constexpr int kQuadBwdTiles = 1000;
+
+struct QuadStage {
+    LSplat sp[2][kQuadChunk];
+    unsigned long long mask[2][4];  // per quadrant: the chunk's splats that can reach it
+    int cnt[2];
+    int done[2][4];  // forward, by the round's parity: the quadrant's pixels are all finished
+};
+
+// Stages the record of entry raw (lane < n) into buffer b.
+template <bool MERGE>
+__device__ __forceinline__ void quad_stage(const Rec& r, uint32_t gid, int n, int tx, int ty, int b, QuadStage& s) {
+    const int lane = __lane_id();
+    uint32_t q = 0u;  // quadrants, bit 2 row + column
+    if (lane < n) {
+        stage_splat(r, gid, ty * 16, ty * 16 + 15, s.sp[b][lane]);
+        const CullShape cs = cull_shape(r);
+        if (cs.mode == 0) q = 0xFu;
+        if (cs.mode == 1) {
+            int r0, r1;
+            slab_rows<8>(cs, 2 * ty, 2 * ty + 1, r0, r1);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int y = 2 * ty + k;
+                const uint32_t e = y >= r0 && y <= r1 ? row_columns<8>(cs, y, 2 * tx, 2 * tx + 1) : 0u;
+                if (e != 0u) {
+                    const uint32_t lo = (e & 0xFFFFu) - 2u * (uint32_t)tx, hi = (e >> 16) - 2u * (uint32_t)tx;
+                    q |= ((1u << hi) - (1u << lo)) << (2 * k);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const unsigned long long m = __ballot((q >> k) & 1u);
+        if (lane == 0) s.mask[b][k] = m;
+    }
+    if (lane == 0) s.cnt[b] = n;
+}
+
+// Whether every quadrant had finished before the round of parity b (each wave
+// writes its flag before the round's barrier; the next write to the same slot
+// lies behind the next barrier, which no wave passes before all have read).
+__device__ __forceinline__ bool quad_done(const QuadStage& s, int b) {
+    return (s.done[b][0] & s.done[b][1] & s.done[b][2] & s.done[b][3]) != 0;
+}
+
+// A wave-uniform 64-bit value in scalar registers.
+__device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// Takes the next set bit off m (j unchanged and false when there is none).
+__device__ __forceinline__ bool take_bit(unsigned long long& m, int& j) {
+    if (m == 0ull) return false;
+    j = (int)__builtin_ctzll(m);
+    m &= m - 1ull;
+    return true;
+}
+
+template <bool MERGE>
+__global__ void __launch_bounds__(kQuadThreads) k_composite_fwd_quad(
+    const Rec* __restrict__ recs, int N, CoarseLists lists, const ViewParams* __restrict__ views, int v0, int v1,
+    const uint32_t* __restrict__ order, PtrTable images, float* __restrict__ Tfin, uint32_t* __restrict__ ncontrib,
+    float* __restrict__ Cout, uint32_t* __restrict__ tcost, uint32_t* __restrict__ thist,
+    uint32_t* __restrict__ tids, int tile_ids, float4* __restrict__ chk, Status* __restrict__ status) {
+    __shared__ QuadStage s_st;
+    __shared__ WalkQueues s_q;
+    __shared__ uint32_t s_cost;
+    const int gt = views[v0].tile_base + dispatch_tile(order);
+    const int view = find_view_of_tile(views, v0, v1, gt);
+    const ViewParams& V = views[view];
+    const int tile = gt - V.tile_base;
+    const int tx = tile % V.tiles_x, ty = tile / V.tiles_x;
+    const int tid = (int)threadIdx.x, lane = __lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid == 0) s_cost = 0u;
+    if (chk && blockIdx.x == 0 && tid == 0) status->checkpoints = 1ull;
+    // every wave runs the same rounds: round c blends chunk c (buffer c & 1)
+    // while the staging wave fills the other buffer with chunk c + 1
+    if (w == 4) {
+        TileWalk<MERGE> walk;
+        walk.init(lists, V, view, recs, N, super_factor(16), tx, ty);
+        uint32_t raw, ahead;
+        int n = walk.next(kQuadChunk, s_q, raw);
+        uint32_t rel = 0;
+        for (int c = 0;; ++c) {
+            const Rec r = lane < n ? walk.record(raw) : Rec{};
+            const int na = n == kQuadChunk ? walk.next(kQuadChunk, s_q, ahead) : 0;
+            if (tids && lane < n && rel + (uint32_t)lane < (uint32_t)tile_ids)
+                tids[(size_t)gt * tile_ids + rel + lane] = raw;  // the list's head, kept for the adjoint
+            quad_stage<MERGE>(r, raw & ~kFromStatic, n, tx, ty, c & 1, s_st);
+            rel += (uint32_t)n;
+            __syncthreads();
+            if (n == 0 || quad_done(s_st, c & 1)) break;
+            raw = ahead;
+            n = na;
+        }
+    } else {
+        const int px = tx * 16 + (w & 1) * 8 + (lane & 7), py = ty * 16 + (w >> 1) * 8 + (lane >> 3);
+        const float pxc = (float)px + 0.5f, pyc = (float)py + 0.5f;
+        const bool inside = px < V.W && py < V.H;
+        bool alive = inside;
+        float T = 1.0f, cr = 0.f, cg = 0.f, cb = 0.f;
+        uint32_t last = 0u, rel0 = 0u;
+        bool done = __ballot(alive) == 0ull;
+        for (int c = 0;; ++c) {
+            const int b = c & 1;
+            if (lane == 0) s_st.done[b][w] = done;
+            __syncthreads();
+            const int cnt = s_st.cnt[b];
+            if (cnt == 0 || quad_done(s_st, b)) break;
+            if (chk && c > 0 && c < kQuadSegs && alive)  // (a finished pixel's is never read)
+                chk[((size_t)gt * (kQuadSegs - 1) + (c - 1)) * 256 + tid] = make_float4(T, cr, cg, cb);
+            if (!done) {
+                unsigned long long m = uniform64(s_st.mask[b][w]);
+                // four splats at a time: their alphas are independent, only the
+                // transmittance runs through them in order
+                while (m != 0ull) {
+                    int j[4] = {0, 0, 0, 0};
+                    bool have[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) have[q] = take_bit(m, j[q]);
+                    float alpha[4], r[4], g[4], bl[4];
+                    bool ok[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const Splat s = to_splat(s_st.sp[b][j[q]]);
+                        const ColTerm ct = eval_col(s, px, pxc);
+                        float dy, G;
+                        bool clamped;
+                        ok[q] = eval_pix(s, ct, square_test<false>(s, ct, py), pyc, dy, G, alpha[q], clamped) && have[q];
+                        r[q] = s.cr; g[q] = s.cg; bl[q] = s.cb;
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float Tn = next_T(T, alpha[q]);
+                        const bool pass = ok[q] && alive, low = Tn < kMinT;
+                        const bool blend = pass && !low;
+                        alive = alive && !(pass && low);
+                        const float wgt = blend ? alpha[q] * T : 0.0f;
+                        cr = __builtin_fmaf(r[q], wgt, cr);
+                        cg = __builtin_fmaf(g[q], wgt, cg);
+                        cb = __builtin_fmaf(bl[q], wgt, cb);
+                        T = blend ? Tn : T;
+                        last = blend ? rel0 + (uint32_t)j[q] + 1u : last;
+                    }
+                    if (__ballot(alive) == 0ull) {
+                        done = true;
+                        break;
+                    }
+                }
+            }
+            rel0 += (uint32_t)cnt;
+        }
+        if (inside) {
+            const size_t HW = (size_t)V.W * V.H, p = (size_t)py * V.W + px;
+            float* __restrict__ image = images.p[view];
+            const float o0 = __builtin_fmaf(T, V.bg[0], cr), o1 = __builtin_fmaf(T, V.bg[1], cg),
+                        o2 = __builtin_fmaf(T, V.bg[2], cb);
+            image[p] = o0;
+            image[HW + p] = o1;
+            image[2 * HW + p] = o2;
+            if (Tfin) {  // the adjoint's per-pixel state (not kept by an inference render)
+                const size_t q = (size_t)V.pix_base + p;
+                Tfin[q] = T;
+                ncontrib[q] = last;
+                Cout[3 * (size_t)V.pix_base + p] = o0;
+                Cout[3 * (size_t)V.pix_base + HW + p] = o1;
+                Cout[3 * (size_t)V.pix_base + 2 * HW + p] = o2;
+            }
+        }
+        if (tcost) {
+            const uint32_t wave_last = wave_max_u32(last);
+            if (lane == 0) atomicMax(&s_cost, wave_last);
+        }
+    }
+    // the tile's cost for the adjoint (tcost is the same for the whole launch)
+    if (tcost) {
+        __syncthreads();
+        if (tid == 0) {
+            tcost[gt] = s_cost;
+            atomicAdd(&thist[cost_bucket(s_cost)], 1u);
+        }
+    }
+}
+
 // Cross-lane building blocks of the backward's reduction (gfx950).
 // swap32_add(a, b): lanes 0-31 get a[l] + a[l + 32], lanes 32-63 get b[l - 32] + b[l].
 __device__ __forceinline__ float swap32_add(float a, float b) {
@@ -483,6 +697,34 @@ __device__ __forceinline__ float wave_sum9(float e0, float e1, float e2, float e
     return z;
 }
 
+// The segments of a launch's tiles (kQuadSegs per tile), and what the forward
+// left for them.
+struct QuadSegs {
+    int n_tiles;
+    const uint32_t* tcost;  // per global tile: its last contributor
+    const float4* chk;      // checkpoints
+    const Status* status;
+};
+// The (tile, segment) of this workgroup and the list entries [first, end) it
+// takes; false: none.  The last segment goes on to the list's end; without
+// checkpoints (status->checkpoints: a counting forward leaves none) the first
+// one takes the whole list.
+__device__ __forceinline__ bool quad_segment(const QuadSegs& q, const ViewParams* __restrict__ views, int v0,
+                                             const uint32_t* __restrict__ order, int& gt, int& seg, uint32_t& first,
+                                             uint32_t& end) {
+    // the last segment, which may be the longest, starts first, then the others
+    // in order (most tiles have no late ones)
+    const int rank = (int)blockIdx.x % q.n_tiles;
+    seg = ((int)blockIdx.x / q.n_tiles + kQuadSegs - 1) % kQuadSegs;
+    const uint32_t o = order[rank];
+    gt = views[v0].tile_base + (int)(o < (uint32_t)q.n_tiles ? o : (uint32_t)rank);
+    const uint32_t total = q.tcost[gt];
+    const bool cut = q.status->checkpoints != 0ull;
+    first = (uint32_t)(seg * kQuadChunk);
+    end = cut && seg < kQuadSegs - 1 ? min(total, first + kQuadChunk) : total;
+    return first < end && (cut || seg == 0);
+}
+
 // Per splat of the tile's list (up to its last contributor), the wave's nine
 // gradient sums (wave_sum9) are added into the splat's g2 record with one
 // global atomic instruction (twelve lanes, one record).
@@ -490,19 +732,28 @@ __device__ __forceinline__ float wave_sum9(float e0, float e1, float e2, float e
 // records of the static group's view.
 // (registers for 5 waves per SIMD, what the plain adjoint uses anyway: the
 // merging walk would otherwise take the occupancy down to 4)
-template <int B, int CHUNK, bool STATS, bool MERGE>
+// SEG (16 x 16 tiles, one wave): one wave per (tile, segment of its list), from
+// the forward's checkpoints, as k_composite_bwd_quad.
+template <int B, int CHUNK, bool STATS, bool MERGE, bool SEG = false>
 __global__ void __launch_bounds__(Shape<B>::NT, 5) k_composite_bwd(
     const Rec* __restrict__ recs, int N, CoarseLists lists, int static_rows, const ViewParams* __restrict__ views,
     int v0, int v1, const uint32_t* __restrict__ order, CPtrTable dls, const float* __restrict__ Tfin,
     const uint32_t* __restrict__ ncontrib, const float* __restrict__ Cout, const uint32_t* __restrict__ tids,
-    float* __restrict__ g2, unsigned long long* counters) {
+    int tile_ids, float* __restrict__ g2, unsigned long long* counters, QuadSegs segs) {
     constexpr int NT = Shape<B>::NT, PPL = Shape<B>::PPL;
+    static_assert(!SEG || (B == 16 && CHUNK == kQuadChunk && !STATS), "");
     __shared__ LSplat s_sp[CHUNK];
     __shared__ uint32_t s_ids[CHUNK];
     __shared__ WalkQueues s_q;
     __shared__ int s_cnt;
     __shared__ uint32_t s_max;
-    const int gt = views[v0].tile_base + dispatch_tile(order);
+    int gt, seg = 0;
+    uint32_t first = 0u, end = 0u;  // SEG: the segment's entries
+    if constexpr (SEG) {
+        if (!quad_segment(segs, views, v0, order, gt, seg, first, end)) return;  // uniform
+    } else {
+        gt = views[v0].tile_base + dispatch_tile(order);
+    }
     const int view = find_view_of_tile(views, v0, v1, gt);
     const ViewParams& V = views[view];
     const int tile = gt - V.tile_base;
@@ -529,18 +780,29 @@ __global__ void __launch_bounds__(Shape<B>::NT, 5) k_composite_bwd(
         py[k] = ty * B + p / B;
         pyc[k] = (float)py[k] + 0.5f;
         G0[k] = G1[k] = G2[k] = R[k] = 0.f;
+        T[k] = 1.0f;
         nc[k] = 0u;
         if (px < V.W && py[k] < V.H) {
             const size_t q = (size_t)py[k] * V.W + px;
             G0[k] = dl[q]; G1[k] = dl[HW + q]; G2[k] = dl[2 * HW + q];
-            const float c0 = Cout[3 * (size_t)V.pix_base + q];
-            const float c1 = Cout[3 * (size_t)V.pix_base + HW + q];
-            const float c2 = Cout[3 * (size_t)V.pix_base + 2 * HW + q];
-            R[k] = G0[k] * c0 + G1[k] * c1 + G2[k] * c2;  // dot(dL/dC, C_out)
+            float c0 = Cout[3 * (size_t)V.pix_base + q];
+            float c1 = Cout[3 * (size_t)V.pix_base + HW + q];
+            float c2 = Cout[3 * (size_t)V.pix_base + 2 * HW + q];
             nc[k] = ncontrib[(size_t)V.pix_base + q];
             lane_min = min(lane_min, nc[k]);
+            if constexpr (SEG) {
+                if (seg > 0) {
+                    // (a pixel that finished before the segment has no checkpoint, and no terms)
+                    const bool on = nc[k] > first;
+                    const int c = (((p / B) >> 3) << 7) | (((p % B) >> 3) << 6) | (((p / B) & 7) << 3) | ((p % B) & 7);
+                    const float4 at = on ? segs.chk[((size_t)gt * (kQuadSegs - 1) + (seg - 1)) * 256 + c]
+                                         : make_float4(1.f, c0, c1, c2);
+                    T[k] = at.x;
+                    c0 -= at.y; c1 -= at.z; c2 -= at.w;
+                }
+            }
+            R[k] = G0[k] * c0 + G1[k] * c1 + G2[k] * c2;  // dot(dL/dC, C_out, or the colour from the segment on)
         }
-        T[k] = 1.0f;
         lane_nc = max(lane_nc, nc[k]);
     }
     if (threadIdx.x == 0) s_max = 0u;
@@ -550,7 +812,7 @@ __global__ void __launch_bounds__(Shape<B>::NT, 5) k_composite_bwd(
     // the forward's last contributor (the walk ends with the tile's list, so a
     // state whose per-pixel part comes from another forward reads no foreign
     // entries)
-    const uint32_t total = s_max;
+    const uint32_t total = SEG ? end : s_max;
     const uint32_t wave_nc = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(lane_nc));
     // entries before the smallest last contributor of the wave's pixels in the
     // image have every pixel live; pixels outside the image have no upstream
@@ -577,11 +839,16 @@ __global__ void __launch_bounds__(Shape<B>::NT, 5) k_composite_bwd(
     const int tid = (int)threadIdx.x;
     // the forward kept the list's head: a tile whose contributors all lie in
     // it reads them from there, any other walks its list again
-    const bool kept = total <= (uint32_t)kTileIds;
-    const uint32_t* __restrict__ head = tids + (size_t)gt * kTileIds;
-    for (uint32_t rel0 = 0; rel0 < total;) {
+    bool kept = SEG ? true : total <= (uint32_t)tile_ids;
+    const uint32_t* __restrict__ head = tids + (size_t)gt * tile_ids;
+    for (uint32_t rel0 = first; rel0 < total;) {
         __syncthreads();  // the previous chunk's LDS is no longer read
         int cnt;
+        if (SEG && kept && rel0 >= (uint32_t)tile_ids) {  // past the head: walk to here
+            uint32_t id;
+            for (uint32_t r = 0; r < rel0; r += 64) (void)walk.next(64, s_q, id);
+            kept = false;
+        }
         if (kept) {
             cnt = (int)min((uint32_t)CHUNK, total - rel0);
         } else {
@@ -709,6 +976,153 @@ __global__ void __launch_bounds__(Shape<B>::NT, 5) k_composite_bwd(
     }
 }
 
+// The adjoint of the quadrant kernels: four waves per (tile, segment of its
+// list), a wave per quadrant.  The forward leaves every pixel's transmittance
+// and colour at the segments' starts (chk), so that the segments of a tile run
+// at the same time: a launch lasts as long as 64 entries take, not as long as
+// the longest list.
+template <bool MERGE>
+__global__ void __launch_bounds__(256) k_composite_bwd_quad(
+    const Rec* __restrict__ recs, int N, CoarseLists lists, int static_rows, const ViewParams* __restrict__ views,
+    int v0, int v1, const uint32_t* __restrict__ order, CPtrTable dls, const uint32_t* __restrict__ ncontrib,
+    const float* __restrict__ Cout, const uint32_t* __restrict__ tids, float* __restrict__ g2, QuadSegs segs) {
+    __shared__ QuadStage s_st;
+    __shared__ WalkQueues s_q;
+    __shared__ uint32_t s_ids[kQuadChunk];
+    __shared__ int s_cnt;
+    // the quadrants' sums per splat (slots as in its record) and the splats each
+    // quadrant blended: added up here, so that a record takes one addition per
+    // slot and tile as from a single wave
+    __shared__ float s_part[4][kQuadChunk][kG2Slots];
+    __shared__ unsigned long long s_hit[4];
+    int gt, seg;
+    uint32_t first, end;
+    if (!quad_segment(segs, views, v0, order, gt, seg, first, end)) return;  // uniform
+    const int view = find_view_of_tile(views, v0, v1, gt);
+    const ViewParams& V = views[view];
+    const int tile = gt - V.tile_base;
+    float* __restrict__ g2s = g2 + (size_t)(MERGE && static_rows ? V.static_view : view) * N * kG2Stride;
+    g2 += (size_t)view * N * kG2Stride;
+    const float* __restrict__ dl = dls.p[view];
+    const int tx = tile % V.tiles_x, ty = tile / V.tiles_x;
+    const int tid = (int)threadIdx.x, lane = __lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int px = tx * 16 + (w & 1) * 8 + (lane & 7), py = ty * 16 + (w >> 1) * 8 + (lane >> 3);
+    const float pxc = (float)px + 0.5f, pyc = (float)py + 0.5f;
+    float G0 = 0.f, G1 = 0.f, G2 = 0.f, R = 0.f, T = 1.0f;
+    uint32_t nc = 0u;
+    if (px < V.W && py < V.H) {
+        const size_t HW = (size_t)V.W * V.H, q = (size_t)py * V.W + px;
+        nc = ncontrib[(size_t)V.pix_base + q];
+        if (nc > first) {
+            G0 = dl[q]; G1 = dl[HW + q]; G2 = dl[2 * HW + q];
+            float c0 = Cout[3 * (size_t)V.pix_base + q];
+            float c1 = Cout[3 * (size_t)V.pix_base + HW + q];
+            float c2 = Cout[3 * (size_t)V.pix_base + 2 * HW + q];
+            if (seg > 0) {
+                const float4 k = segs.chk[((size_t)gt * (kQuadSegs - 1) + (seg - 1)) * 256 + tid];
+                T = k.x;
+                c0 -= k.y; c1 -= k.z; c2 -= k.w;
+            }
+            R = G0 * c0 + G1 * c1 + G2 * c2;  // dot(dL/dC, colour from the segment on)
+        }
+    }
+    const uint32_t wave_nc = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(nc));
+    // the record slots of the wave sums, as in k_composite_bwd
+    const int row = lane >> 4, lr = lane & 15;
+    const int comp0 = ((row & 1) << 1) | (row >> 1);
+    const bool alane = lr == 0 || lr == 4 || lr == 8;
+    const int comp = lr == 0 ? comp0 : (lr == 8 ? 4 + comp0 : 8 + row);
+    TileWalk<MERGE> walk;
+    walk.init(lists, V, view, recs, N, super_factor(16), tx, ty);
+    bool walking = false;  // past the kept head: the list is walked again
+    for (uint32_t rel0 = first; rel0 < end;) {
+        int cnt = (int)min((uint32_t)kQuadChunk, end - rel0);
+        if (rel0 + (uint32_t)cnt > (uint32_t)kQuadIds) {  // uniform
+            if (w == 0) {
+                uint32_t id = 0u;
+                for (uint32_t r = 0; !walking && r < rel0; r += kQuadChunk) (void)walk.next(kQuadChunk, s_q, id);
+                const int got = walk.next(cnt, s_q, id);
+                s_ids[lane] = id;
+                if (lane == 0) s_cnt = got;
+            }
+            walking = true;
+            __syncthreads();
+            cnt = s_cnt;
+            if (cnt == 0) break;  // uniform: the list is exhausted
+        }
+        if (w == 0) {
+            uint32_t raw = walking ? s_ids[lane] : (lane < cnt ? tids[(size_t)gt * kQuadIds + rel0 + lane] : 0u);
+            // (a head written by another forward reads no record past the set)
+            if ((MERGE ? (raw & ~kFromStatic) : raw) >= (uint32_t)N) raw = 0u;
+            const Rec r = lane < cnt ? walk.record(raw) : Rec{};
+            quad_stage<MERGE>(r, raw, cnt, tx, ty, 0, s_st);  // (gid keeps the static flag)
+        }
+        __syncthreads();
+        unsigned long long m = wave_nc > rel0 ? uniform64(s_st.mask[0][w]) : 0ull;
+        if (wave_nc > rel0 && wave_nc - rel0 < 64u) m &= (1ull << (wave_nc - rel0)) - 1ull;
+        unsigned long long hit = 0ull;
+        while (m != 0ull) {
+            int j[2] = {0, 0};
+            bool have[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) have[q] = take_bit(m, j[q]);
+            Splat s[2];
+            ColTerm ct[2];
+            float qa2[2], qc2[2], dy[2], G[2], alpha[2];
+            bool ok[2], clamped[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                s[q] = to_splat_wide(s_st.sp[0][j[q]], qa2[q], qc2[q]);
+                ct[q] = eval_col(s[q], px, pxc);
+                ok[q] = eval_pix(s[q], ct[q], square_test<false>(s[q], ct[q], py), pyc, dy[q], G[q], alpha[q],
+                                 clamped[q]) &&
+                        have[q] && rel0 + (uint32_t)j[q] < nc;
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (__builtin_amdgcn_ballot_w64(ok[q]) == 0ull) continue;  // wave-uniform: nothing blends
+                // (the terms of k_composite_bwd's step for one pixel)
+                const float a = ok[q] ? alpha[q] : 0.0f;
+                const float wgt = a * T;
+                const float gc = G0 * s[q].cr + G1 * s[q].cg + G2 * s[q].cb;
+                R = __builtin_fmaf(-wgt, gc, R);
+                const float ioma = __builtin_amdgcn_rcpf(1.0f - alpha[q]);
+                const float da = __builtin_fmaf(T, gc, -(R * ioma));
+                const float e6 = G0 * wgt, e7 = G1 * wgt, e8 = G2 * wgt;
+                const float gz = (ok[q] && !clamped[q]) ? G[q] : 0.0f;
+                const float e5 = da * gz, sdy = e5 * dy[q], e4 = sdy * dy[q];
+                T = next_T(T, a);
+                const float A = ct[q].dx * e5;
+                const float e0 = __builtin_fmaf(qa2[q], A, s[q].qb * sdy);
+                const float e1 = __builtin_fmaf(s[q].qb, A, qc2[q] * sdy);
+                const float e2 = ct[q].dx * A, e3 = ct[q].dx * sdy;
+                const float h = wave_sum9(e0, e1, e2, e3, e4, e5, e6, e7, e8);
+                asm volatile("" ::"v"(h));  // the cross-lane result, before the lane-divergent store
+                hit |= 1ull << j[q];
+                if (alane) s_part[w][j[q]][comp] = h;
+            }
+        }
+        if (lane == 0) s_hit[w] = hit;
+        __syncthreads();
+        const unsigned long long hits[4] = {s_hit[0], s_hit[1], s_hit[2], s_hit[3]};
+        const unsigned long long any = hits[0] | hits[1] | hits[2] | hits[3];
+        // sixteen lanes per splat, twelve of them a slot each
+        for (int k = tid >> 4; k < cnt; k += 16) {
+            const int c = tid & 15;
+            if (((any >> k) & 1ull) == 0ull || c >= kG2Slots) continue;
+            float sum = 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if ((hits[q] >> k) & 1ull) sum += s_part[q][k][c];
+            const uint32_t gid = s_st.sp[0][k].gid;
+            atomicAdd(((MERGE && (gid & kFromStatic)) ? g2s : g2) + (size_t)(gid & ~kFromStatic) * kG2Stride + c, sum);
+        }
+        rel0 += (uint32_t)cnt;
+        if (rel0 < end) __syncthreads();  // uniform: the records and sums are no longer read
+    }
+}
+
 bool composite_supported(int tile, int chunk) {
     return (tile == 8 || tile == 16 || tile == 32) && (chunk == 64 || chunk == 128 || chunk == 256 || chunk == 512);
 }
@@ -733,16 +1147,23 @@ static void launch_timed(void (*k)(P...), int grid, int block, hipStream_t st, h
 template <int B, int C>
 static void fwd_t(const Rec* recs, int N, const CoarseLists& lists, bool merge, const ViewParams* views, int v0,
                   int v1, int n_tiles, const uint32_t* order, const PtrTable& images, float* Tfin,
-                  uint32_t* ncontrib, float* Cout, uint32_t* tcost, uint32_t* thist, uint32_t* tids,
-                  unsigned long long* counters, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+                  uint32_t* ncontrib, float* Cout, uint32_t* tcost, uint32_t* thist, uint32_t* tids, int tile_ids,
+                  float4* chk, Status* status, unsigned long long* counters, hipStream_t st, hipEvent_t e0,
+                  hipEvent_t e1) {
     const bool stats = counters != nullptr;
 #define H4D_FWD(SPLIT)                                                                                            \
     launch_timed(merge ? (stats ? k_composite_fwd<B, C, true, SPLIT, true> : k_composite_fwd<B, C, false, SPLIT, true>) \
                        : (stats ? k_composite_fwd<B, C, true, SPLIT, false>                                         \
                                 : k_composite_fwd<B, C, false, SPLIT, false>),                                      \
                  n_tiles, ShapeF<B, SPLIT>::NT, st, e0, e1, recs, N, lists, views, v0, v1, order, images, Tfin,    \
-                 ncontrib, Cout, tcost, thist, tids, counters)
+                 ncontrib, Cout, tcost, thist, tids, tile_ids, counters)
     if constexpr (B == 16) {
+        if (n_tiles <= kQuadTiles && !stats) {
+            launch_timed(merge ? k_composite_fwd_quad<true> : k_composite_fwd_quad<false>, n_tiles, kQuadThreads, st, e0,
+                         e1, recs, N, lists, views, v0, v1, order, images, Tfin, ncontrib, Cout, tcost, thist, tids, tile_ids,
+                         chk, status);
+            return;
+        }
         if (n_tiles <= kSplitTiles) {
             H4D_FWD(true);
             return;
@@ -754,14 +1175,29 @@ static void fwd_t(const Rec* recs, int N, const CoarseLists& lists, bool merge, 
 template <int B, int C>
 static void bwd_t(const Rec* recs, int N, const CoarseLists& lists, bool merge, int static_rows,
                   const ViewParams* views, int v0, int v1, int n_tiles, const uint32_t* order, const CPtrTable& dls,
-                  const float* Tfin, const uint32_t* ncontrib, const float* Cout, const uint32_t* tids, float* g2,
+                  const float* Tfin, const uint32_t* ncontrib, const float* Cout, const uint32_t* tcost,
+                  const uint32_t* tids, int tile_ids, const float4* chk, const Status* status, float* g2,
                   unsigned long long* counters, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
     constexpr int NT = Shape<B>::NT;
     const bool stats = counters != nullptr;
+    if constexpr (B == 16) {
+        if (chk && !stats) {
+            if (n_tiles <= kQuadBwdTiles)
+                launch_timed(merge ? k_composite_bwd_quad<true> : k_composite_bwd_quad<false>, n_tiles * kQuadSegs, 256,
+                             st, e0, e1, recs, N, lists, static_rows, views, v0, v1, order, dls, ncontrib, Cout, tids, g2,
+                             QuadSegs{n_tiles, tcost, chk, status});
+            else
+                launch_timed(merge ? k_composite_bwd<16, kQuadChunk, false, true, true>
+                                   : k_composite_bwd<16, kQuadChunk, false, false, true>,
+                             n_tiles * kQuadSegs, 64, st, e0, e1, recs, N, lists, static_rows, views, v0, v1, order, dls,
+                             Tfin, ncontrib, Cout, tids, tile_ids, g2, counters, QuadSegs{n_tiles, tcost, chk, status});
+            return;
+        }
+    }
     launch_timed(merge ? (stats ? k_composite_bwd<B, C, true, true> : k_composite_bwd<B, C, false, true>)
                        : (stats ? k_composite_bwd<B, C, true, false> : k_composite_bwd<B, C, false, false>),
                  n_tiles, NT, st, e0, e1, recs, N, lists, static_rows, views, v0, v1, order, dls, Tfin, ncontrib,
-                 Cout, tids, g2, counters);
+                 Cout, tids, tile_ids, g2, counters, QuadSegs{});
 }
 
 // Tile lists written out (for inspection): one wave per tile walks the list as
@@ -851,21 +1287,22 @@ void launch_walk_lists(int tile, const Rec* recs, int N, const CoarseLists& list
 void launch_composite_fwd(int tile, int chunk, const Rec* recs, int N, const CoarseLists& lists, bool merge,
                           const ViewParams* views, int v0, int v1, int n_tiles, const uint32_t* order,
                           const PtrTable& images, float* Tfin, uint32_t* ncontrib, float* Cout, uint32_t* tcost,
-                          uint32_t* thist, uint32_t* tids, unsigned long long* counters, hipStream_t st,
-                          hipEvent_t e0, hipEvent_t e1) {
+                          uint32_t* thist, uint32_t* tids, int tile_ids, float4* chk, Status* status,
+                          unsigned long long* counters, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
     if (n_tiles == 0) return;
     H4D_DISPATCH(fwd_t, recs, N, lists, merge, views, v0, v1, n_tiles, order, images, Tfin, ncontrib, Cout, tcost,
-                 thist, tids, counters, st, e0, e1);
+                 thist, tids, tile_ids, chk, status, counters, st, e0, e1);
 }
 
 void launch_composite_bwd(int tile, int chunk, const Rec* recs, int N, const CoarseLists& lists, bool merge,
                           int static_rows, const ViewParams* views, int v0, int v1, int n_tiles,
                           const uint32_t* order, const CPtrTable& dls, const float* Tfin, const uint32_t* ncontrib,
-                          const float* Cout, const uint32_t* tids, float* g2, unsigned long long* counters,
+                          const float* Cout, const uint32_t* tcost, const uint32_t* tids, int tile_ids,
+                          const float4* chk, const Status* status, float* g2, unsigned long long* counters,
                           hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
     if (n_tiles == 0) return;
     H4D_DISPATCH(bwd_t, recs, N, lists, merge, static_rows, views, v0, v1, n_tiles, order, dls, Tfin, ncontrib,
-                 Cout, tids, g2, counters, st, e0, e1);
+                 Cout, tcost, tids, tile_ids, chk, status, g2, counters, st, e0, e1);
 }
 
 }  // namespace h4d

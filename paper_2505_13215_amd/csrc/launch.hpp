@@ -198,20 +198,26 @@ bool composite_supported(int tile, int chunk);
 // dispatch order, a permutation.  The forward writes, per tile, its last
 // contributor into tcost[global tile] and counts the launch's tiles per
 // cost_bucket into thist[kCostBuckets] (zero on entry) and keeps the first
-// kTileIds entries of each tile's list in tids[global tile][kTileIds] (may be
+// tile_ids entries of each tile's list in tids[global tile][tile_ids] (may be
 // null), which the adjoint reads for tiles whose contributors all lie there.
+// chk (may be null; launches of at most kQuadTiles 16 x 16 tiles, tile_ids =
+// kQuadIds): the pixels' transmittance and colour at the starts of the list's
+// segments after the first, [global tile][kQuadSegs - 1][256]; status: where
+// the forward notes that it wrote them.
 // Non-null e0 / e1 receive the kernel's own start / end time.
 void launch_composite_fwd(int tile, int chunk, const Rec* recs, int N, const CoarseLists& lists, bool merge,
                           const ViewParams* views, int v0, int v1, int n_tiles, const uint32_t* order,
                           const PtrTable& images, float* Tfin, uint32_t* ncontrib, float* Cout, uint32_t* tcost,
-                          uint32_t* thist, uint32_t* tids, unsigned long long* counters, hipStream_t st,
-                          hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+                          uint32_t* thist, uint32_t* tids, int tile_ids, float4* chk, Status* status,
+                          unsigned long long* counters, hipStream_t st, hipEvent_t e0 = nullptr,
+                          hipEvent_t e1 = nullptr);
 // static_rows (merge only): the 3D entries' gradients go to the records of
 // their static group's view instead of the tile's own view.
 void launch_composite_bwd(int tile, int chunk, const Rec* recs, int N, const CoarseLists& lists, bool merge,
                           int static_rows, const ViewParams* views, int v0, int v1, int n_tiles,
                           const uint32_t* order, const CPtrTable& dls, const float* Tfin, const uint32_t* ncontrib,
-                          const float* Cout, const uint32_t* tids, float* g2, unsigned long long* counters,
+                          const float* Cout, const uint32_t* tcost, const uint32_t* tids, int tile_ids,
+                          const float4* chk, const Status* status, float* g2, unsigned long long* counters,
                           hipStream_t st, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // The tile lists of the views [v0, v1) written out: ids (indices into the
 // merged set [4D | 3D]) of tile t (relative to view v0's first tile) at
