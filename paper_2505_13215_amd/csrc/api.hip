@@ -921,6 +921,8 @@ static h4d_status render_backward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d
     // go to its view's records
     const bool want_stats = stats3 || stats4;
     const int static_rows = (L.shared && !want_stats) ? 1 : 0;
+    // the segments' adjoint of few tiles adds into wide records
+    const int wide = quad && !ctx->stats && L.total_tiles <= kQuadBwdTiles ? 1 : 0;
     PassTiles pt;
     pt.n = L.n_passes();
     for (int k = 0; k < pt.n; ++k) pt.tile0[k] = L.vg[L.pass(k).v0].tile_base;
@@ -947,7 +949,7 @@ static h4d_status render_backward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d
                                  at<float>(stt, L.st_T),
                                  at<uint32_t>(stt, L.st_nc), at<float>(stt, L.st_C), at<uint32_t>(stt, L.st_tcost),
                                  at<uint32_t>(stt, L.st_tids), quad ? kQuadIds : kTileIds,
-                                 quad ? at<float4>(stt, L.st_chk) : nullptr, status, g2,
+                                 quad ? at<float4>(stt, L.st_chk) : nullptr, wide, status, g2,
                                  stat_counters(ctx, stt, L),
                                  st, km.a, km.b);
         }
@@ -961,7 +963,7 @@ static h4d_status render_backward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d
                                : SetStats{nullptr, nullptr, nullptr};
     {
         StageScope sc(ctx, st, H4D_STAGE_PREPROCESS_BWD);
-        launch_preprocess_bwd(to_ptr(g3), to_ptr(g4), vp, n_views, at<Rec>(stt, L.st_recs), g2, r3, r4, s3, s4,
+        launch_preprocess_bwd(to_ptr(g3), to_ptr(g4), vp, n_views, at<Rec>(stt, L.st_recs), g2, wide, r3, r4, s3, s4,
                               static_rows, status, st);
     }
     return hip_check(ctx, "render_bwd");

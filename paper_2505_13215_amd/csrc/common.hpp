@@ -85,6 +85,11 @@ constexpr int kTileIds = 256;
 constexpr int kQuadTiles = 2048;
 constexpr int kQuadSegs = 8;
 constexpr int kQuadIds = 64 * kQuadSegs;
+// The adjoint takes four waves per segment (one pixel per lane, culled by
+// quadrant) up to this many tiles, one (four pixels per lane) beyond: 336 tiles
+// 0.040 against 0.052 ms, 1200 tiles 0.074-0.085 against 0.075-0.080 ms, 1900 tiles
+// 0.112 against 0.094 ms (before segments 0.215, 0.133-0.140 and 0.121 ms).
+constexpr int kQuadBwdTiles = 1000;
 
 // Layout of a pass's depth-ordered entries: na segments of la entries (the
 // views v0 .. v0 + na - 1, all their Gaussians, or only the 4D ones when the
@@ -105,6 +110,29 @@ struct SegLayout {
 // add their 3D gradients into the records of the group's view.
 constexpr int kG2Stride = 16;
 constexpr int kG2Slots = 12;
+// Calls with the quadrant kernels' checkpoints keep wide records in the same
+// 64 bytes: du dv dQ00 dQ01 dQ11 dop as doubles, then dr dg db as floats.  Their
+// additions come from many short workgroups in no steady order, and a thin
+// splat's gradient is a small difference of large sums, so that their rounding
+// in float32 would show from run to run.
+constexpr int kG2Wide = 6;
+
+struct ScreenGrad {
+    double v[9];  // du dv dQ00 dQ01 dQ11 dop dr dg db
+};
+__device__ __forceinline__ ScreenGrad load_screen_grad(const float* rec, int wide) {
+    ScreenGrad g;
+    if (wide) {
+        const double* d = reinterpret_cast<const double*>(rec);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) g.v[k] = k < kG2Wide ? d[k] : (double)rec[kG2Wide + k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) g.v[k] = (double)rec[k];
+        g.v[8] = (double)rec[8] + rec[9] + rec[10] + rec[11];
+    }
+    return g;
+}
 
 // Per-view device pointers passed by value to the batched kernels.
 struct PtrTable {
@@ -180,10 +208,10 @@ struct SetStats {
 };
 
 // One view's share: the image-plane gradient (pixels) of the centre, scale
-// times (e0, e1), in normalised device coordinates (half the image size per
+// times e's first two, in normalised device coordinates (half the image size per
 // unit).
-__device__ inline double ndc_grad_norm(float e0, float e1, double scale, int W, int H) {
-    const double gx = (double)e0 * scale * (0.5 * (double)W), gy = (double)e1 * scale * (0.5 * (double)H);
+__device__ inline double ndc_grad_norm(const ScreenGrad& e, double scale, int W, int H) {
+    const double gx = e.v[0] * scale * (0.5 * (double)W), gy = e.v[1] * scale * (0.5 * (double)H);
     return sqrt(gx * gx + gy * gy);
 }
 

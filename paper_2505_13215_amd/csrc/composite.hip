@@ -453,11 +453,6 @@ __global__ void __launch_bounds__((ShapeF<B, SPLIT>::NT), (FwdWaves<B, SPLIT, ME
 // between.
 constexpr int kQuadChunk = 64;                 // one list entry per lane of the staging wave
 constexpr int kQuadThreads = 5 * 64;
-// The adjoint takes four waves per segment (one pixel per lane, culled by
-// quadrant) up to this many tiles, one (four pixels per lane) beyond: 336 tiles
-// 0.040 against 0.052 ms, 1200 tiles 0.074-0.085 against 0.075-0.080 ms, 1900 tiles
-// 0.112 against 0.094 ms (before segments 0.215, 0.133-0.140 and 0.121 ms).
-constexpr int kQuadBwdTiles = 1000;
 
 struct QuadStage {
     LSplat sp[2][kQuadChunk];
@@ -1107,16 +1102,21 @@ __global__ void __launch_bounds__(256) k_composite_bwd_quad(
         __syncthreads();
         const unsigned long long hits[4] = {s_hit[0], s_hit[1], s_hit[2], s_hit[3]};
         const unsigned long long any = hits[0] | hits[1] | hits[2] | hits[3];
-        // sixteen lanes per splat, twelve of them a slot each
+        // sixteen lanes per splat, nine of them a value each, into wide records
         for (int k = tid >> 4; k < cnt; k += 16) {
             const int c = tid & 15;
-            if (((any >> k) & 1ull) == 0ull || c >= kG2Slots) continue;
+            if (((any >> k) & 1ull) == 0ull || c > 8) continue;
             float sum = 0.f;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if ((hits[q] >> k) & 1ull) sum += s_part[q][k][c];
+                if ((hits[q] >> k) & 1ull) {
+                    const float* p = s_part[q][k];
+                    sum += c < 8 ? p[c] : (p[8] + p[9]) + (p[10] + p[11]);
+                }
             const uint32_t gid = s_st.sp[0][k].gid;
-            atomicAdd(((MERGE && (gid & kFromStatic)) ? g2s : g2) + (size_t)(gid & ~kFromStatic) * kG2Stride + c, sum);
+            float* rec = ((MERGE && (gid & kFromStatic)) ? g2s : g2) + (size_t)(gid & ~kFromStatic) * kG2Stride;
+            if (c < kG2Wide) atomicAdd(reinterpret_cast<double*>(rec) + c, (double)sum);
+            else atomicAdd(rec + kG2Wide + c, sum);
         }
         rel0 += (uint32_t)cnt;
         if (rel0 < end) __syncthreads();  // uniform: the records and sums are no longer read
@@ -1176,13 +1176,13 @@ template <int B, int C>
 static void bwd_t(const Rec* recs, int N, const CoarseLists& lists, bool merge, int static_rows,
                   const ViewParams* views, int v0, int v1, int n_tiles, const uint32_t* order, const CPtrTable& dls,
                   const float* Tfin, const uint32_t* ncontrib, const float* Cout, const uint32_t* tcost,
-                  const uint32_t* tids, int tile_ids, const float4* chk, const Status* status, float* g2,
+                  const uint32_t* tids, int tile_ids, const float4* chk, int wide, const Status* status, float* g2,
                   unsigned long long* counters, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
     constexpr int NT = Shape<B>::NT;
     const bool stats = counters != nullptr;
     if constexpr (B == 16) {
         if (chk && !stats) {
-            if (n_tiles <= kQuadBwdTiles)
+            if (wide)
                 launch_timed(merge ? k_composite_bwd_quad<true> : k_composite_bwd_quad<false>, n_tiles * kQuadSegs, 256,
                              st, e0, e1, recs, N, lists, static_rows, views, v0, v1, order, dls, ncontrib, Cout, tids, g2,
                              QuadSegs{n_tiles, tcost, chk, status});
@@ -1298,11 +1298,11 @@ void launch_composite_bwd(int tile, int chunk, const Rec* recs, int N, const Coa
                           int static_rows, const ViewParams* views, int v0, int v1, int n_tiles,
                           const uint32_t* order, const CPtrTable& dls, const float* Tfin, const uint32_t* ncontrib,
                           const float* Cout, const uint32_t* tcost, const uint32_t* tids, int tile_ids,
-                          const float4* chk, const Status* status, float* g2, unsigned long long* counters,
+                          const float4* chk, int wide, const Status* status, float* g2, unsigned long long* counters,
                           hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
     if (n_tiles == 0) return;
     H4D_DISPATCH(bwd_t, recs, N, lists, merge, static_rows, views, v0, v1, n_tiles, order, dls, Tfin, ncontrib,
-                 Cout, tcost, tids, tile_ids, chk, status, g2, counters, st, e0, e1);
+                 Cout, tcost, tids, tile_ids, chk, wide, status, g2, counters, st, e0, e1);
 }
 
 }  // namespace h4d

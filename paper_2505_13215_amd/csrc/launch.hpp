@@ -42,9 +42,9 @@ void launch_preprocess(const G3Ptr& g3, const G4Ptr& g4, const ViewParams* views
                        Rec* recs, uint32_t* dkeys, uint32_t* dvals, float* g2, hipStream_t st);
 // static_rows: the adjoint added each static group's 3D gradients into the
 // records of the group's view (no statistics then).  Marks g2 used
-// (status->g2_dirty).
+// (status->g2_dirty).  wide: the records' form (kG2Wide).
 void launch_preprocess_bwd(const G3Ptr& g3, const G4Ptr& g4, const ViewParams* views, int n_views, const Rec* recs,
-                           const float* g2, const G3Grad& gr3, const G4Grad& gr4, const SetStats& st3,
+                           const float* g2, int wide, const G3Grad& gr3, const G4Grad& gr4, const SetStats& st3,
                            const SetStats& st4, int static_rows, Status* status, hipStream_t st);
 void launch_splats_to_records(int n, const float* u, const float* v, const float* conic, const float* opacity,
                               const float* rgb, const int32_t* radius, const float* depth, const uint8_t* visible,
@@ -203,7 +203,8 @@ bool composite_supported(int tile, int chunk);
 // chk (may be null; launches of at most kQuadTiles 16 x 16 tiles, tile_ids =
 // kQuadIds): the pixels' transmittance and colour at the starts of the list's
 // segments after the first, [global tile][kQuadSegs - 1][256]; status: where
-// the forward notes that it wrote them.
+// the forward notes that it wrote them; wide (adjoint): four waves per segment,
+// into wide records (kG2Wide).
 // Non-null e0 / e1 receive the kernel's own start / end time.
 void launch_composite_fwd(int tile, int chunk, const Rec* recs, int N, const CoarseLists& lists, bool merge,
                           const ViewParams* views, int v0, int v1, int n_tiles, const uint32_t* order,
@@ -217,7 +218,7 @@ void launch_composite_bwd(int tile, int chunk, const Rec* recs, int N, const Coa
                           int static_rows, const ViewParams* views, int v0, int v1, int n_tiles,
                           const uint32_t* order, const CPtrTable& dls, const float* Tfin, const uint32_t* ncontrib,
                           const float* Cout, const uint32_t* tcost, const uint32_t* tids, int tile_ids,
-                          const float4* chk, const Status* status, float* g2, unsigned long long* counters,
+                          const float4* chk, int wide, const Status* status, float* g2, unsigned long long* counters,
                           hipStream_t st, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // The tile lists of the views [v0, v1) written out: ids (indices into the
 // merged set [4D | 3D]) of tile t (relative to view v0's first tile) at

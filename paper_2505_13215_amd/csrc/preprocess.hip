@@ -352,7 +352,7 @@ __global__ void __launch_bounds__(256) k_preprocess(G3Ptr g3, G4Ptr g4, const Vi
 // Backward kernel: one thread per Gaussian, looping over the views of the call
 // (no atomics: every view's contribution to a Gaussian lands in one lane).
 // g2: per (view, Gaussian) screen-space gradients from the blending adjoint,
-// layout [view][N][kG2Stride]: du dv dQ00 dQ01 dQ11 dop dr dg, then db as
+// layout [view][N][kG2Stride], in doubles when wide, else: du dv dQ00 dQ01 dQ11 dop dr dg, then db as
 // four parts (w.r.t. the unscaled conic entries, Q01 counted once; the first
 // five without their factors -op / log2 e, -op / log2 e, -op / 2, -op, -op / 2).
 //
@@ -366,17 +366,15 @@ __global__ void __launch_bounds__(256) k_preprocess(G3Ptr g3, G4Ptr g4, const Vi
 // separate instantiation, so that sets without them compile as plain SH).
 template <bool TIME>
 __device__ inline void proj_bwd(const ViewParams& V, const WorldF& w, const ProjF& p, const float* shp, int shn,
-                                int shi, const float* g2, size_t gstride, double gmu[3], double Sb[3][3],
+                                int shi, const ScreenGrad& e, double gmu[3], double Sb[3][3],
                                 double& gop, float* gsh, const TimeColour* tc = nullptr, double* gmt = nullptr) {
     // the blending adjoint sums the centre and conic terms without their
     // constant factors and the effective opacity: du, dv take -op / log2 e,
     // dQ00, dQ11 -op / 2, dQ01 -op
     const double ku = -kLn2 * w.op, kq = -0.5 * w.op;
-    const double gu = ku * g2[0], gv = ku * g2[gstride], gQa = kq * g2[2 * gstride], gQb = -w.op * g2[3 * gstride],
-                 gQc = kq * g2[4 * gstride];
-    gop = g2[5 * gstride];
-    const double grgb[3] = {g2[6 * gstride], g2[7 * gstride],
-                            (double)g2[8 * gstride] + g2[9 * gstride] + g2[10 * gstride] + g2[11 * gstride]};
+    const double gu = ku * e.v[0], gv = ku * e.v[1], gQa = kq * e.v[2], gQb = -w.op * e.v[3], gQc = kq * e.v[4];
+    gop = e.v[5];
+    const double grgb[3] = {e.v[6], e.v[7], e.v[8]};
     // colour
     double Y[16], raw[3];
     sh_eval(p.dir[0], p.dir[1], p.dir[2], Y);
@@ -467,7 +465,7 @@ __device__ inline void unit_bwd(const double qh[4], double nrm, const double gqh
 
 template <bool TIME>
 __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restrict__ views, int n_views, int N,
-                              const Rec* __restrict__ recs, const float* __restrict__ g2, const G4Grad& gr,
+                              const Rec* __restrict__ recs, const float* __restrict__ g2, int wide, const G4Grad& gr,
                               const SetStats& st) {
     const size_t n = (size_t)g4.n;
     double s[4], ql[4], qr[4];
@@ -516,9 +514,9 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restri
         for (int r = 0; r < 3; ++r)
             for (int k = 0; k < 3; ++k) w.S[r][k] = S4[r][k] - b[r] * b[k] * ic;
         w.op = sig * pt;
+        const ScreenGrad e = load_screen_grad(g2 + ((size_t)v * N + i) * kG2Stride, wide);
         if (st.grad || st.vis || st.step_vis) {
-            const float* e = g2 + ((size_t)v * N + i) * kG2Stride;
-            stat_g += ndc_grad_norm(e[0], e[1], kLn2 * w.op, V.W, V.H);
+            stat_g += ndc_grad_norm(e, kLn2 * w.op, V.W, V.H);
             ++stat_n;
         }
         ProjF p;
@@ -530,10 +528,10 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restri
             tc.i = i;
             tc.gsht = gr.sh_t;
             time_weights(g4, i, V.time, tc.w, tc.dw);
-            proj_bwd<true>(V, w, p, g4.sh, g4.n, i, g2 + ((size_t)v * N + i) * kG2Stride, 1, gmc, Sb, gop, gsh, &tc,
+            proj_bwd<true>(V, w, p, g4.sh, g4.n, i, e, gmc, Sb, gop, gsh, &tc,
                            &gmt);
         } else {
-            proj_bwd<false>(V, w, p, g4.sh, g4.n, i, g2 + ((size_t)v * N + i) * kG2Stride, 1, gmc, Sb, gop, gsh);
+            proj_bwd<false>(V, w, p, g4.sh, g4.n, i, e, gmc, Sb, gop, gsh);
         }
         // effective opacity sigma * p(t); p(t) = exp(-delta^2 / (2 c))
         gsig += gop * pt;
@@ -606,7 +604,7 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restri
 }
 
 __device__ inline void bwd_3d(const G3Ptr& g3, int i, int gidx, const ViewParams* __restrict__ views, int n_views,
-                              int N, const Rec* __restrict__ recs, const float* __restrict__ g2, const G3Grad& gr,
+                              int N, const Rec* __restrict__ recs, const float* __restrict__ g2, int wide, const G3Grad& gr,
                               const SetStats& st, int static_rows) {
     const size_t n = (size_t)g3.n;
     WorldF w;
@@ -627,28 +625,20 @@ __device__ inline void bwd_3d(const G3Ptr& g3, int i, int gidx, const ViewParams
         if (recs[(size_t)v * N + gidx].d.w == 0u) continue;  // covers no pixel in this camera
         // (a view alone, or the group's sum already in its record: that record
         // as it is; otherwise the members' records summed here)
-        float e[kG2Slots];
-        for (int k = 0; k < kG2Slots; ++k) e[k] = 0.f;
-        const float* direct = nullptr;
-        if (static_rows || V.static_next < 0) {
-            direct = g2 + ((size_t)v * N + gidx) * kG2Stride;
+        ScreenGrad e{};
+        const bool direct = static_rows || V.static_next < 0;
+        for (int u = v; u >= 0; u = direct ? -1 : views[u].static_next) {
+            const ScreenGrad g = load_screen_grad(g2 + ((size_t)u * N + gidx) * kG2Stride, wide);
             if (st.grad || st.vis || st.step_vis) {
-                stat_g += ndc_grad_norm(direct[0], direct[1], kLn2 * w.op, V.W, V.H);
+                stat_g += ndc_grad_norm(g, kLn2 * w.op, views[u].W, views[u].H);
                 ++stat_n;
             }
-        }
-        for (int u = direct ? -1 : v; u >= 0; u = views[u].static_next) {
-            const float* g = g2 + ((size_t)u * N + gidx) * kG2Stride;
-            if (st.grad || st.vis || st.step_vis) {
-                stat_g += ndc_grad_norm(g[0], g[1], kLn2 * w.op, views[u].W, views[u].H);
-                ++stat_n;
-            }
-            for (int k = 0; k < kG2Slots; ++k) e[k] += g[k];
+            for (int k = 0; k < 9; ++k) e.v[k] += g.v[k];
         }
         ProjF p;
         project(V, w, p);
         double gmc[3], Sb[3][3], gop;
-        proj_bwd<false>(V, w, p, g3.sh, g3.n, i, direct ? direct : e, 1, gmc, Sb, gop, gsh);
+        proj_bwd<false>(V, w, p, g3.sh, g3.n, i, e, gmc, Sb, gop, gsh);
         gsig += gop;
         for (int r = 0; r < 3; ++r) {
             gmu[r] += gmc[r];
@@ -691,17 +681,17 @@ __device__ inline void bwd_3d(const G3Ptr& g3, int i, int gidx, const ViewParams
 template <bool TIME>
 __global__ void __launch_bounds__(128) k_preprocess_bwd(G3Ptr g3, G4Ptr g4, int nb4, const ViewParams* __restrict__ views,
                                                         int n_views, const Rec* __restrict__ recs,
-                                                        const float* __restrict__ g2, G3Grad gr3, G4Grad gr4,
+                                                        const float* __restrict__ g2, int wide, G3Grad gr3, G4Grad gr4,
                                                         SetStats st3, SetStats st4, int static_rows,
                                                         Status* status) {
     const int N = g3.n + g4.n;
     if (blockIdx.x == 0 && threadIdx.x == 0) status->g2_dirty = 1ull;  // (read by the next backward's prologue)
     if ((int)blockIdx.x < nb4) {
         const int g = blockIdx.x * blockDim.x + threadIdx.x;
-        if (g < g4.n) bwd_4d<TIME>(g4, g, views, n_views, N, recs, g2, gr4, st4);
+        if (g < g4.n) bwd_4d<TIME>(g4, g, views, n_views, N, recs, g2, wide, gr4, st4);
     } else {
         const int i = (blockIdx.x - nb4) * blockDim.x + threadIdx.x;
-        if (i < g3.n) bwd_3d(g3, i, g4.n + i, views, n_views, N, recs, g2, gr3, st3, static_rows);
+        if (i < g3.n) bwd_3d(g3, i, g4.n + i, views, n_views, N, recs, g2, wide, gr3, st3, static_rows);
     }
 }
 
@@ -775,16 +765,16 @@ void launch_preprocess(const G3Ptr& g3, const G4Ptr& g4, const ViewParams* views
 }
 
 void launch_preprocess_bwd(const G3Ptr& g3, const G4Ptr& g4, const ViewParams* views, int n_views, const Rec* recs,
-                           const float* g2, const G3Grad& gr3, const G4Grad& gr4, const SetStats& st3,
+                           const float* g2, int wide, const G3Grad& gr3, const G4Grad& gr4, const SetStats& st3,
                            const SetStats& st4, int static_rows, Status* status, hipStream_t st) {
     const int N = g3.n + g4.n;
     const int nb4 = ceil_div(g4.n, 128), nb3 = ceil_div(g3.n, 128);
     const int nb = std::max(1, nb4 + nb3);  // (one workgroup at least: it marks the records used)
     if (g4.sh_t_deg > 0 && N > 0)
-        k_preprocess_bwd<true><<<nb, 128, 0, st>>>(g3, g4, nb4, views, n_views, recs, g2, gr3, gr4, st3, st4,
+        k_preprocess_bwd<true><<<nb, 128, 0, st>>>(g3, g4, nb4, views, n_views, recs, g2, wide, gr3, gr4, st3, st4,
                                                    static_rows, status);
     else
-        k_preprocess_bwd<false><<<nb, 128, 0, st>>>(g3, g4, nb4, views, n_views, recs, g2, gr3, gr4, st3, st4,
+        k_preprocess_bwd<false><<<nb, 128, 0, st>>>(g3, g4, nb4, views, n_views, recs, g2, wide, gr3, gr4, st3, st4,
                                                     static_rows, status);
 }
 
