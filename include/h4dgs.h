@@ -301,6 +301,18 @@ h4d_status h4dgs_convert_static(h4d_ctx *ctx, const h4d_g4d *in4, const h4d_g3d 
                                 h4d_g4d_mut *out4, h4d_g3d_mut *out3, int32_t *perm, int32_t *n4_out,
                                 int32_t *n3_out, void *scratch, size_t scratch_bytes, void *stream);
 
+/* The same conversion in two calls, for outputs of the exact size.
+ * h4dgs_convert_plan writes perm and the row counts (synchronises `stream`);
+ * h4dgs_convert_rows, with those, moves the rows of one pair of sets: the
+ * parameters (moments = 0) or moment arrays laid out like them (moments = 1:
+ * zeros for a converted row's quaternion).  out4->n >= n4_out and out3->n >=
+ * n3_out are the outputs' row strides.  Enqueued on `stream`. */
+h4d_status h4dgs_convert_plan(h4d_ctx *ctx, const h4d_g4d *in4, const h4d_g3d *in3, float tau, int32_t *perm,
+                              int32_t *n4_out, int32_t *n3_out, void *scratch, size_t scratch_bytes, void *stream);
+h4d_status h4dgs_convert_rows(h4d_ctx *ctx, const h4d_g4d *in4, const h4d_g3d *in3, const int32_t *perm,
+                              int32_t n4_out, int32_t n3_out, int32_t moments, h4d_g4d_mut *out4,
+                              h4d_g3d_mut *out3, void *stream);
+
 /* Adaptive densification and pruning, run on the 3D and the 4D set
  * separately with limits of their own (Sec. 4.3 adopts the clone / split /
  * prune scheme of 3D Gaussian Splatting and applies it to each set; the paper
@@ -341,6 +353,23 @@ h4d_status h4dgs_densify(h4d_ctx *ctx, const h4d_g3d *in3, const h4d_g4d *in4, c
                          const h4d_densify_params *p3, const h4d_densify_params *p4, h4d_g3d_mut *out3,
                          h4d_g4d_mut *out4, int32_t *src3, int32_t *src4, int32_t *n3_out, int32_t *n4_out,
                          void *scratch, size_t scratch_bytes, void *stream);
+
+/* The same densification in two calls, for outputs of the exact size.
+ * h4dgs_densify_plan counts the rows: counts (host) receives kept originals,
+ * clones and split rows of the 3D set, then of the 4D set (synchronises
+ * `stream`); a set's output has counts[0] + counts[1] + split_n counts[2] rows.
+ * h4dgs_densify_rows, with the same inputs, counts and scratch (unchanged in
+ * between), writes outputs and sources of at least that many rows.  Enqueued on
+ * `stream`. */
+h4d_status h4dgs_densify_plan(h4d_ctx *ctx, const h4d_g3d *in3, const h4d_g4d *in4, const h4d_set_stats *stats3,
+                              const h4d_set_stats *stats4, const h4d_densify_params *p3,
+                              const h4d_densify_params *p4, int32_t *counts, void *scratch, size_t scratch_bytes,
+                              void *stream);
+h4d_status h4dgs_densify_rows(h4d_ctx *ctx, const h4d_g3d *in3, const h4d_g4d *in4, const h4d_set_stats *stats3,
+                              const h4d_set_stats *stats4, const float *noise3, const float *noise4,
+                              const h4d_densify_params *p3, const h4d_densify_params *p4, const int32_t *counts,
+                              h4d_g3d_mut *out3, h4d_g4d_mut *out4, int32_t *src3, int32_t *src4, void *scratch,
+                              size_t scratch_bytes, void *stream);
 
 /* Optimiser state across densification: out row r of a set takes row
  * src[r] of the input arrays (laid out as the parameters) when src[r] >= 0,

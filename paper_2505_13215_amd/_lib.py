@@ -30,6 +30,7 @@ EXPORTS = (
     "h4dgs_profile", "h4dgs_profile_read", "h4dgs_stats", "h4dgs_stats_read", "h4dgs_radix_hist_words",
     "h4dgs_radix_pass_check", "h4dgs_render_infer_noalloc", "h4dgs_convert_moments", "h4dgs_render_bwd_stats",
     "h4dgs_densify_scratch_bytes", "h4dgs_densify", "h4dgs_gather_rows", "h4dgs_adam_masked", "h4dgs_tile_lists",
+    "h4dgs_convert_plan", "h4dgs_convert_rows", "h4dgs_densify_plan", "h4dgs_densify_rows",
 )
 
 NOALLOC_BYTES = 256 << 20  # H4DGS_NOALLOC_BYTES
@@ -104,6 +105,10 @@ def load(path: str = LIB_PATH):
     L.h4dgs_convert_scratch_bytes.restype = sz
     L.h4dgs_convert_static.argtypes = [vp, vp, vp, f32, vp, vp, vp, P(i32), P(i32), vp, sz, vp]
     L.h4dgs_convert_moments.argtypes = [vp, vp, vp, vp, vp, vp, vp]
+    L.h4dgs_convert_plan.argtypes = [vp, vp, vp, f32, vp, P(i32), P(i32), vp, sz, vp]
+    L.h4dgs_convert_rows.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp, vp, vp]
+    L.h4dgs_densify_plan.argtypes = [vp, vp, vp, vp, vp, vp, vp, P(i32), vp, sz, vp]
+    L.h4dgs_densify_rows.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, P(i32), vp, vp, vp, vp, vp, sz, vp]
     L.h4dgs_render_bwd_stats.argtypes = [vp, vp, vp, vp, i32, vp, vp, vp, sz, vp, sz, vp, vp, vp, vp, vp]
     L.h4dgs_densify_scratch_bytes.argtypes = [i32, i32]
     L.h4dgs_densify_scratch_bytes.restype = sz

@@ -118,6 +118,14 @@ h4d_status hip_check(h4d_ctx* c, const char* where) {
     return H4D_OK;
 }
 
+// Copies a few words behind the work enqueued on `st` to the host (synchronises).
+h4d_status read_back(h4d_ctx* c, void* dst, const void* src, size_t bytes, hipStream_t st, const char* where) {
+    if (hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+        return hip_check(c, where);
+    return H4D_OK;
+}
+
 constexpr size_t kAlign = 256;
 constexpr size_t kPixelAlign = (size_t)1 << 21;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -1083,6 +1091,76 @@ size_t h4dgs_convert_scratch_bytes(int32_t n4) {
     return align_up(8 * n) + align_up(16 * (n + 1)) + align_up(16 * (nb + 1)) + align_up(16);
 }
 
+namespace {
+G4Grad to_grad4(const h4d_g4d_mut* g) {
+    return G4Grad{g->n, g->mean, g->mean_t, g->log_scale, g->quat_l, g->quat_r, g->opacity, g->sh, g->sh_t};
+}
+G3Grad to_grad3(const h4d_g3d_mut* g) { return G3Grad{g->n, g->mean, g->log_scale, g->quat, g->opacity, g->sh}; }
+bool has_arrays4(const h4d_g4d_mut* g) {
+    return g->mean && g->mean_t && g->log_scale && g->quat_l && g->quat_r && g->opacity && g->sh;
+}
+bool has_arrays3(const h4d_g3d_mut* g) { return g->mean && g->log_scale && g->quat && g->opacity && g->sh; }
+
+h4d_status check_no_alias(h4d_ctx* ctx, const h4d_g4d* in4, const h4d_g3d* in3, const h4d_g4d_mut* out4,
+                          const h4d_g3d_mut* out3) {
+    if ((in3->n > 0 && (const void*)out3->mean == (const void*)in3->mean) ||
+        (in4->n > 0 && (const void*)out4->mean == (const void*)in4->mean))
+        return fail(ctx, H4D_ERR_INVALID_ARG, "outputs must not alias inputs");
+    return H4D_OK;
+}
+
+// The order of a conversion's rows: perm enqueued, the counts read back
+// (synchronises).
+h4d_status convert_plan(h4d_ctx* ctx, const h4d_g4d* in4, int n3, float tau, int32_t* perm, int32_t* n4_out,
+                        int32_t* n3_out, void* scratch, hipStream_t st) {
+    unsigned long long* partials = at<unsigned long long>(scratch, 0);
+    const int nb = scan_blocks(in4->n);
+    launch_convert_plan(to_ptr(in4), n3, std::log((double)tau), perm, partials, st);
+    h4d_status s;
+    if ((s = hip_check(ctx, "convert_static")) != H4D_OK) return s;
+    unsigned long long conv = 0;
+    if ((s = read_back(ctx, &conv, partials + nb, sizeof(conv), st, "convert_static: count readback")) != H4D_OK) return s;
+    *n4_out = in4->n - (int32_t)conv;
+    *n3_out = n3 + (int32_t)conv;
+    return H4D_OK;
+}
+}  // namespace
+
+h4d_status h4dgs_convert_plan(h4d_ctx* ctx, const h4d_g4d* in4, const h4d_g3d* in3, float tau, int32_t* perm,
+                              int32_t* n4_out, int32_t* n3_out, void* scratch, size_t scratch_bytes, void* stream) {
+    if (!ctx) return H4D_ERR_INVALID_ARG;
+    h4d_status s;
+    if ((s = check_sets(ctx, in3, in4)) != H4D_OK) return s;
+    if (!n4_out || !n3_out || (in4->n > 0 && !perm)) return fail(ctx, H4D_ERR_INVALID_ARG, "null output");
+    if (!(tau > 0.f) || !std::isfinite(tau)) return fail(ctx, H4D_ERR_INVALID_ARG, "tau must be finite and > 0");
+    const size_t need = h4dgs_convert_scratch_bytes(in4->n);
+    if (!scratch || scratch_bytes < need)
+        return fail(ctx, H4D_ERR_INVALID_ARG, "scratch too small (%zu < %zu)", scratch_bytes, need);
+    return convert_plan(ctx, in4, in3->n, tau, perm, n4_out, n3_out, scratch, static_cast<hipStream_t>(stream));
+}
+
+h4d_status h4dgs_convert_rows(h4d_ctx* ctx, const h4d_g4d* in4, const h4d_g3d* in3, const int32_t* perm,
+                              int32_t n4_out, int32_t n3_out, int32_t moments, h4d_g4d_mut* out4, h4d_g3d_mut* out3,
+                              void* stream) {
+    if (!ctx) return H4D_ERR_INVALID_ARG;
+    h4d_status s;
+    if ((s = check_sets(ctx, in3, in4)) != H4D_OK) return s;
+    if (!out4 || !out3) return fail(ctx, H4D_ERR_INVALID_ARG, "null output");
+    if (n4_out < 0 || n4_out > in4->n || (int64_t)n3_out != (int64_t)in3->n + in4->n - n4_out)
+        return fail(ctx, H4D_ERR_INVALID_ARG, "row counts %d, %d are not of a conversion of %d 4D and %d 3D rows", n4_out,
+                    n3_out, in4->n, in3->n);
+    if (out4->n < n4_out) return fail(ctx, H4D_ERR_CAPACITY, "out4 capacity %d < %d", out4->n, n4_out);
+    if (out3->n < n3_out) return fail(ctx, H4D_ERR_CAPACITY, "out3 capacity %d < %d", out3->n, n3_out);
+    if (in4->n > 0 && !perm) return fail(ctx, H4D_ERR_INVALID_ARG, "perm is null");
+    if (n4_out > 0 && !has_arrays4(out4)) return fail(ctx, H4D_ERR_INVALID_ARG, "null 4D output array");
+    if (n3_out > 0 && !has_arrays3(out3)) return fail(ctx, H4D_ERR_INVALID_ARG, "null 3D output array");
+    if ((s = check_no_alias(ctx, in4, in3, out4, out3)) != H4D_OK) return s;
+    if ((s = check_time_out(ctx, in4, out4, n4_out, "convert_rows")) != H4D_OK) return s;
+    launch_convert_rows(to_ptr(in4), to_ptr(in3), perm, to_grad4(out4), to_grad3(out3), moments ? 1 : 0,
+                        static_cast<hipStream_t>(stream));
+    return hip_check(ctx, "convert_rows");
+}
+
 h4d_status h4dgs_convert_static(h4d_ctx* ctx, const h4d_g4d* in4, const h4d_g3d* in3, float tau, h4d_g4d_mut* out4,
                                 h4d_g3d_mut* out3, int32_t* perm, int32_t* n4_out, int32_t* n3_out, void* scratch,
                                 size_t scratch_bytes, void* stream) {
@@ -1094,40 +1172,18 @@ h4d_status h4dgs_convert_static(h4d_ctx* ctx, const h4d_g4d* in4, const h4d_g3d*
     if (out4->n < in4->n) return fail(ctx, H4D_ERR_CAPACITY, "out4 capacity %d < %d", out4->n, in4->n);
     if ((int64_t)out3->n < (int64_t)in3->n + in4->n)
         return fail(ctx, H4D_ERR_CAPACITY, "out3 capacity %d < %d", out3->n, in3->n + in4->n);
-    if (in4->n > 0 && (!perm || !out4->mean || !out4->mean_t || !out4->log_scale || !out4->quat_l || !out4->quat_r ||
-                       !out4->opacity || !out4->sh))
-        return fail(ctx, H4D_ERR_INVALID_ARG, "null 4D output array");
-    if (out3->n > 0 && (!out3->mean || !out3->log_scale || !out3->quat || !out3->opacity || !out3->sh))
-        return fail(ctx, H4D_ERR_INVALID_ARG, "null 3D output array");
-    if ((in3->n > 0 && (const void*)out3->mean == (const void*)in3->mean) ||
-        (in4->n > 0 && (const void*)out4->mean == (const void*)in4->mean))
-        return fail(ctx, H4D_ERR_INVALID_ARG, "outputs must not alias inputs");
+    if (in4->n > 0 && (!perm || !has_arrays4(out4))) return fail(ctx, H4D_ERR_INVALID_ARG, "null 4D output array");
+    if (out3->n > 0 && !has_arrays3(out3)) return fail(ctx, H4D_ERR_INVALID_ARG, "null 3D output array");
+    if ((s = check_no_alias(ctx, in4, in3, out4, out3)) != H4D_OK) return s;
     if ((s = check_time_out(ctx, in4, out4, in4->n, "convert_static")) != H4D_OK) return s;
-    const int n4 = in4->n;
-    const size_t need = h4dgs_convert_scratch_bytes(n4);
+    const size_t need = h4dgs_convert_scratch_bytes(in4->n);
     if (!scratch || scratch_bytes < need) return fail(ctx, H4D_ERR_INVALID_ARG, "scratch too small (%zu < %zu)",
                                                      scratch_bytes, need);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const size_t n = (size_t)n4;
-    const size_t nb = (size_t)std::max(1, scan_blocks(n4));
-    Carve c;
-    const size_t o_flags = c.take(8 * n), o_scan = c.take(16 * (n + 1)), o_part = c.take(16 * (nb + 1)),
-                 o_cnt = c.take(16);
-    const G4Grad o4{out4->n,  out4->mean,    out4->mean_t, out4->log_scale, out4->quat_l, out4->quat_r,
-                    out4->opacity, out4->sh, out4->sh_t};
-    const G3Grad o3{out3->n, out3->mean, out3->log_scale, out3->quat, out3->opacity, out3->sh};
-    const double log_tau = std::log((double)tau);
-    int32_t* dcounts = at<int32_t>(scratch, o_cnt);
-    launch_convert_static(to_ptr(in4), to_ptr(in3), log_tau, o4, o3, perm, at<uint32_t>(scratch, o_flags),
-                          at<unsigned long long>(scratch, o_scan), at<unsigned long long>(scratch, o_part), dcounts,
-                          st);
+    if ((s = convert_plan(ctx, in4, in3->n, tau, perm, n4_out, n3_out, scratch, st)) != H4D_OK) return s;
+    launch_convert_rows(to_ptr(in4), to_ptr(in3), perm, to_grad4(out4), to_grad3(out3), 0, st);
     if ((s = hip_check(ctx, "convert_static")) != H4D_OK) return s;
-    int32_t hc[2] = {0, 0};
-    if (hipMemcpyAsync(hc, dcounts, sizeof(hc), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return hip_check(ctx, "convert_static: count readback");
-    *n4_out = hc[0];
-    *n3_out = hc[1];
+    if (hipStreamSynchronize(st) != hipSuccess) return hip_check(ctx, "convert_static: synchronize");
     return H4D_OK;
 }
 
@@ -1153,6 +1209,110 @@ DensifyP to_densify(const h4d_densify_params& p) {
                     p.log_shrink};
 }
 }  // namespace
+
+namespace {
+// The two sets of a densification over the blocks' counts in scratch.
+DensifySets densify_sets(const h4d_g3d* in3, const h4d_g4d* in4, const h4d_set_stats* st3, const h4d_set_stats* st4,
+                         const h4d_densify_params* p3, const h4d_densify_params* p4, void* scratch) {
+    DensifySets d{};
+    const size_t b3 = (size_t)scan_blocks(in3->n), b4 = (size_t)scan_blocks(in4->n);
+    unsigned long long* totals = at<unsigned long long>(scratch, 0);  // six words
+    d.s[0] = DensifySet{in3->n, in3->log_scale, in3->opacity, st3->grad_norm, st3->visible, to_densify(*p3),
+                        totals + 6, totals, b3, 0, 0, 0, nullptr};
+    d.s[1] = DensifySet{in4->n, in4->log_scale, in4->opacity, st4->grad_norm, st4->visible, to_densify(*p4),
+                        totals + 6 + 3 * b3, totals + 3, b4, 0, 0, 0, nullptr};
+    return d;
+}
+
+// Counts of the rows of each kind (kept, clones, split), 3D then 4D
+// (synchronises).
+h4d_status densify_plan(h4d_ctx* ctx, const h4d_g3d* in3, const h4d_g4d* in4, const h4d_set_stats* st3,
+                        const h4d_set_stats* st4, const h4d_densify_params* p3, const h4d_densify_params* p4,
+                        int32_t* counts, void* scratch, hipStream_t st) {
+    const DensifySets d = densify_sets(in3, in4, st3, st4, p3, p4, scratch);
+    launch_densify_plan(d, st);
+    h4d_status s;
+    if ((s = hip_check(ctx, "densify")) != H4D_OK) return s;
+    unsigned long long h[6];
+    if ((s = read_back(ctx, h, d.s[0].totals, sizeof(h), st, "densify: count readback")) != H4D_OK) return s;
+    for (int q = 0; q < 6; ++q) counts[q] = (int32_t)h[q];
+    return H4D_OK;
+}
+
+// The output rows of a densification whose counts are known (enqueued).
+h4d_status densify_rows(h4d_ctx* ctx, const h4d_g3d* in3, const h4d_g4d* in4, const h4d_set_stats* st3,
+                        const h4d_set_stats* st4, const float* noise3, const float* noise4,
+                        const h4d_densify_params* p3, const h4d_densify_params* p4, const int32_t* counts,
+                        h4d_g3d_mut* out3, h4d_g4d_mut* out4, int32_t* src3, int32_t* src4, void* scratch,
+                        hipStream_t st) {
+    DensifySets d = densify_sets(in3, in4, st3, st4, p3, p4, scratch);
+    for (int q = 0; q < 2; ++q) {
+        d.s[q].k0 = counts[3 * q];
+        d.s[q].k1 = counts[3 * q + 1];
+        d.s[q].k2 = counts[3 * q + 2];
+        d.s[q].src = q ? src4 : src3;
+    }
+    launch_densify_rows(d, to_ptr(in3), to_ptr(in4), noise3, noise4, to_grad3(out3), to_grad4(out4), st);
+    return hip_check(ctx, "densify");
+}
+
+// What both forms of a densification check of their inputs.
+h4d_status check_densify(h4d_ctx* ctx, const h4d_g3d* in3, const h4d_g4d* in4, const h4d_set_stats* st3,
+                         const h4d_set_stats* st4, const h4d_densify_params* p3, const h4d_densify_params* p4,
+                         const void* scratch, size_t scratch_bytes) {
+    h4d_status s;
+    if ((s = check_sets(ctx, in3, in4)) != H4D_OK) return s;
+    if ((s = check_densify_params(ctx, p3, "3D")) != H4D_OK) return s;
+    if ((s = check_densify_params(ctx, p4, "4D")) != H4D_OK) return s;
+    if (!st3 || !st4) return fail(ctx, H4D_ERR_INVALID_ARG, "null statistics");
+    if ((int64_t)in3->n * std::max(2, p3->split_n) > 0x7FFFFFFF || (int64_t)in4->n * std::max(2, p4->split_n) > 0x7FFFFFFF)
+        return fail(ctx, H4D_ERR_INVALID_ARG, "too many output rows");
+    if ((in3->n > 0 && (!st3->grad_norm || !st3->visible)) || (in4->n > 0 && (!st4->grad_norm || !st4->visible)))
+        return fail(ctx, H4D_ERR_INVALID_ARG, "null statistics array");
+    const size_t need = h4dgs_densify_scratch_bytes(in3->n, in4->n);
+    if (!scratch || scratch_bytes < need)
+        return fail(ctx, H4D_ERR_INVALID_ARG, "scratch too small (%zu < %zu)", scratch_bytes, need);
+    return H4D_OK;
+}
+}  // namespace
+
+h4d_status h4dgs_densify_plan(h4d_ctx* ctx, const h4d_g3d* in3, const h4d_g4d* in4, const h4d_set_stats* st3,
+                              const h4d_set_stats* st4, const h4d_densify_params* p3, const h4d_densify_params* p4,
+                              int32_t* counts, void* scratch, size_t scratch_bytes, void* stream) {
+    if (!ctx) return H4D_ERR_INVALID_ARG;
+    h4d_status s;
+    if ((s = check_densify(ctx, in3, in4, st3, st4, p3, p4, scratch, scratch_bytes)) != H4D_OK) return s;
+    if (!counts) return fail(ctx, H4D_ERR_INVALID_ARG, "null counts");
+    return densify_plan(ctx, in3, in4, st3, st4, p3, p4, counts, scratch, static_cast<hipStream_t>(stream));
+}
+
+h4d_status h4dgs_densify_rows(h4d_ctx* ctx, const h4d_g3d* in3, const h4d_g4d* in4, const h4d_set_stats* st3,
+                              const h4d_set_stats* st4, const float* noise3, const float* noise4,
+                              const h4d_densify_params* p3, const h4d_densify_params* p4, const int32_t* counts,
+                              h4d_g3d_mut* out3, h4d_g4d_mut* out4, int32_t* src3, int32_t* src4, void* scratch,
+                              size_t scratch_bytes, void* stream) {
+    if (!ctx) return H4D_ERR_INVALID_ARG;
+    h4d_status s;
+    if ((s = check_densify(ctx, in3, in4, st3, st4, p3, p4, scratch, scratch_bytes)) != H4D_OK) return s;
+    if (!counts || !out3 || !out4) return fail(ctx, H4D_ERR_INVALID_ARG, "null counts or output");
+    for (int q = 0; q < 2; ++q) {
+        const int32_t* c = counts + 3 * q;
+        const int64_t n = q ? in4->n : in3->n;
+        if (c[0] < 0 || c[1] < 0 || c[2] < 0 || (int64_t)c[0] + c[2] > n || (int64_t)c[1] + c[2] > n)
+            return fail(ctx, H4D_ERR_INVALID_ARG, "row counts are not of a densification of %lld rows", (long long)n);
+        const int64_t rows = (int64_t)c[0] + c[1] + (int64_t)(q ? p4->split_n : p3->split_n) * c[2];
+        if ((q ? out4->n : out3->n) < rows)
+            return fail(ctx, H4D_ERR_CAPACITY, "out%d capacity %d < %lld", q ? 4 : 3, q ? out4->n : out3->n,
+                        (long long)rows);
+        if (rows > 0 && (q ? (!src4 || !noise4 || !has_arrays4(out4)) : (!src3 || !noise3 || !has_arrays3(out3))))
+            return fail(ctx, H4D_ERR_INVALID_ARG, "%dD set: null noise, src or output array", q ? 4 : 3);
+    }
+    if ((s = check_no_alias(ctx, in4, in3, out4, out3)) != H4D_OK) return s;
+    const int32_t rows4 = counts[3] + counts[4] + p4->split_n * counts[5];
+    if ((s = check_time_out(ctx, in4, out4, rows4, "densify_rows")) != H4D_OK) return s;
+    return densify_rows(ctx, in3, in4, st3, st4, noise3, noise4, p3, p4, counts, out3, out4, src3, src4, scratch,
+                        static_cast<hipStream_t>(stream));
+}
 
 h4d_status h4dgs_densify(h4d_ctx* ctx, const h4d_g3d* in3, const h4d_g4d* in4, const h4d_set_stats* st3,
                          const h4d_set_stats* st4, const float* noise3, const float* noise4,
@@ -1183,33 +1343,14 @@ h4d_status h4dgs_densify(h4d_ctx* ctx, const h4d_g3d* in3, const h4d_g4d* in4, c
     if (!scratch || scratch_bytes < need)
         return fail(ctx, H4D_ERR_INVALID_ARG, "scratch too small (%zu < %zu)", scratch_bytes, need);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const size_t n = (size_t)std::max(in3->n, in4->n);
-    const size_t nb = (size_t)std::max(1, scan_blocks((int)n));
-    Carve c;
-    const size_t o_flags = c.take(3 * 4 * n), o_scan = c.take(3 * 8 * (n + 1)), o_part = c.take(3 * 8 * (nb + 1)),
-                 o_cnt = c.take(16);
-    int32_t* dcount = at<int32_t>(scratch, o_cnt);
-    const G3Grad o3{out3->n, out3->mean, out3->log_scale, out3->quat, out3->opacity, out3->sh};
-    const G4Grad o4{out4->n,  out4->mean,    out4->mean_t, out4->log_scale, out4->quat_l, out4->quat_r,
-                    out4->opacity, out4->sh, out4->sh_t};
-    int32_t hc[2] = {0, 0};
-    // the sets one after another in the same scratch (each ends in a count read back)
-    launch_densify3(to_ptr(in3), st3->grad_norm, st3->visible, noise3, to_densify(*p3), o3, src3,
-                    at<uint32_t>(scratch, o_flags), at<unsigned long long>(scratch, o_scan),
-                    at<unsigned long long>(scratch, o_part), dcount, st);
-    if ((s = hip_check(ctx, "densify (3D)")) != H4D_OK) return s;
-    if (hipMemcpyAsync(&hc[0], dcount, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return hip_check(ctx, "densify: count readback");
-    launch_densify4(to_ptr(in4), st4->grad_norm, st4->visible, noise4, to_densify(*p4), o4, src4,
-                    at<uint32_t>(scratch, o_flags), at<unsigned long long>(scratch, o_scan),
-                    at<unsigned long long>(scratch, o_part), dcount, st);
-    if ((s = hip_check(ctx, "densify (4D)")) != H4D_OK) return s;
-    if (hipMemcpyAsync(&hc[1], dcount, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return hip_check(ctx, "densify: count readback");
-    *n3_out = hc[0];
-    *n4_out = hc[1];
+    int32_t counts[6];
+    if ((s = densify_plan(ctx, in3, in4, st3, st4, p3, p4, counts, scratch, st)) != H4D_OK) return s;
+    if ((s = densify_rows(ctx, in3, in4, st3, st4, noise3, noise4, p3, p4, counts, out3, out4, src3, src4, scratch,
+                          st)) != H4D_OK)
+        return s;
+    if (hipStreamSynchronize(st) != hipSuccess) return hip_check(ctx, "densify: synchronize");
+    *n3_out = counts[0] + counts[1] + p3->split_n * counts[2];
+    *n4_out = counts[3] + counts[4] + p4->split_n * counts[5];
     return H4D_OK;
 }
 
@@ -1253,10 +1394,7 @@ h4d_status h4dgs_convert_moments(h4d_ctx* ctx, const h4d_g4d* in4, const h4d_g3d
         (in4->n > 0 && (const void*)out4->mean == (const void*)in4->mean))
         return fail(ctx, H4D_ERR_INVALID_ARG, "outputs must not alias inputs");
     if ((s = check_time_out(ctx, in4, out4, in4->n, "convert_moments")) != H4D_OK) return s;
-    const G4Grad o4{out4->n,  out4->mean,    out4->mean_t, out4->log_scale, out4->quat_l, out4->quat_r,
-                    out4->opacity, out4->sh, out4->sh_t};
-    const G3Grad o3{out3->n, out3->mean, out3->log_scale, out3->quat, out3->opacity, out3->sh};
-    launch_convert_moments(to_ptr(in4), to_ptr(in3), perm, o4, o3, static_cast<hipStream_t>(stream));
+    launch_convert_rows(to_ptr(in4), to_ptr(in3), perm, to_grad4(out4), to_grad3(out3), 1, static_cast<hipStream_t>(stream));
     return hip_check(ctx, "convert_moments");
 }
 

@@ -8,14 +8,55 @@
 
 namespace h4d {
 
-// mask_i = (double)s_t > log((double)tau); flags hold 1 for converted rows
-__global__ void k_convert_mask(const float* __restrict__ ls4, int n4, double log_tau, uint32_t* __restrict__ conv,
-                               uint32_t* __restrict__ keep) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n4) return;
-    const bool m = (double)ls4[(size_t)3 * n4 + i] > log_tau;
-    conv[i] = m ? 1u : 0u;
-    keep[i] = m ? 0u : 1u;
+// Row i is converted iff (double)s_t > log((double)tau).
+__device__ __forceinline__ bool is_static(const float* __restrict__ ls4, int n4, int i, double log_tau) {
+    return (double)ls4[(size_t)3 * n4 + i] > log_tau;
+}
+
+// The row order is found in three small launches: the converted rows of each
+// block of kScanTile, their scan, and perm (kept rows need no scan of their own:
+// a row's kept predecessors are those that are not converted).
+__global__ void __launch_bounds__(256) k_convert_count(const float* __restrict__ ls4, int n4, double log_tau,
+                                                       unsigned long long* __restrict__ partials) {
+    __shared__ uint32_t s_c[4];
+    uint32_t c = 0;
+#pragma unroll
+    for (int k = 0; k < kScanTile / 256; ++k) {
+        const int i = blockIdx.x * kScanTile + k * 256 + (int)threadIdx.x;
+        c += (uint32_t)__popcll(__ballot(i < n4 && is_static(ls4, n4, i, log_tau)));
+    }
+    if ((threadIdx.x & 63) == 0) s_c[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) partials[blockIdx.x] = (unsigned long long)(s_c[0] + s_c[1] + s_c[2] + s_c[3]);
+}
+
+// perm[i] = new 4D row, or -(1 + new 3D row); partials scanned.
+__global__ void __launch_bounds__(256) k_convert_perm(const float* __restrict__ ls4, int n4, double log_tau, int n3,
+                                                      const unsigned long long* __restrict__ partials,
+                                                      int32_t* __restrict__ perm) {
+    constexpr int R = kScanTile / 256;
+    __shared__ uint32_t s_c[R * 4];  // converted rows per (round, wave), in row order
+    const int tid = (int)threadIdx.x, lane = tid & 63, w = tid >> 6;
+    unsigned long long m[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int i = blockIdx.x * kScanTile + k * 256 + tid;
+        m[k] = __ballot(i < n4 && is_static(ls4, n4, i, log_tau));
+        if (lane == 0) s_c[k * 4 + w] = (uint32_t)__popcll(m[k]);
+    }
+    __syncthreads();
+    uint32_t run = (uint32_t)partials[blockIdx.x];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        uint32_t before = run;
+        for (int q = 0; q < 4; ++q) {
+            if (q < w) before += s_c[k * 4 + q];
+            run += s_c[k * 4 + q];
+        }
+        const int i = blockIdx.x * kScanTile + k * 256 + tid;
+        const uint32_t off = before + (uint32_t)__popcll(m[k] & ((1ull << lane) - 1ull));
+        if (i < n4) perm[i] = ((m[k] >> lane) & 1ull) ? -(int32_t)(1u + (uint32_t)n3 + off) : (int32_t)((uint32_t)i - off);
+    }
 }
 
 __device__ inline void mat2quat(const double R[3][3], double q[4]) {
@@ -52,39 +93,70 @@ __device__ inline void unit4(const float* q, int n, int i, double o[4]) {
     for (int k = 0; k < 4; ++k) o[k] = a[k] * inv;
 }
 
-// keep_off / conv_off: exclusive scans of keep / conv (64-bit), [n4 + 1]
-__global__ void k_convert_scatter(G4Ptr in4, const uint32_t* __restrict__ conv,
-                                  const unsigned long long* __restrict__ keep_off,
-                                  const unsigned long long* __restrict__ conv_off, int n3, G4Grad out4, G3Grad out3,
-                                  int32_t* __restrict__ perm) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n4 = in4.n;
+// ---------------------------------------------------------------------------
+// Moving rows of component-major arrays.
+// ---------------------------------------------------------------------------
+// Bound by memory: 4 bytes per component and row, in and out.  A row per thread
+// with its 59 or 65 components one after another kept one load in flight and
+// a sixteenth of the chip's waves busy; here blockIdx.y takes a slab of up to
+// eight components, all loaded before any is stored, so a launch has ten times
+// the waves and eight loads in flight each.  Rows go to outputs of the exact size
+// instead of being copied out of larger ones afterwards.  500k 4D rows, half of
+// them converted, 250 MB: 0.062 ms (4.1 TB/s); the densified rows of 175k 3D and
+// 75k 4D Gaussians 0.030 + 0.016 ms, from 0.090 + 0.077 ms and a copy.
+__global__ void __launch_bounds__(256) k_rows_gather(RowSlabs t, const int32_t* __restrict__ src, int rows,
+                                                     int negative) {
+    const RowSlab& s = t.s[blockIdx.y];
+    const int r = blockIdx.x * 256 + (int)threadIdx.x;
+    if (r >= rows || r >= s.limit) return;
+    int32_t i = src ? src[r] : r;
+    if (negative == kNegativeParent && i < 0) i = -1 - i;
+    const bool ok = i >= 0 && (size_t)i < t.ni;
+    float v[kSlabComps];
+#pragma unroll
+    for (int k = 0; k < kSlabComps; ++k) v[k] = (ok && k < s.comps) ? s.in[(size_t)k * t.ni + i] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < kSlabComps; ++k)
+        if (k < s.comps) s.out[(size_t)k * t.no + r] = v[k];
+}
+
+// Rows of the 4D set to their places: perm >= 0 to out4's row, else to out3's
+// (the components both sets have).
+__global__ void __launch_bounds__(256) k_rows_split(RowSlabs t, const int32_t* __restrict__ perm, int n4) {
+    const RowSlab& s = t.s[blockIdx.y];
+    const int i = blockIdx.x * 256 + (int)threadIdx.x;
     if (i >= n4) return;
-    const size_t ni = (size_t)n4;
-    if (!conv[i]) {
-        const size_t r = (size_t)keep_off[i];
-        const size_t no = (size_t)out4.n;  // output capacity (row stride)
-        for (int k = 0; k < 3; ++k) out4.mean[k * no + r] = in4.mean[k * ni + i];
-        out4.mean_t[r] = in4.mean_t[i];
-        for (int k = 0; k < 4; ++k) out4.log_scale[k * no + r] = in4.log_scale[k * ni + i];
-        for (int k = 0; k < 4; ++k) out4.quat_l[k * no + r] = in4.quat_l[k * ni + i];
-        for (int k = 0; k < 4; ++k) out4.quat_r[k * no + r] = in4.quat_r[k * ni + i];
-        out4.opacity[r] = in4.opacity[i];
-        for (int k = 0; k < 48; ++k) out4.sh[k * no + r] = in4.sh[k * ni + i];
-        if (in4.sh_t)
-            for (int k = 0; k < 48 * in4.sh_t_deg; ++k) out4.sh_t[k * no + r] = in4.sh_t[k * ni + i];
-        perm[i] = (int32_t)r;
-    } else {
-        const size_t r = (size_t)n3 + (size_t)conv_off[i];
-        const size_t no = (size_t)out3.n;
-        for (int k = 0; k < 3; ++k) out3.mean[k * no + r] = in4.mean[k * ni + i];
-        for (int k = 0; k < 3; ++k) out3.log_scale[k * no + r] = in4.log_scale[k * ni + i];
-        out3.opacity[r] = in4.opacity[i];
-        for (int k = 0; k < 48; ++k) out3.sh[k * no + r] = in4.sh[k * ni + i];
-        // Eq. 8-9: quaternion of the top-left 3x3 block of R_l R_r
+    const int32_t p = perm[i];
+    const bool conv = p < 0;
+    const size_t r = conv ? (size_t)(-1 - (int64_t)p) : (size_t)p;
+    float* out = conv ? s.out3 : s.out;
+    const size_t no = conv ? t.no3 : t.no;
+    const int comps = conv ? s.comps3 : s.comps;
+    if (r >= no) return;  // (never so for a perm of the same sets)
+    float v[kSlabComps];
+#pragma unroll
+    for (int k = 0; k < kSlabComps; ++k) v[k] = k < comps ? s.in[(size_t)k * t.ni + i] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < kSlabComps; ++k)
+        if (k < comps) out[(size_t)k * no + r] = v[k];
+}
+
+// Eq. 8-9: the converted rows' quaternions, of the top-left 3x3 block of R_l
+// R_r; zeros for moments.
+__global__ void __launch_bounds__(256) k_convert_quat(const float* __restrict__ ql, const float* __restrict__ qr, int n4,
+                                                      const int32_t* __restrict__ perm, float* __restrict__ quat3,
+                                                      size_t no, int zero) {
+    const int i = blockIdx.x * 256 + (int)threadIdx.x;
+    if (i >= n4) return;
+    const int32_t p = perm[i];
+    if (p >= 0) return;
+    const size_t r = (size_t)(-1 - (int64_t)p);
+    if (r >= no) return;
+    double q[4] = {0.0, 0.0, 0.0, 0.0};
+    if (!zero) {
         double a[4], b[4];
-        unit4(in4.quat_l, n4, i, a);
-        unit4(in4.quat_r, n4, i, b);
+        unit4(ql, n4, i, a);
+        unit4(qr, n4, i, b);
         const double L[4][4] = {{a[0], -a[1], -a[2], -a[3]}, {a[1], a[0], -a[3], a[2]},
                                 {a[2], a[3], a[0], -a[1]}, {a[3], -a[2], a[1], a[0]}};
         const double Rr[4][4] = {{b[0], -b[1], -b[2], -b[3]}, {b[1], b[0], b[3], -b[2]},
@@ -96,88 +168,78 @@ __global__ void k_convert_scatter(G4Ptr in4, const uint32_t* __restrict__ conv,
                 for (int k = 0; k < 4; ++k) acc += L[r2][k] * Rr[k][c];
                 R3[r2][c] = acc;
             }
-        double q[4];
         mat2quat(R3, q);
-        for (int k = 0; k < 4; ++k) out3.quat[k * no + r] = (float)q[k];
-        perm[i] = -(int32_t)(1 + r);
+    }
+    for (int k = 0; k < 4; ++k) quat3[k * no + r] = (float)q[k];
+}
+
+namespace {
+// Adds the slabs of one array of `comps` components to t.
+void add_slabs(RowSlabs& t, const float* in, float* out, float* out3, int comps, int comps3, int limit) {
+    for (int c = 0; c < comps; c += kSlabComps) {
+        RowSlab& s = t.s[t.n++];
+        s.in = in + (size_t)c * t.ni;
+        s.out = out ? out + (size_t)c * t.no : nullptr;
+        s.out3 = out3 ? out3 + (size_t)c * t.no3 : nullptr;
+        s.comps = std::min(kSlabComps, comps - c);
+        s.comps3 = out3 ? std::max(0, std::min(kSlabComps, comps3 - c)) : 0;
+        s.limit = limit;
     }
 }
+}  // namespace
 
-// copy of the existing 3D rows into the (wider) output arrays
-__global__ void k_copy_rows(G3Ptr in3, G3Grad out3) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= in3.n) return;
-    const size_t ni = (size_t)in3.n, no = (size_t)out3.n;
-    for (int k = 0; k < 3; ++k) out3.mean[k * no + i] = in3.mean[k * ni + i];
-    for (int k = 0; k < 3; ++k) out3.log_scale[k * no + i] = in3.log_scale[k * ni + i];
-    for (int k = 0; k < 4; ++k) out3.quat[k * no + i] = in3.quat[k * ni + i];
-    out3.opacity[i] = in3.opacity[i];
-    for (int k = 0; k < 48; ++k) out3.sh[k * no + i] = in3.sh[k * ni + i];
+// placed: rows from there on take their means and log-scales elsewhere.
+RowSlabs slabs3(const G3Ptr& in, const G3Grad& out, int placed) {
+    RowSlabs t{};
+    t.ni = (size_t)in.n;
+    t.no = (size_t)out.n;
+    add_slabs(t, in.mean, out.mean, nullptr, 3, 0, placed);
+    add_slabs(t, in.log_scale, out.log_scale, nullptr, 3, 0, placed);
+    add_slabs(t, in.quat, out.quat, nullptr, 4, 0, INT32_MAX);
+    add_slabs(t, in.opacity, out.opacity, nullptr, 1, 0, INT32_MAX);
+    add_slabs(t, in.sh, out.sh, nullptr, 48, 0, INT32_MAX);
+    return t;
+}
+RowSlabs slabs4(const G4Ptr& in, const G4Grad& out, const G3Grad* out3, int placed) {
+    RowSlabs t{};
+    t.ni = (size_t)in.n;
+    t.no = (size_t)out.n;
+    t.no3 = out3 ? (size_t)out3->n : 0;
+    add_slabs(t, in.mean, out.mean, out3 ? out3->mean : nullptr, 3, 3, placed);
+    add_slabs(t, in.mean_t, out.mean_t, nullptr, 1, 0, placed);
+    add_slabs(t, in.log_scale, out.log_scale, out3 ? out3->log_scale : nullptr, 4, 3, placed);
+    add_slabs(t, in.quat_l, out.quat_l, nullptr, 4, 0, INT32_MAX);
+    add_slabs(t, in.quat_r, out.quat_r, nullptr, 4, 0, INT32_MAX);
+    add_slabs(t, in.opacity, out.opacity, out3 ? out3->opacity : nullptr, 1, 1, INT32_MAX);
+    add_slabs(t, in.sh, out.sh, out3 ? out3->sh : nullptr, 48, 48, INT32_MAX);
+    if (in.sh_t) add_slabs(t, in.sh_t, out.sh_t, nullptr, 48 * in.sh_t_deg, 0, INT32_MAX);
+    return t;
 }
 
-__global__ void k_convert_counts(const unsigned long long* keep_off, const unsigned long long* conv_off, int n4, int n3,
-                                 int32_t* counts) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        counts[0] = (int32_t)keep_off[n4];
-        counts[1] = n3 + (int32_t)conv_off[n4];
-    }
+void launch_rows_gather(const RowSlabs& t, const int32_t* src, int rows, int negative, hipStream_t st) {
+    if (rows <= 0) return;
+    k_rows_gather<<<dim3((unsigned)ceil_div(rows, 256), (unsigned)t.n), 256, 0, st>>>(t, src, rows, negative);
 }
 
-// Optimiser state across the conversion: the moment arrays (laid out as the
-// parameters) follow the rows the conversion moved (perm from
-// k_convert_scatter).  A kept 4D row takes all its moments; a converted row
-// takes those of the fields it copies (mean, spatial log-scales, opacity, SH)
-// and starts its new quaternion's at zero.
-__global__ void k_convert_moments(G4Ptr in4, const int32_t* __restrict__ perm, G4Grad out4, G3Grad out3) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n4 = in4.n;
-    if (i >= n4) return;
-    const size_t ni = (size_t)n4;
-    const int32_t p = perm[i];
-    if (p >= 0) {
-        const size_t r = (size_t)p, no = (size_t)out4.n;
-        for (int k = 0; k < 3; ++k) out4.mean[k * no + r] = in4.mean[k * ni + i];
-        out4.mean_t[r] = in4.mean_t[i];
-        for (int k = 0; k < 4; ++k) out4.log_scale[k * no + r] = in4.log_scale[k * ni + i];
-        for (int k = 0; k < 4; ++k) out4.quat_l[k * no + r] = in4.quat_l[k * ni + i];
-        for (int k = 0; k < 4; ++k) out4.quat_r[k * no + r] = in4.quat_r[k * ni + i];
-        out4.opacity[r] = in4.opacity[i];
-        for (int k = 0; k < 48; ++k) out4.sh[k * no + r] = in4.sh[k * ni + i];
-        if (in4.sh_t)
-            for (int k = 0; k < 48 * in4.sh_t_deg; ++k) out4.sh_t[k * no + r] = in4.sh_t[k * ni + i];
-    } else {
-        const size_t r = (size_t)(-1 - (int64_t)p), no = (size_t)out3.n;
-        for (int k = 0; k < 3; ++k) out3.mean[k * no + r] = in4.mean[k * ni + i];
-        for (int k = 0; k < 3; ++k) out3.log_scale[k * no + r] = in4.log_scale[k * ni + i];
-        for (int k = 0; k < 4; ++k) out3.quat[k * no + r] = 0.0f;
-        out3.opacity[r] = in4.opacity[i];
-        for (int k = 0; k < 48; ++k) out3.sh[k * no + r] = in4.sh[k * ni + i];
-    }
+// partials: scan_blocks(n4) + 1 words; the last receives the converted rows.
+void launch_convert_plan(const G4Ptr& in4, int n3, double log_tau, int32_t* perm, unsigned long long* partials,
+                         hipStream_t st) {
+    const int n4 = in4.n, nb = scan_blocks(n4);
+    if (n4 > 0) k_convert_count<<<nb, 256, 0, st>>>(in4.log_scale, n4, log_tau, partials);
+    launch_scan_top(partials, nb, 1, 0, partials + nb, st);
+    if (n4 > 0) k_convert_perm<<<nb, 256, 0, st>>>(in4.log_scale, n4, log_tau, n3, partials, perm);
 }
 
-void launch_convert_moments(const G4Ptr& in4, const G3Ptr& in3, const int32_t* perm, const G4Grad& out4,
-                            const G3Grad& out3, hipStream_t st) {
-    if (in3.n > 0) k_copy_rows<<<ceil_div(in3.n, 256), 256, 0, st>>>(in3, out3);
-    if (in4.n > 0) k_convert_moments<<<ceil_div(in4.n, 256), 256, 0, st>>>(in4, perm, out4, out3);
-}
-
-// flags: [2][n4] uint32; scan: [2][n4 + 1] u64; partials: [2][scan_blocks + 1]
-void launch_convert_static(const G4Ptr& in4, const G3Ptr& in3, double log_tau, const G4Grad& out4,
-                           const G3Grad& out3, int32_t* perm, uint32_t* flags, unsigned long long* scan,
-                           unsigned long long* partials, int32_t* counts, hipStream_t st) {
-    const int n4 = in4.n;
-    uint32_t* conv = flags;
-    uint32_t* keep = flags + n4;
-    unsigned long long* conv_off = scan;
-    unsigned long long* keep_off = scan + (n4 + 1);
-    const int nb = std::max(1, scan_blocks(n4));
-    if (in3.n > 0) k_copy_rows<<<ceil_div(in3.n, 256), 256, 0, st>>>(in3, out3);
-    if (n4 > 0) k_convert_mask<<<ceil_div(n4, 256), 256, 0, st>>>(in4.log_scale, n4, log_tau, conv, keep);
-    launch_scan_u32_u64(conv, nullptr, n4, conv_off, partials, st);
-    launch_scan_u32_u64(keep, nullptr, n4, keep_off, partials + nb + 1, st);
-    if (n4 > 0)
-        k_convert_scatter<<<ceil_div(n4, 256), 256, 0, st>>>(in4, conv, keep_off, conv_off, in3.n, out4, out3, perm);
-    k_convert_counts<<<1, 1, 0, st>>>(keep_off, conv_off, n4, in3.n, counts);
+// The 3D rows copied, the 4D rows moved by perm; moments: zeros for the
+// converted rows' quaternions.
+void launch_convert_rows(const G4Ptr& in4, const G3Ptr& in3, const int32_t* perm, const G4Grad& out4,
+                         const G3Grad& out3, int moments, hipStream_t st) {
+    launch_rows_gather(slabs3(in3, out3, INT32_MAX), nullptr, in3.n, kNegativeZero, st);
+    if (in4.n <= 0) return;
+    const RowSlabs t = slabs4(in4, out4, &out3, INT32_MAX);
+    k_rows_split<<<dim3((unsigned)ceil_div(in4.n, 256), (unsigned)t.n), 256, 0, st>>>(t, perm, in4.n);
+    k_convert_quat<<<ceil_div(in4.n, 256), 256, 0, st>>>(in4.quat_l, in4.quat_r, in4.n, perm, out3.quat,
+                                                         (size_t)out3.n, moments);
 }
 
 }  // namespace h4d

@@ -92,6 +92,10 @@ bool launch_radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, uint32_
                        const uint32_t* val_map = nullptr, int skip_empty = 0,
                        unsigned long long* out_count = nullptr, uint2* pairs_out = nullptr);
 int scan_blocks(int n);
+// Exclusive scans of `count` arrays of nparts words, stride apart, in place;
+// their totals go to totals[0 .. count).
+void launch_scan_top(unsigned long long* partials, int nparts, int count, size_t stride, unsigned long long* totals,
+                     hipStream_t st);
 // out[j] = sum_{i<j} in[idx[i]] (idx may be null), out[n] = total; 64-bit.
 // With run_start, run_start[r] (r < run_cap) receives the index i whose range
 // [out[i], out[i + 1]) holds output 256 r.
@@ -233,26 +237,61 @@ void launch_walk_lists(int tile, const Rec* recs, int N, const CoarseLists& list
 void launch_l1_loss_grad(const float* img, const float* target, float* dl, size_t n, float scale, float* loss,
                          hipStream_t st);
 
-// convert.hip
+// densify.hip
 // Densification limits as the kernels take them (see h4d_densify_params).
 struct DensifyP {
     float thr;
     int split_n;
     double log_dense, logit_min, log_max_scale, log_shrink;
 };
-void launch_densify3(const G3Ptr& g, const float* grad, const float* vis, const float* noise, const DensifyP& p,
-                     const G3Grad& o, int32_t* src, uint32_t* flags, unsigned long long* scan,
-                     unsigned long long* partials, int32_t* count, hipStream_t st);
-void launch_densify4(const G4Ptr& g, const float* grad, const float* vis, const float* noise, const DensifyP& p,
-                     const G4Grad& o, int32_t* src, uint32_t* flags, unsigned long long* scan,
-                     unsigned long long* partials, int32_t* count, hipStream_t st);
+// One set of a densification: the inputs of its decisions, the blocks' counts
+// of the three kinds of rows ([3][stride], stride = scan_blocks(n)) with their
+// totals, and, once those are known, the kinds' rows and the source rows.
+struct DensifySet {
+    int n;
+    const float *log_scale, *opacity, *grad, *vis;
+    DensifyP p;
+    unsigned long long *partials, *totals;
+    size_t stride;
+    int k0, k1, k2;
+    int32_t* src;
+};
+struct DensifySets {
+    DensifySet s[2];
+};
+void launch_densify_plan(const DensifySets& s, hipStream_t st);
+void launch_densify_rows(const DensifySets& s, const G3Ptr& g3, const G4Ptr& g4, const float* noise3,
+                         const float* noise4, const G3Grad& o3, const G4Grad& o4, hipStream_t st);
 void launch_gather_rows(const G3Ptr& g3, const int32_t* src3, int rows3, const G3Grad& o3, const G4Ptr& g4,
                         const int32_t* src4, int rows4, const G4Grad& o4, hipStream_t st);
-void launch_convert_moments(const G4Ptr& in4, const G3Ptr& in3, const int32_t* perm, const G4Grad& out4,
-                            const G3Grad& out3, hipStream_t st);
-void launch_convert_static(const G4Ptr& in4, const G3Ptr& in3, double log_tau, const G4Grad& out4,
-                           const G3Grad& out3, int32_t* perm, uint32_t* flags, unsigned long long* scan,
-                           unsigned long long* partials, int32_t* counts, hipStream_t st);
+
+// convert.hip
+// Arrays of a set as slabs of up to kSlabComps components (in, out: the slab's
+// first component; rows ni / no apart).  out3 / comps3: where a converted row's
+// components go and how many of them the 3D set has.  Rows from limit on are
+// left alone.
+constexpr int kSlabComps = 8;
+constexpr int kMaxSlabs = 7 + 6 * (1 + kMaxTimeDeg);
+struct RowSlab {
+    const float* in;
+    float *out, *out3;
+    int32_t comps, comps3, limit;
+};
+struct RowSlabs {
+    int32_t n;
+    size_t ni, no, no3;
+    RowSlab s[kMaxSlabs];
+};
+RowSlabs slabs3(const G3Ptr& in, const G3Grad& out, int placed);
+RowSlabs slabs4(const G4Ptr& in, const G4Grad& out, const G3Grad* out3, int placed);
+// out row r = in row src[r] (src null: r), zeros outside the set; a negative
+// source means zeros too, or the row -1 - src[r] (kNegativeParent).
+constexpr int kNegativeZero = 0, kNegativeParent = 1;
+void launch_rows_gather(const RowSlabs& t, const int32_t* src, int rows, int negative, hipStream_t st);
+void launch_convert_plan(const G4Ptr& in4, int n3, double log_tau, int32_t* perm, unsigned long long* partials,
+                         hipStream_t st);
+void launch_convert_rows(const G4Ptr& in4, const G3Ptr& in3, const int32_t* perm, const G4Grad& out4,
+                         const G3Grad& out3, int moments, hipStream_t st);
 
 // adam.hip
 struct AdamSeg {

@@ -322,8 +322,11 @@ __global__ void __launch_bounds__(256) k_scan_reduce(const uint32_t* __restrict_
     if (threadIdx.x == 0) partials[blockIdx.x] = tot;
 }
 
-__global__ void __launch_bounds__(256) k_scan_top(unsigned long long* __restrict__ partials, int nparts) {
+// (blockIdx.x: the array; totals: where its total goes, null: behind it)
+__global__ void __launch_bounds__(256) k_scan_top(unsigned long long* __restrict__ partials, int nparts, size_t stride,
+                                                  unsigned long long* __restrict__ totals) {
     __shared__ unsigned long long s_buf[256];
+    partials += (size_t)blockIdx.x * stride;
     unsigned long long carry = 0;
     for (int start = 0; start < nparts; start += 256) {
         const int i = start + threadIdx.x;
@@ -333,7 +336,7 @@ __global__ void __launch_bounds__(256) k_scan_top(unsigned long long* __restrict
         if (i < nparts) partials[i] = carry + ex;
         carry += tot;
     }
-    if (threadIdx.x == 0) partials[nparts] = carry;
+    if (threadIdx.x == 0) (totals ? totals[blockIdx.x] : partials[nparts]) = carry;
 }
 
 // With run_start: for every run of 256 outputs, the index whose range
@@ -365,13 +368,18 @@ __global__ void __launch_bounds__(256) k_scan_down(const uint32_t* __restrict__ 
     if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = partials[nparts];
 }
 
-int scan_blocks(int n) { return (n + kScanTile - 1) / kScanTile; }
+int scan_blocks(int n) { return (int)(((int64_t)n + kScanTile - 1) / kScanTile); }
+
+void launch_scan_top(unsigned long long* partials, int nparts, int count, size_t stride, unsigned long long* totals,
+                     hipStream_t st) {
+    k_scan_top<<<count, 256, 0, st>>>(partials, nparts, stride, totals);
+}
 
 void launch_scan_u32_u64(const uint32_t* in, const uint32_t* idx, int n, unsigned long long* out,
                          unsigned long long* partials, hipStream_t st, uint32_t* run_start, uint64_t run_cap) {
     const int nb = std::max(1, scan_blocks(n));
     k_scan_reduce<<<nb, 256, 0, st>>>(in, idx, n, partials);
-    k_scan_top<<<1, 256, 0, st>>>(partials, nb);
+    k_scan_top<<<1, 256, 0, st>>>(partials, nb, 0, nullptr);
     k_scan_down<<<nb, 256, 0, st>>>(in, idx, n, partials, nb, out, run_start, run_cap);
 }
 

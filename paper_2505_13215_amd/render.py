@@ -398,8 +398,8 @@ def _set_buffers(n3: int, n4: int, dev="cuda", deg4: int = 0):
     return o3, o4
 
 
-def _first_rows(d: dict, k: int) -> dict:
-    return {name: (v[..., :k] if v.dim() == 2 else v[:k]).contiguous() for name, v in d.items()}
+def _mut3(d: dict, n: int) -> L.G3D:
+    return L.G3D(n, *[_ptr(d[k]) for k in G3_KEYS])
 
 
 def convert_static(rast: Rasterizer, g3: dict, g4: dict, tau: float, moments=()):
@@ -409,31 +409,24 @@ def convert_static(rast: Rasterizer, g3: dict, g4: dict, tau: float, moments=())
     s3, s4 = g3_struct(g3), g4_struct(g4, rast.time_period)
     n3, n4 = s3.n, s4.n
     dev = "cuda"
-    cap3 = n3 + n4
-    deg = time_degree(g4)
-    o3, o4 = _set_buffers(cap3, n4, dev, deg)
-    m3 = L.G3D(cap3, *[_ptr(o3[k]) for k in G3_KEYS])
-    m4 = g4_struct(o4, rast.time_period, n=n4)
     perm = torch.empty(max(1, n4), dtype=torch.int32, device=dev)
     nsc = int(rast.ctx.L.h4dgs_convert_scratch_bytes(n4))
     scratch = torch.empty(max(256, nsc), dtype=torch.uint8, device=dev)
     n4o, n3o = C.c_int32(), C.c_int32()
-    rast.ctx.check(rast.ctx.L.h4dgs_convert_static(
-        rast.ctx.h, C.byref(s4), C.byref(s3), C.c_float(tau), C.byref(m4), C.byref(m3), _ptr(perm), C.byref(n4o),
-        C.byref(n3o), _ptr(scratch), scratch.numel(), _stream()))
+    rast.ctx.check(rast.ctx.L.h4dgs_convert_plan(
+        rast.ctx.h, C.byref(s4), C.byref(s3), C.c_float(tau), _ptr(perm), C.byref(n4o), C.byref(n3o), _ptr(scratch),
+        scratch.numel(), _stream()))
     k3, k4 = n3o.value, n4o.value
-    g3n, g4n = _first_rows(o3, k3), _first_rows(o4, k4)
-    if not moments:
-        return g3n, g4n, perm[:n4]
+    # the rows go straight to outputs of the exact size
     moved = []
-    for a3, a4 in moments:
-        b3, b4 = _set_buffers(cap3, n4, dev, time_degree(a4))
-        rast.ctx.check(rast.ctx.L.h4dgs_convert_moments(
-            rast.ctx.h, C.byref(g4_struct(a4, rast.time_period)), C.byref(g3_struct(a3)), _ptr(perm),
-            C.byref(g4_struct(b4, rast.time_period, n=n4)), C.byref(L.G3D(cap3, *[_ptr(b3[k]) for k in G3_KEYS])),
-            _stream()))
-        moved.append((_first_rows(b3, k3), _first_rows(b4, k4)))
-    return g3n, g4n, perm[:n4], moved
+    for i, (a3, a4) in enumerate(((g3, g4), *moments)):
+        b3, b4 = _set_buffers(k3, k4, dev, time_degree(a4))
+        rast.ctx.check(rast.ctx.L.h4dgs_convert_rows(
+            rast.ctx.h, C.byref(g4_struct(a4, rast.time_period)), C.byref(g3_struct(a3)), _ptr(perm), k4, k3,
+            int(i > 0), C.byref(g4_struct(b4, rast.time_period, n=k4)), C.byref(_mut3(b3, k3)), _stream()))
+        moved.append((b3, b4))
+    g3n, g4n = moved.pop(0)
+    return (g3n, g4n, perm[:n4], moved) if moments else (g3n, g4n, perm[:n4])
 
 
 def densify(rast: Rasterizer, g3: dict, g4: dict, stats3: dict, stats4: dict, noise3: torch.Tensor,
@@ -444,35 +437,37 @@ def densify(rast: Rasterizer, g3: dict, g4: dict, stats3: dict, stats4: dict, no
     (m3, m4) gathered to the new rows (zeros for new rows)."""
     s3, s4 = g3_struct(g3), g4_struct(g4, rast.time_period)
     n3, n4 = s3.n, s4.n
-    cap3, cap4 = n3 * max(2, p3.split_n), n4 * max(2, p4.split_n)
-    o3, o4 = _set_buffers(cap3, cap4, deg4=time_degree(g4))
-    src3 = torch.empty(max(1, cap3), dtype=torch.int32, device="cuda")
-    src4 = torch.empty(max(1, cap4), dtype=torch.int32, device="cuda")
     nsc = int(rast.ctx.L.h4dgs_densify_scratch_bytes(n3, n4))
     scratch = torch.empty(max(256, nsc), dtype=torch.uint8, device="cuda")
     st3, st4 = _stats_struct(stats3, n3), _stats_struct(stats4, n4)
-    n3o, n4o = C.c_int32(), C.c_int32()
     for t, shape in ((noise3, (p3.split_n, 3, n3)), (noise4, (p4.split_n, 4, n4))):
         if tuple(t.shape) != shape or t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous():
             raise ValueError(f"noise: expected a contiguous float32 CUDA tensor of shape {shape}")
-    rast.ctx.check(rast.ctx.L.h4dgs_densify(
-        rast.ctx.h, C.byref(s3), C.byref(s4), C.byref(st3), C.byref(st4), _ptr(noise3), _ptr(noise4),
-        C.byref(p3), C.byref(p4), C.byref(L.G3D(cap3, *[_ptr(o3[k]) for k in G3_KEYS])),
-        C.byref(g4_struct(o4, rast.time_period, n=cap4)), _ptr(src3), _ptr(src4), C.byref(n3o), C.byref(n4o),
+    counts = (C.c_int32 * 6)()
+    rast.ctx.check(rast.ctx.L.h4dgs_densify_plan(
+        rast.ctx.h, C.byref(s3), C.byref(s4), C.byref(st3), C.byref(st4), C.byref(p3), C.byref(p4), counts,
         _ptr(scratch), scratch.numel(), _stream()))
-    k3, k4 = n3o.value, n4o.value
-    out = [_first_rows(o3, k3), _first_rows(o4, k4), src3[:k3].clone(), src4[:k4].clone()]
+    k3 = counts[0] + counts[1] + p3.split_n * counts[2]
+    k4 = counts[3] + counts[4] + p4.split_n * counts[5]
+    # the rows go straight to outputs of the exact size
+    o3, o4 = _set_buffers(k3, k4, deg4=time_degree(g4))
+    src3 = torch.empty(k3, dtype=torch.int32, device="cuda")
+    src4 = torch.empty(k4, dtype=torch.int32, device="cuda")
+    rast.ctx.check(rast.ctx.L.h4dgs_densify_rows(
+        rast.ctx.h, C.byref(s3), C.byref(s4), C.byref(st3), C.byref(st4), _ptr(noise3), _ptr(noise4),
+        C.byref(p3), C.byref(p4), counts, C.byref(_mut3(o3, k3)), C.byref(g4_struct(o4, rast.time_period, n=k4)),
+        _ptr(src3), _ptr(src4), _ptr(scratch), scratch.numel(), _stream()))
+    out = (o3, o4, src3, src4)
     if not moments:
-        return tuple(out)
+        return out
     moved = []
     for a3, a4 in moments:
         b3, b4 = _set_buffers(k3, k4, deg4=time_degree(a4))
         rast.ctx.check(rast.ctx.L.h4dgs_gather_rows(
             rast.ctx.h, C.byref(g3_struct(a3)), C.byref(g4_struct(a4, rast.time_period)), _ptr(src3), k3, _ptr(src4),
-            k4, C.byref(L.G3D(k3, *[_ptr(b3[k]) for k in G3_KEYS])), C.byref(g4_struct(b4, rast.time_period, n=k4)),
-            _stream()))
+            k4, C.byref(_mut3(b3, k3)), C.byref(g4_struct(b4, rast.time_period, n=k4)), _stream()))
         moved.append((b3, b4))
-    return tuple(out) + (moved,)
+    return out + (moved,)
 
 
 class CapturedStep:
