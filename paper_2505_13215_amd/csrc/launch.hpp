@@ -91,6 +91,10 @@ bool launch_radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, uint32_
                        int64_t* digit_ranges = nullptr, int n_digit_ranges = 0, int items = kSortItems,
                        const uint32_t* val_map = nullptr, int skip_empty = 0,
                        unsigned long long* out_count = nullptr, uint2* pairs_out = nullptr);
+// The values of n_seg segments of n keys each (one after another) in stable
+// ascending key order, in one launch (short segments: n_seg n^2 bounds its time).
+void launch_rank_sort(const uint32_t* keys, const uint32_t* vals, uint32_t* vals_out, int n, int n_seg,
+                      hipStream_t st);
 int scan_blocks(int n);
 // Exclusive scans of `count` arrays of nparts words, stride apart, in place;
 // their totals go to totals[0 .. count).
@@ -152,8 +156,10 @@ void launch_coarse_emit(const unsigned long long* offsets, const uint32_t* run_s
 constexpr int kBinSupers = 2048;  // a block's bits take 32 bytes of LDS per super-tile
 constexpr int kBinBlock = 256;    // splats per block
 constexpr int kBinChunk = 64;     // blocks per chunk of the histograms' scan
+constexpr int kBinDirect = 32;    // blocks of a segment up to which its rows are summed in one go
 struct BinPlan {
     int n_seg = 0, words = 0;
+    bool direct = false;
     int64_t blocks = 0, chunks = 0;
     size_t bytes = 0, hist = 0, partials = 0, chunk_sums = 0, chunk_entries = 0, lists = 0, seg_entries = 0;
 };

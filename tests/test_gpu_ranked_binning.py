@@ -43,3 +43,23 @@ def test_lists_at_the_edges(h4d, tile, W, H, n, max_radius):
     img1, T1, _, ranges1 = h4d.rasterize_splats(culled, rec, W, H)
     assert torch.equal(img, img1) and torch.equal(T, T1)
     assert int(ranges1[-1, 1]) <= int(ranges[-1, 1])
+
+
+@pytest.mark.parametrize("n", [63, 64, 65, 2000, 16384, 16385, 24577])
+def test_depth_order(h4d, n):
+    """Short sorts on both sides of their range (ranks by counting to 16384 keys,
+    radix passes that sum their own histograms to 24576): a whole-image tile's
+    list is the stable depth order, with many equal depths."""
+    print(f"[depth order] n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    W = H = 16
+    rec = sg.synthetic_records(n, W, H, seed=32, max_radius=40)
+    rec["u"][:], rec["v"][:], rec["radius"][:] = 8.0, 8.0, 30
+    rec["visible"] = (rng.uniform(size=n) > 0.1).astype(np.uint8)
+    rec["depth"] = (0.5 + rng.integers(0, max(1, n // 7), size=n) / 64.0).astype(np.float32)
+    rast = h4d.Rasterizer(tile=16, chunk=64, pair_capacity=1 << 20, cull=False)
+    _, _, ids, ranges = h4d.rasterize_splats(rast, rec, W, H)
+    seen = np.nonzero(rec["visible"])[0]
+    want = seen[np.argsort(rec["depth"][seen], kind="stable")]
+    assert ranges.cpu().numpy().tolist() == [[0, len(want)]]
+    assert np.array_equal(ids.cpu().numpy()[:len(want)], want)
