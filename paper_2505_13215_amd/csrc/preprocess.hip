@@ -7,6 +7,8 @@
 // rate, the stage is bound by its 236-260 B/Gaussian of parameter reads, and in
 // FP64 every discrete decision of the stage (cull, radius, pixel square, depth
 // key) lands exactly where the FP64 definition puts it.
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 #include "rotation.hpp"
@@ -364,17 +366,17 @@ __global__ void __launch_bounds__(256) k_preprocess(G3Ptr g3, G4Ptr g4, const Vi
 // TIME: tc holds the Gaussian's time coefficients; their gradient rows are
 // accumulated and gmt receives mean_t's share through the time weights (a
 // separate instantiation, so that sets without them compile as plain SH).
-template <bool TIME>
+template <bool TIME, class E>
 __device__ inline void proj_bwd(const ViewParams& V, const WorldF& w, const ProjF& p, const float* shp, int shn,
-                                int shi, const ScreenGrad& e, double gmu[3], double Sb[3][3],
+                                int shi, const E& e, double gmu[3], double Sb[3][3],
                                 double& gop, float* gsh, const TimeColour* tc = nullptr, double* gmt = nullptr) {
     // the blending adjoint sums the centre and conic terms without their
     // constant factors and the effective opacity: du, dv take -op / log2 e,
     // dQ00, dQ11 -op / 2, dQ01 -op
     const double ku = -kLn2 * w.op, kq = -0.5 * w.op;
-    const double gu = ku * e.v[0], gv = ku * e.v[1], gQa = kq * e.v[2], gQb = -w.op * e.v[3], gQc = kq * e.v[4];
-    gop = e.v[5];
-    const double grgb[3] = {e.v[6], e.v[7], e.v[8]};
+    const double gu = ku * e.at(0), gv = ku * e.at(1), gQa = kq * e.at(2), gQb = -w.op * e.at(3), gQc = kq * e.at(4);
+    gop = e.at(5);
+    const double grgb[3] = {e.at(6), e.at(7), e.at(8)};
     // colour
     double Y[16], raw[3];
     sh_eval(p.dir[0], p.dir[1], p.dir[2], Y);
@@ -463,9 +465,9 @@ __device__ inline void unit_bwd(const double qh[4], double nrm, const double gqh
     for (int k = 0; k < 4; ++k) out[k * stride] = (float)((gqh[k] - qh[k] * dq) * in);
 }
 
-template <bool TIME>
+template <bool TIME, bool WIDE>
 __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restrict__ views, int n_views, int N,
-                              const Rec* __restrict__ recs, const float* __restrict__ g2, int wide, const G4Grad& gr,
+                              const Rec* __restrict__ recs, const float* __restrict__ g2, const G4Grad& gr,
                               const SetStats& st) {
     const size_t n = (size_t)g4.n;
     double s[4], ql[4], qr[4];
@@ -514,9 +516,9 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restri
         for (int r = 0; r < 3; ++r)
             for (int k = 0; k < 3; ++k) w.S[r][k] = S4[r][k] - b[r] * b[k] * ic;
         w.op = sig * pt;
-        const ScreenGrad e = load_screen_grad(g2 + ((size_t)v * N + i) * kG2Stride, wide);
+        const ScreenGrad<WIDE> e{g2 + ((size_t)v * N + i) * kG2Stride};
         if (st.grad || st.vis || st.step_vis) {
-            stat_g += ndc_grad_norm(e, kLn2 * w.op, V.W, V.H);
+            stat_g += ndc_grad_norm(e.at(0), e.at(1), kLn2 * w.op, V.W, V.H);
             ++stat_n;
         }
         ProjF p;
@@ -603,8 +605,9 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restri
     for (int k = 0; k < 48; ++k) gr.sh[k * n + i] = gsh[k];
 }
 
+template <bool WIDE>
 __device__ inline void bwd_3d(const G3Ptr& g3, int i, int gidx, const ViewParams* __restrict__ views, int n_views,
-                              int N, const Rec* __restrict__ recs, const float* __restrict__ g2, int wide, const G3Grad& gr,
+                              int N, const Rec* __restrict__ recs, const float* __restrict__ g2, const G3Grad& gr,
                               const SetStats& st, int static_rows) {
     const size_t n = (size_t)g3.n;
     WorldF w;
@@ -625,20 +628,39 @@ __device__ inline void bwd_3d(const G3Ptr& g3, int i, int gidx, const ViewParams
         if (recs[(size_t)v * N + gidx].d.w == 0u) continue;  // covers no pixel in this camera
         // (a view alone, or the group's sum already in its record: that record
         // as it is; otherwise the members' records summed here)
-        ScreenGrad e{};
+        using Sum = std::conditional_t<WIDE, double, float>;
+        Sum e[kG2Slots];
+        for (int k = 0; k < kG2Slots; ++k) e[k] = (Sum)0;
         const bool direct = static_rows || V.static_next < 0;
-        for (int u = v; u >= 0; u = direct ? -1 : views[u].static_next) {
-            const ScreenGrad g = load_screen_grad(g2 + ((size_t)u * N + gidx) * kG2Stride, wide);
+        const ScreenGrad<WIDE> own{g2 + ((size_t)v * N + gidx) * kG2Stride};
+        if (direct && (st.grad || st.vis || st.step_vis)) {
+            stat_g += ndc_grad_norm(own.at(0), own.at(1), kLn2 * w.op, V.W, V.H);
+            ++stat_n;
+        }
+        for (int u = direct ? -1 : v; u >= 0; u = views[u].static_next) {
+            const ScreenGrad<WIDE> g{g2 + ((size_t)u * N + gidx) * kG2Stride};
             if (st.grad || st.vis || st.step_vis) {
-                stat_g += ndc_grad_norm(g, kLn2 * w.op, views[u].W, views[u].H);
+                stat_g += ndc_grad_norm(g.at(0), g.at(1), kLn2 * w.op, views[u].W, views[u].H);
                 ++stat_n;
             }
-            for (int k = 0; k < 9; ++k) e.v[k] += g.v[k];
+            if constexpr (WIDE)
+                for (int k = 0; k < 9; ++k) e[k] += g.at(k);
+            else
+                for (int k = 0; k < kG2Slots; ++k) e[k] += g.rec[k];
         }
         ProjF p;
         project(V, w, p);
         double gmc[3], Sb[3][3], gop;
-        proj_bwd<false>(V, w, p, g3.sh, g3.n, i, e, gmc, Sb, gop, gsh);
+        if constexpr (WIDE) {
+            struct {
+                const double* e;
+                const ScreenGrad<true>* own;
+                __device__ double at(int k) const { return own ? own->at(k) : e[k]; }
+            } src{e, direct ? &own : nullptr};
+            proj_bwd<false>(V, w, p, g3.sh, g3.n, i, src, gmc, Sb, gop, gsh);
+        } else {
+            proj_bwd<false>(V, w, p, g3.sh, g3.n, i, ScreenGrad<false>{direct ? own.rec : e}, gmc, Sb, gop, gsh);
+        }
         gsig += gop;
         for (int r = 0; r < 3; ++r) {
             gmu[r] += gmc[r];
@@ -678,20 +700,20 @@ __device__ inline void bwd_3d(const G3Ptr& g3, int i, int gidx, const ViewParams
 // wave per SIMD (FP64 state of 400+ registers), so sharing the launch costs no
 // occupancy and lets the two sets fill the machine together.
 // TIME: the 4D set carries time coefficients of its colour.
-template <bool TIME>
+template <bool TIME, bool WIDE>
 __global__ void __launch_bounds__(128) k_preprocess_bwd(G3Ptr g3, G4Ptr g4, int nb4, const ViewParams* __restrict__ views,
                                                         int n_views, const Rec* __restrict__ recs,
-                                                        const float* __restrict__ g2, int wide, G3Grad gr3, G4Grad gr4,
+                                                        const float* __restrict__ g2, G3Grad gr3, G4Grad gr4,
                                                         SetStats st3, SetStats st4, int static_rows,
                                                         Status* status) {
     const int N = g3.n + g4.n;
     if (blockIdx.x == 0 && threadIdx.x == 0) status->g2_dirty = 1ull;  // (read by the next backward's prologue)
     if ((int)blockIdx.x < nb4) {
         const int g = blockIdx.x * blockDim.x + threadIdx.x;
-        if (g < g4.n) bwd_4d<TIME>(g4, g, views, n_views, N, recs, g2, wide, gr4, st4);
+        if (g < g4.n) bwd_4d<TIME, WIDE>(g4, g, views, n_views, N, recs, g2, gr4, st4);
     } else {
         const int i = (blockIdx.x - nb4) * blockDim.x + threadIdx.x;
-        if (i < g3.n) bwd_3d(g3, i, g4.n + i, views, n_views, N, recs, g2, wide, gr3, st3, static_rows);
+        if (i < g3.n) bwd_3d<WIDE>(g3, i, g4.n + i, views, n_views, N, recs, g2, gr3, st3, static_rows);
     }
 }
 
@@ -770,12 +792,12 @@ void launch_preprocess_bwd(const G3Ptr& g3, const G4Ptr& g4, const ViewParams* v
     const int N = g3.n + g4.n;
     const int nb4 = ceil_div(g4.n, 128), nb3 = ceil_div(g3.n, 128);
     const int nb = std::max(1, nb4 + nb3);  // (one workgroup at least: it marks the records used)
-    if (g4.sh_t_deg > 0 && N > 0)
-        k_preprocess_bwd<true><<<nb, 128, 0, st>>>(g3, g4, nb4, views, n_views, recs, g2, wide, gr3, gr4, st3, st4,
-                                                   static_rows, status);
-    else
-        k_preprocess_bwd<false><<<nb, 128, 0, st>>>(g3, g4, nb4, views, n_views, recs, g2, wide, gr3, gr4, st3, st4,
-                                                    static_rows, status);
+    const auto run = [&](auto kernel) {
+        kernel<<<nb, 128, 0, st>>>(g3, g4, nb4, views, n_views, recs, g2, gr3, gr4, st3, st4, static_rows, status);
+    };
+    const bool time = g4.sh_t_deg > 0 && N > 0;
+    if (wide) run(time ? k_preprocess_bwd<true, true> : k_preprocess_bwd<false, true>);
+    else run(time ? k_preprocess_bwd<true, false> : k_preprocess_bwd<false, false>);
 }
 
 }  // namespace h4d
