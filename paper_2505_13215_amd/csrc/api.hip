@@ -153,10 +153,7 @@ int bits_for(int n) {
 }
 
 // LSD passes for a key of `bits` bits with digits of at most `width` bits, of
-// near-equal width.  The depth sort uses 8-bit digits (its blocks are few and a
-// wide digit's per-block cost dominates); the super-tile sort up to 11.
-constexpr int kDepthDigitBits = 8;
-constexpr int kDepthSortItems = 2;  // 512 keys per block: ~500 blocks for 250k Gaussians
+// near-equal width (the super-tile sort: up to 11 bits).
 int n_passes_for(int bits, int width) { return (bits + width - 1) / width; }
 // Digit width of pass p (shift bits done) of the super-tile sort over `bits`
 // bits: an even split, except that of two passes the first (over the low,
@@ -207,7 +204,7 @@ struct Layout {
         st_tcost, infer_bytes, st_g2, st_tids, st_chk, min_state_bytes, state_bytes;
     bool quad = false;  // the call's tiles are few enough for the quadrant kernels' checkpoints
     // scratch, forward use
-    size_t sc_dkeys, sc_dvals, sc_dkeys2, sc_dvals2, sc_cnt, sc_rect, sc_offsets, sc_partials, sc_eff, sc_ceff,
+    size_t sc_dkeys, sc_dvals, sc_dpairs, sc_cnt, sc_rect, sc_offsets, sc_partials, sc_eff, sc_ceff,
         sc_pkeys, sc_pvals, sc_pkeys2, sc_pvals2, sc_hist, sc_totals, sc_shape, sc_spans, sc_runs, sc_wcnt, sc_woff, sc_wpart,
         fwd_bytes;
     size_t hist_words = 0, totals_words = 0;  // 32-bit words of the radix histogram / digit totals
@@ -371,8 +368,8 @@ Layout make_layout(int N, int n3, const h4d_view* views, int V, const h4d_config
     Carve f;
     L.sc_dkeys = f.take(4 * np);
     L.sc_dvals = f.take(4 * np);
-    L.sc_dkeys2 = f.take(4 * np);
-    L.sc_dvals2 = f.take(4 * np);
+    L.sc_dpairs = f.take(4 * np);
+    f.take(4 * np);  // (8 bytes per key)
     L.sc_cnt = f.take(4 * np);
     L.sc_rect = f.take(8 * np);
     L.sc_offsets = f.take(8 * (np + 1));
@@ -391,10 +388,12 @@ Layout make_layout(int N, int n3, const h4d_view* views, int V, const h4d_config
         cbits = std::max(cbits, coarse_max_bits(bits_for(L.pass(k).supers)));
     // the depth sort's segments: a pass's views (all Gaussians, or the 4D ones
     // when shared) and the static groups (3D ones)
-    size_t dwords = radix_hist_words(n, max_views, kDepthDigitBits, kDepthSortItems);
+    // (words for 256 counts per 512 keys: five eighths suffice, and the ranked
+    // binning's scratch extends over them)
+    size_t dwords = radix_hist_words(n, max_views, kDepthDigitBits, 2);
     if (L.shared)
-        dwords = std::max(radix_hist_words((uint64_t)L.n4, V, kDepthDigitBits, kDepthSortItems),
-                          radix_hist_words((uint64_t)L.n3, L.n_groups, kDepthDigitBits, kDepthSortItems));
+        dwords = std::max(radix_hist_words((uint64_t)L.n4, V, kDepthDigitBits, 2),
+                          radix_hist_words((uint64_t)L.n3, L.n_groups, kDepthDigitBits, 2));
     L.hist_words = std::max(radix_hist_words(L.ccap, 1, cbits, kSortItems), dwords);
     L.totals_words = (size_t)kMaxRadix * (size_t)max_views;
     L.sc_hist = f.take(4 * L.hist_words);
@@ -433,37 +432,30 @@ struct DepthJob {
     size_t offset;
     int n_seg;
     int len;
+    uint32_t id0;  // id of a segment's first Gaussian
 };
-// Keys per thread of a depth-sort job: two (more, smaller blocks) for short
-// key sets, which are latency-bound; kSortItems from 2^19 keys on, where the
-// longer digit runs of 2048-key blocks coalesce the scatter (one view of 1M
-// Gaussians: 0.121 -> 0.100 ms; 32 views of 1M batched: 0.89 -> 0.60 ms;
-// 250k keys: 0.068 -> 0.083 ms with them).
-int depth_items(const DepthJob& j) {
-    return (uint64_t)j.len * (uint64_t)j.n_seg >= (1ull << 19) ? kSortItems : kDepthSortItems;
-}
 // Whether a pass's segments are short enough to rank by counting pairs of keys.
-// A workgroup places 64 keys against all of its segment's in 0.9 ns per key, one
+// A workgroup places 64 keys against all of its segment's in 1.6 ns per key, one
 // workgroup on each of 256 CUs at a time: 2,000 keys 0.005 ms, 8,000 0.014 ms,
-// 16,000 0.026 ms, 20,000 (two rounds) 0.045 ms.  The radix sort takes 0.045-0.05 ms
-// whatever the length up to there, and eleven launches more.
+// 16,000 0.026 ms.  Bins of sampled keys take 0.021 ms at 10,000 keys and 0.023 at
+// 18,000, and three launches more.
 bool depth_ranks(const DepthJob* jobs, int n) {
     int64_t keys = 0;
     for (int q = 0; q < n; ++q) {
         const int64_t rounds = ((int64_t)jobs[q].n_seg * ((jobs[q].len + 63) / 64) + 255) / 256;
         keys += rounds * jobs[q].len;
     }
-    return keys <= 20000;
+    return keys <= 13000;
 }
 int depth_jobs(const Layout& L, const Pass& P, DepthJob* jobs) {
     const int nv = P.v1 - P.v0;
     int n = 0;
     if (!L.shared) {
-        jobs[n++] = DepthJob{0, nv, L.N};
+        jobs[n++] = DepthJob{0, nv, L.N, 0u};
         return n;
     }
-    if (L.n4 > 0) jobs[n++] = DepthJob{0, nv, L.n4};
-    if (L.n3 > 0) jobs[n++] = DepthJob{(size_t)nv * L.n4, L.n_groups, L.n3};
+    if (L.n4 > 0) jobs[n++] = DepthJob{0, nv, L.n4, 0u};
+    if (L.n3 > 0) jobs[n++] = DepthJob{(size_t)nv * L.n4, L.n_groups, L.n3, (uint32_t)L.n4};
     return n;
 }
 
@@ -472,15 +464,8 @@ bool plan_fits(const Layout& L) {
         const Pass P = L.pass(k);
         DepthJob jobs[2];
         const int nj = depth_jobs(L, P, jobs);
-        const int passes = n_passes_for(32, kDepthDigitBits);
-        for (int q = 0; q < nj; ++q)
-            for (int p = 0, shift = 0; p < passes; ++p) {
-                const int nb = (32 - shift + (passes - p) - 1) / (passes - p);
-                if (!radix_pass_fits((uint64_t)jobs[q].len, jobs[q].n_seg, nb, depth_items(jobs[q]), L.hist_words,
-                                     L.totals_words))
-                    return false;
-                shift += nb;
-            }
+        for (int q = 0; q < nj && !depth_ranks(jobs, nj); ++q)
+            if (depth_plan(jobs[q].len, jobs[q].n_seg).words > L.hist_words) return false;
         const int bits = bits_for(P.supers);
         const int cp = n_passes_for(bits, kMaxRadixBits);
         for (int p = 0, shift = 0; p < cp; ++p) {
@@ -623,37 +608,20 @@ bool bin_pass(h4d_ctx* c, const Layout& L, const Pass& P, int tile, int cull, vo
     const ViewParams* vp = at<ViewParams>(state, L.st_views);
     uint32_t* dk = at<uint32_t>(scratch, L.sc_dkeys);
     uint32_t* dv = at<uint32_t>(scratch, L.sc_dvals);
-    uint32_t* dk2 = at<uint32_t>(scratch, L.sc_dkeys2);
-    uint32_t* dv2 = at<uint32_t>(scratch, L.sc_dvals2);
+    uint64_t* pairs = at<uint64_t>(scratch, L.sc_dpairs);
     uint32_t* hist = at<uint32_t>(scratch, L.sc_hist);
     uint32_t* totals = at<uint32_t>(scratch, L.sc_totals);
     {
-        // depth order per segment: stable LSD passes over the float32 depth bits
+        // depth order per segment: (float32 depth bits, id)
         StageScope sc(c, st, H4D_STAGE_DEPTH_SORT);
         DepthJob jobs[2];
         const int nj = depth_jobs(L, P, jobs);
-        if (depth_ranks(jobs, nj)) {
-            for (int q = 0; q < nj; ++q)
-                launch_rank_sort(dk + jobs[q].offset, dv + jobs[q].offset, dv2 + jobs[q].offset, jobs[q].len,
-                                 jobs[q].n_seg, st);
-            std::swap(dv, dv2);
-        } else {
-            const int passes = n_passes_for(32, kDepthDigitBits);
-            int shift = 0;
-            for (int pass = 0; pass < passes; ++pass) {
-                const int nb = (32 - shift + (passes - pass) - 1) / (passes - pass);
-                for (int q = 0; q < nj; ++q) {
-                    const size_t o = jobs[q].offset;
-                    if (!launch_radix_pass(dk + o, dv + o, dk2 + o, dv2 + o, nullptr, (uint64_t)jobs[q].len,
-                                           (uint64_t)jobs[q].len, shift, nb, hist, L.hist_words, totals,
-                                           L.totals_words, nullptr, st, jobs[q].n_seg, (uint64_t)jobs[q].len, nullptr,
-                                           0, depth_items(jobs[q])))
-                        return false;
-                }
-                std::swap(dk, dk2);
-                std::swap(dv, dv2);
-                shift += nb;
-            }
+        const bool ranks = depth_ranks(jobs, nj);
+        for (int q = 0; q < nj; ++q) {
+            const size_t o = jobs[q].offset;
+            if (!launch_depth_sort(dk + o, jobs[q].id0, dv + o, jobs[q].len, jobs[q].n_seg, ranks, pairs + o, hist,
+                                   L.hist_words, totals, L.totals_words, st))
+                return false;
         }
     }
     // dv now holds the depth-ordered ids
@@ -711,7 +679,7 @@ bool bin_pass(h4d_ctx* c, const Layout& L, const Pass& P, int tile, int cull, vo
         uint32_t* vout = last ? nullptr : (vin == pv ? pv2 : pv);
         if (!launch_radix_pass(kin, vin, kout, vout, p == 0 ? eff_c : ceff, 0, L.ccap, shift, nb, hist,
                                L.hist_words, totals, L.totals_words, last ? out0 : nullptr, st, 1, 0,
-                               passes == 1 ? cranges : nullptr, P.supers, kSortItems, last ? dv : nullptr,
+                               passes == 1 ? cranges : nullptr, P.supers, last ? dv : nullptr,
                                (drop && p == 0) ? 1 : 0, (drop && p == 0) ? ceff : nullptr, last ? coarse : nullptr))
             return false;
         kin = kout;
@@ -852,8 +820,7 @@ static h4d_status render_forward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d*
         {
             StageScope sc(ctx, st, H4D_STAGE_PREPROCESS);
             launch_preprocess(p3, p4, vp, P.v0, P.v1 - P.v0, L.shared ? 1 : 0, at<Rec>(state, L.st_recs),
-                              at<uint32_t>(scratch, L.sc_dkeys), at<uint32_t>(scratch, L.sc_dvals),
-                              keep ? at<float>(state, L.st_g2) : nullptr, st);
+                              at<uint32_t>(scratch, L.sc_dkeys), keep ? at<float>(state, L.st_g2) : nullptr, st);
         }
         if (!bin_pass(ctx, L, P, cfg->tile, cfg->cull, state, scratch, st, keep))
             return fail(ctx, H4D_ERR_UNSUPPORTED, "internal: a radix pass did not fit its buffers");
@@ -1062,7 +1029,7 @@ h4d_status h4dgs_rasterize_splats(h4d_ctx* ctx, int32_t n, const float* u, const
                       at<unsigned long long>(state, L.st_cranges), range_words(L), st);
     Rec* recs = at<Rec>(state, L.st_recs);
     launch_splats_to_records(n, u, v, conic, opacity, rgb, radius, depth, visible, width, height, recs,
-                             at<uint32_t>(scratch, L.sc_dkeys), at<uint32_t>(scratch, L.sc_dvals), st);
+                             at<uint32_t>(scratch, L.sc_dkeys), st);
     PtrTable tab;
     std::memset(&tab, 0, sizeof(tab));
     tab.p[0] = image;

@@ -39,7 +39,7 @@ void launch_count_onscreen(const Rec* recs, int N, int n4, const ViewParams* vie
 // static group g (computed for its leader view only) at nv * n4 + g * n3.
 // g2 (may be null): zeroed for every record that covers a pixel.
 void launch_preprocess(const G3Ptr& g3, const G4Ptr& g4, const ViewParams* views, int v0, int nv, int shared,
-                       Rec* recs, uint32_t* dkeys, uint32_t* dvals, float* g2, hipStream_t st);
+                       Rec* recs, uint32_t* dkeys, float* g2, hipStream_t st);
 // static_rows: the adjoint added each static group's 3D gradients into the
 // records of the group's view (no statistics then).  Marks g2 used
 // (status->g2_dirty).  wide: the records' form (kG2Wide).
@@ -48,7 +48,7 @@ void launch_preprocess_bwd(const G3Ptr& g3, const G4Ptr& g4, const ViewParams* v
                            const SetStats& st4, int static_rows, Status* status, hipStream_t st);
 void launch_splats_to_records(int n, const float* u, const float* v, const float* conic, const float* opacity,
                               const float* rgb, const int32_t* radius, const float* depth, const uint8_t* visible,
-                              int W, int H, Rec* recs, uint32_t* dkeys, uint32_t* dvals, hipStream_t st);
+                              int W, int H, Rec* recs, uint32_t* dkeys, hipStream_t st);
 
 // sort.hip
 constexpr int kSortThreads = 256;
@@ -74,9 +74,8 @@ bool radix_pass_fits(uint64_t capacity, int n_seg, int nbits, int items, size_t 
 // the count.  Output positions (keys, values, digit ranges) are offset by
 // *out_offset when out_offset != null.
 // hist / totals hold hist_words / totals_words words; a pass that does not fit
-// them (radix_pass_fits) launches nothing and returns false.  items: keys per
-// thread, kSortItems or 2 (8-bit digits only; for short key sets, more and
-// smaller blocks).
+// them (radix_pass_fits with kSortItems) launches nothing and returns false.
+// vals_in null: value i of a segment is val0 + i.
 // digit_ranges (may be null): for a pass over whole keys, [start, end) of each
 // of the first n_digit_ranges digits in the output.  val_map (may be null):
 // the values written out are val_map[value].  skip_empty: keys whose upper 16
@@ -88,13 +87,25 @@ bool launch_radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, uint32_
                        const unsigned long long* dcount, uint64_t hcount, uint64_t capacity, int shift, int nbits,
                        uint32_t* hist, size_t hist_words, uint32_t* totals, size_t totals_words,
                        const unsigned long long* out_offset, hipStream_t st, int n_seg = 1, uint64_t seg_stride = 0,
-                       int64_t* digit_ranges = nullptr, int n_digit_ranges = 0, int items = kSortItems,
+                       int64_t* digit_ranges = nullptr, int n_digit_ranges = 0,
                        const uint32_t* val_map = nullptr, int skip_empty = 0,
-                       unsigned long long* out_count = nullptr, uint2* pairs_out = nullptr);
-// The values of n_seg segments of n keys each (one after another) in stable
-// ascending key order, in one launch (short segments: n_seg n^2 bounds its time).
-void launch_rank_sort(const uint32_t* keys, const uint32_t* vals, uint32_t* vals_out, int n, int n_seg,
-                      hipStream_t st);
+                       unsigned long long* out_count = nullptr, uint2* pairs_out = nullptr, uint32_t val0 = 0);
+// The ids val0 .. val0 + n - 1 of each of n_seg segments of n depth keys (one
+// after another), in ascending (key, id) order.  ranks: by counting pairs of
+// keys, in one launch (short segments: n_seg n^2 bounds its time); otherwise as
+// depth_plan says, with room for n_seg n pairs at `pairs` and plan words at `work`
+// (256-byte aligned): given less it launches nothing more and returns false.  The
+// keys are scratch.
+constexpr int kDepthDigitBits = 8;
+struct DepthPlan {
+    bool radix;
+    int lg_bins, items, blocks;  // (bins of sampled keys)
+    size_t words;                // 32-bit words of work
+};
+DepthPlan depth_plan(int n, int n_seg);
+bool launch_depth_sort(uint32_t* keys, uint32_t val0, uint32_t* vals_out, int n, int n_seg, bool ranks,
+                       uint64_t* pairs, uint32_t* work, size_t work_words, uint32_t* totals, size_t totals_words,
+                       hipStream_t st);
 int scan_blocks(int n);
 // Exclusive scans of `count` arrays of nparts words, stride apart, in place;
 // their totals go to totals[0 .. count).

@@ -262,8 +262,8 @@ struct TimeColour {
 // Forward kernel: one thread per Gaussian of the merged list [4D | 3D].
 // ---------------------------------------------------------------------------
 // grid.y runs over the views [v0, v0 + gridDim.y): records go to recs[view][N]
-// (absolute), depth keys and ids to the pass's segment layout: unshared,
-// dkeys/dvals[view - v0][N]; shared (static binning per camera), the view's 4D
+// (absolute), depth keys to the pass's segment layout: unshared,
+// dkeys[view - v0][N]; shared (static binning per camera), the view's 4D
 // Gaussians at (view - v0) n4 + g and, for a static group's leader view only,
 // the 3D Gaussians at nv n4 + group n3 + (g - n4) (the other views of the group
 // use the leader's 3D records and compute none).
@@ -271,8 +271,7 @@ struct TimeColour {
 // that cover a pixel.
 __global__ void __launch_bounds__(256) k_preprocess(G3Ptr g3, G4Ptr g4, const ViewParams* __restrict__ views,
                                                     int v0, int shared, Rec* __restrict__ recs,
-                                                    uint32_t* __restrict__ dkeys, uint32_t* __restrict__ dvals,
-                                                    float* __restrict__ g2) {
+                                                    uint32_t* __restrict__ dkeys, float* __restrict__ g2) {
     const int N = g3.n + g4.n;
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= N) return;
@@ -289,7 +288,6 @@ __global__ void __launch_bounds__(256) k_preprocess(G3Ptr g3, G4Ptr g4, const Vi
     }
     recs += (size_t)view * N;
     dkeys += slot - g;
-    dvals += slot - g;
     WorldF w;
     const float* shp;
     int shn, shi;
@@ -347,7 +345,6 @@ __global__ void __launch_bounds__(256) k_preprocess(G3Ptr g3, G4Ptr g4, const Vi
     }
     recs[g] = rec;
     dkeys[g] = key;
-    dvals[g] = (uint32_t)g;
 }
 
 // ---------------------------------------------------------------------------
@@ -780,10 +777,10 @@ void launch_init_state(const ViewTableIn& in, ViewParams* views, Status* status,
 }
 
 void launch_preprocess(const G3Ptr& g3, const G4Ptr& g4, const ViewParams* views, int v0, int nv, int shared,
-                       Rec* recs, uint32_t* dkeys, uint32_t* dvals, float* g2, hipStream_t st) {
+                       Rec* recs, uint32_t* dkeys, float* g2, hipStream_t st) {
     const int N = g3.n + g4.n;
     if (N == 0 || nv == 0) return;
-    k_preprocess<<<dim3(ceil_div(N, 256), nv), 256, 0, st>>>(g3, g4, views, v0, shared, recs, dkeys, dvals, g2);
+    k_preprocess<<<dim3(ceil_div(N, 256), nv), 256, 0, st>>>(g3, g4, views, v0, shared, recs, dkeys, g2);
 }
 
 void launch_preprocess_bwd(const G3Ptr& g3, const G4Ptr& g4, const ViewParams* views, int n_views, const Rec* recs,
@@ -814,8 +811,7 @@ __global__ void __launch_bounds__(256) k_splats_to_records(int n, const float* _
                                                            const int32_t* __restrict__ radius,
                                                            const float* __restrict__ depth,
                                                            const uint8_t* __restrict__ visible, int W, int H,
-                                                           Rec* __restrict__ recs, uint32_t* __restrict__ dkeys,
-                                                           uint32_t* __restrict__ dvals) {
+                                                           Rec* __restrict__ recs, uint32_t* __restrict__ dkeys) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     Rec rec;
@@ -842,15 +838,14 @@ __global__ void __launch_bounds__(256) k_splats_to_records(int n, const float* _
     }
     recs[i] = rec;
     dkeys[i] = key;
-    dvals[i] = (uint32_t)i;
 }
 
 void launch_splats_to_records(int n, const float* u, const float* v, const float* conic, const float* opacity,
                               const float* rgb, const int32_t* radius, const float* depth, const uint8_t* visible,
-                              int W, int H, Rec* recs, uint32_t* dkeys, uint32_t* dvals, hipStream_t st) {
+                              int W, int H, Rec* recs, uint32_t* dkeys, hipStream_t st) {
     if (n == 0) return;
     k_splats_to_records<<<ceil_div(n, 256), 256, 0, st>>>(n, u, v, conic, opacity, rgb, radius, depth, visible, W, H,
-                                                          recs, dkeys, dvals);
+                                                          recs, dkeys);
 }
 
 }  // namespace h4d

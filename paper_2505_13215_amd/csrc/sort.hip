@@ -1,9 +1,9 @@
 // Binning and ordering on gfx950 (Alg. 1: DuplicateWithKeys, SortByKeys,
 // IdentifyTileRanges).
 //
-// Design: the per-view depth order is established once over the N Gaussians
-// (LSD radix sort of the float32 depth bits, stable, so equal depths keep
-// ascending id).  Binning is then two-level: every depth-ordered Gaussian emits
+// Design: the per-view depth order is established once over the N Gaussians (by
+// float32 depth bits, equal depths by ascending id): by counting, by bins of
+// sampled keys, or by a stable LSD radix sort, by length.  Binning is then two-level: every depth-ordered Gaussian emits
 // one coarse entry per super-tile (S x S tiles) its square touches, keyed by
 // the super-tile and carrying the mask of the super-tile's tiles it reaches.
 // Each entry goes straight to its place in its super-tile's depth-ordered list,
@@ -92,8 +92,7 @@ template <int MB, int ITEMS>
 __global__ void __launch_bounds__(kSortThreads) k_radix_upsweep(const uint32_t* __restrict__ keys,
                                                                 const unsigned long long* dcount, uint64_t hcount,
                                                                 int shift, int nbits, uint32_t* __restrict__ hist,
-                                                                int nblocks, uint64_t seg_stride, int skip_empty,
-                                                                int by_block) {
+                                                                int nblocks, uint64_t seg_stride, int skip_empty) {
     __shared__ uint32_t s_hist[4][1 << MB];
     const int radix = 1 << nbits;
     keys += (size_t)blockIdx.y * seg_stride;
@@ -114,8 +113,7 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_upsweep(const uint32_t* 
     }
     __syncthreads();
     for (int d = tid; d < radix; d += kSortThreads)
-        hist[by_block ? (size_t)blockIdx.x * radix + d : (size_t)d * nblocks + blockIdx.x] =
-            s_hist[0][d] + s_hist[1][d] + s_hist[2][d] + s_hist[3][d];
+        hist[(size_t)d * nblocks + blockIdx.x] = s_hist[0][d] + s_hist[1][d] + s_hist[2][d] + s_hist[3][d];
 }
 
 // one block per (digit, segment): exclusive scan of that digit's per-block
@@ -156,7 +154,7 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_downsweep(
     const uint32_t* __restrict__ hist, const uint32_t* __restrict__ totals, int nblocks,
     const unsigned long long* out_offset, uint64_t seg_stride, int64_t* __restrict__ digit_ranges, int n_digit_ranges,
     const uint32_t* __restrict__ val_map, int skip_empty, unsigned long long* out_count,
-    uint2* __restrict__ pairs_out, int by_block) {
+    uint2* __restrict__ pairs_out, uint32_t val0) {
     __shared__ uint32_t s_wcount[4][1 << MB];
     __shared__ uint32_t s_dstart[1 << MB];
     __shared__ uint32_t s_gbase[1 << MB];
@@ -175,7 +173,8 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_downsweep(
     const int radix = 1 << nbits;
     {
         const size_t so = (size_t)blockIdx.y * seg_stride;
-        keys_in += so; vals_in += so; keys_out += so; vals_out += so;
+        keys_in += so; keys_out += so; vals_out += so;
+        if (vals_in) vals_in += so;
         hist += (size_t)blockIdx.y * radix * nblocks;
         totals += (size_t)blockIdx.y * radix;
     }
@@ -184,25 +183,7 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_downsweep(
 
     for (int d = tid; d < 4 * radix; d += kSortThreads) s_wcount[d / radix][d % radix] = 0;
     // global base of digit d = (exclusive scan of totals)[d] + this block's scanned count
-    uint32_t before = 0u, total = 0u;  // by_block: of digit tid (radix <= kSortThreads)
-    if (by_block) {
-        if (tid < radix) {
-            const int live = (int)min((uint64_t)nblocks, (n + TILE - 1) / TILE);
-            for (int b = 0; b < live; b += 8) {
-                uint32_t v[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = b + q < live ? hist[(size_t)(b + q) * radix + tid] : 0u;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    total += v[q];
-                    before += b + q < (int)blockIdx.x ? v[q] : 0u;
-                }
-            }
-            s_gbase[tid] = total;
-        }
-    } else {
-        for (int d = tid; d < radix; d += kSortThreads) s_gbase[d] = totals[d];
-    }
+    for (int d = tid; d < radix; d += kSortThreads) s_gbase[d] = totals[d];
     __syncthreads();
     const uint32_t n_out = block_scan_digits<MB>(s_gbase, radix, s_buf);
     if (out_count && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *out_count = n_out;
@@ -213,8 +194,7 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_downsweep(
             digit_ranges[2 * (size_t)d] = (int64_t)off + s_gbase[d];
             digit_ranges[2 * (size_t)d + 1] = (int64_t)off + s_gbase[d] + totals[d];
         }
-    for (int d = tid; d < radix; d += kSortThreads)
-        s_gbase[d] += by_block ? before : hist[(size_t)d * nblocks + blockIdx.x];
+    for (int d = tid; d < radix; d += kSortThreads) s_gbase[d] += hist[(size_t)d * nblocks + blockIdx.x];
 
     // wave w owns items [begin + w * 64 ITEMS, begin + (w + 1) * 64 ITEMS), ITEMS rounds of 64
     uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
@@ -223,7 +203,7 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_downsweep(
         const uint64_t idx = begin + (uint64_t)w * (ITEMS * 64) + (uint64_t)r * 64 + lane;
         key[r] = idx < n ? keys_in[idx] : 0u;
         const bool valid = idx < n && (!skip_empty || (key[r] >> 16) != 0u);
-        val[r] = valid ? vals_in[idx] : 0u;
+        val[r] = !valid ? 0u : vals_in ? vals_in[idx] : val0 + (uint32_t)idx;
         const uint32_t d = (key[r] >> shift) & mask;
         unsigned long long peers = __ballot(valid);
         for (int b = 0; b < nbits; ++b) {
@@ -275,8 +255,6 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_downsweep(
     }
 }
 
-constexpr int kDirectBlocks = 48;  // (launch_radix_pass)
-
 int radix_blocks(uint64_t capacity, int items) {
     const uint64_t tile = (uint64_t)kSortThreads * items;
     return (int)((capacity + tile - 1) / tile);
@@ -296,40 +274,29 @@ bool launch_radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, uint32_
                        const unsigned long long* dcount, uint64_t hcount, uint64_t capacity, int shift, int nbits,
                        uint32_t* hist, size_t hist_words, uint32_t* totals, size_t totals_words,
                        const unsigned long long* out_offset, hipStream_t st, int n_seg, uint64_t seg_stride,
-                       int64_t* digit_ranges, int n_digit_ranges, int items, const uint32_t* val_map, int skip_empty,
-                       unsigned long long* out_count, uint2* pairs_out) {
+                       int64_t* digit_ranges, int n_digit_ranges, const uint32_t* val_map, int skip_empty,
+                       unsigned long long* out_count, uint2* pairs_out, uint32_t val0) {
     // every block writes 2^nbits counts per segment: refuse a pass whose
     // histogram or digit totals would not fit the buffers it was given
-    if (!radix_pass_fits(capacity, n_seg, nbits, items, hist_words, totals_words)) return false;
-    const int nb = radix_blocks(capacity, items);
+    if (!radix_pass_fits(capacity, n_seg, nbits, kSortItems, hist_words, totals_words)) return false;
+    const int nb = radix_blocks(capacity, kSortItems);
     if (nb == 0 || n_seg == 0) return true;
     const dim3 grid(nb, n_seg);
-    // few blocks: the histograms stay block by block, and every scatter block sums
-    // the rows itself (a load per block, eight in flight), which costs less than a
-    // launch (four passes over 20,000 keys, 40 blocks: 0.049 -> 0.044 ms; 32,000 keys,
-    // 63 blocks: even)
-    const int by_block = nbits <= 8 && nb <= kDirectBlocks && !digit_ranges ? 1 : 0;
     // the smallest instantiation that holds the digit (LDS is sized by it)
-#define H4D_RADIX_PASS(MB, IT)                                                                                       \
+#define H4D_RADIX_PASS(MB)                                                                                            \
     do {                                                                                                              \
-        k_radix_upsweep<MB, IT><<<grid, kSortThreads, 0, st>>>(keys_in, dcount, hcount, shift, nbits, hist, nb,       \
-                                                              seg_stride, skip_empty, by_block);                     \
-        if (!by_block)                                                                                                \
-            k_radix_digit_scan<<<dim3(1 << nbits, n_seg), 256, 0, st>>>(hist, nb, 1 << nbits, totals, dcount, hcount, \
-                                                                        kSortThreads * IT);                           \
-        k_radix_downsweep<MB, IT><<<grid, kSortThreads, 0, st>>>(keys_in, vals_in, keys_out, vals_out, dcount,        \
-                                                                hcount, shift, nbits, hist, totals, nb, out_offset,   \
-                                                                seg_stride, digit_ranges, n_digit_ranges, val_map,    \
-                                                                skip_empty, out_count, pairs_out, by_block);          \
+        k_radix_upsweep<MB, kSortItems><<<grid, kSortThreads, 0, st>>>(keys_in, dcount, hcount, shift, nbits, hist,   \
+                                                                      nb, seg_stride, skip_empty);                   \
+        k_radix_digit_scan<<<dim3(1 << nbits, n_seg), 256, 0, st>>>(hist, nb, 1 << nbits, totals, dcount, hcount,     \
+                                                                    kSortTile);                                      \
+        k_radix_downsweep<MB, kSortItems><<<grid, kSortThreads, 0, st>>>(                                            \
+            keys_in, vals_in, keys_out, vals_out, dcount, hcount, shift, nbits, hist, totals, nb, out_offset,         \
+            seg_stride, digit_ranges, n_digit_ranges, val_map, skip_empty, out_count, pairs_out, val0);               \
     } while (0)
-    if (items == 2 && nbits <= 8) {
-        H4D_RADIX_PASS(8, 2);  // short key sets: more, smaller blocks
-    } else {  // (a grid sized for smaller blocks only adds blocks past the live count)
-        if (nbits <= 8) H4D_RADIX_PASS(8, kSortItems);
-        else if (nbits == 9) H4D_RADIX_PASS(9, kSortItems);
-        else if (nbits == 10) H4D_RADIX_PASS(10, kSortItems);
-        else H4D_RADIX_PASS(kMaxRadixBits, kSortItems);
-    }
+    if (nbits <= 8) H4D_RADIX_PASS(8);
+    else if (nbits == 9) H4D_RADIX_PASS(9);
+    else if (nbits == 10) H4D_RADIX_PASS(10);
+    else H4D_RADIX_PASS(kMaxRadixBits);
 #undef H4D_RADIX_PASS
     return true;
 }
@@ -373,12 +340,11 @@ __device__ __forceinline__ uint32_t rank_count(const uint32_t* __restrict__ keys
 }
 
 __global__ void __launch_bounds__(64 * kRankWaves) k_rank_sort(const uint32_t* __restrict__ keys,
-                                                             const uint32_t* __restrict__ vals,
-                                                             uint32_t* __restrict__ vals_out, int n) {
+                                                             uint32_t val0, uint32_t* __restrict__ vals_out,
+                                                             int n) {
     __shared__ uint32_t s_rank[kRankWaves][64];
     const size_t seg = (size_t)blockIdx.y * n;
     keys += seg;
-    vals += seg;
     vals_out += seg;
     const int lane = __lane_id(), w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int i0 = (int)blockIdx.x * 64, i = i0 + lane;
@@ -399,14 +365,426 @@ __global__ void __launch_bounds__(64 * kRankWaves) k_rank_sort(const uint32_t* _
         uint32_t at = 0u;
 #pragma unroll
         for (int q = 0; q < kRankWaves; ++q) at += s_rank[q][lane];
-        vals_out[at] = vals[i];
+        vals_out[at] = val0 + (uint32_t)i;
     }
 }
 
-void launch_rank_sort(const uint32_t* keys, const uint32_t* vals, uint32_t* vals_out, int n, int n_seg,
-                      hipStream_t st) {
-    if (n <= 0 || n_seg <= 0) return;
-    k_rank_sort<<<dim3((unsigned)((n + 63) / 64), (unsigned)n_seg), 64 * kRankWaves, 0, st>>>(keys, vals, vals_out, n);
+// ---------------------------------------------------------------------------
+// Longer depth sorts: bins between sampled keys, each bin ordered in LDS.
+// ---------------------------------------------------------------------------
+// Keys are ordered as 64-bit pairs (depth bits, id), which are all different, so
+// bins of a fixed share of the keys exist for any input (equal depths and culled
+// splats included), a bin's keys may arrive in any order, and the result is the
+// stable order.  Four samples per bin, one at a hashed place of each equal stretch
+// of the segment, give the bounds; a counting and a scattering launch move the keys
+// to their bins, and one workgroup per bin orders it.  The keys are read twice and
+// moved once (an 8-bit radix sort reads them eight times and moves them four), in
+// four or five launches instead of twelve: 18,000 keys 0.054 -> 0.023 ms, 250,000
+// 0.065 -> 0.041, 500,000 0.079 -> 0.053, eight segments of 500,000 0.212 -> 0.177.
+// Short segments are bound by the launches and one trip through memory in each,
+// long ones by the searches in LDS (k_depth_bins, 19 ns per 1000 keys).
+constexpr int kSplitThreads = 1024;
+constexpr int kSplitOver = 4;
+constexpr int kSplitMaxBins = 2048;
+// Up to here a scatter workgroup sums the counting workgroups' rows itself, a load
+// per row; beyond, a launch scans them first.
+constexpr int kSplitDirect = 64;
+constexpr int kBinWaves = 8;
+constexpr int kBinKeys = 4096;  // a bin's keys held in LDS (32 KB)
+
+// The radix sort takes the segments whose bounds cost more than its passes: 1M keys
+// 0.089 ms here against 0.100, 2M 0.154 against 0.125 (four segments of 1M take the
+// radix sort 0.206 ms).
+DepthPlan depth_plan(int n, int n_seg) {
+    DepthPlan p;
+    const bool large = n > (1 << 19);
+    p.radix = large && (int64_t)n * n_seg > (1 << 20);
+    p.lg_bins = 6;
+    while (p.lg_bins < (large ? 11 : 10) && ((int64_t)256 << p.lg_bins) < n) ++p.lg_bins;
+    p.items = large ? 8 : 4;
+    p.blocks = (int)(((int64_t)n + kSplitThreads * p.items - 1) / (kSplitThreads * p.items));
+    // per segment and bin: the bound (64 bits), total, start, and a row per workgroup
+    p.words = p.radix ? radix_hist_words((uint64_t)n, n_seg, kDepthDigitBits, kSortItems)
+                      : ((size_t)n_seg << p.lg_bins) * (4 + (size_t)p.blocks);
+    return p;
+}
+
+// Place of sample j of 2^lg: a hashed one of [j n / 2^lg, (j + 1) n / 2^lg).
+__device__ __forceinline__ int sample_place(int j, int n, int lg) {
+    const int lo = (int)(((uint64_t)j * (uint32_t)n) >> lg), hi = (int)(((uint64_t)(j + 1) * (uint32_t)n) >> lg);
+    uint32_t h = (uint32_t)j * 0x9E3779B1u;
+    h ^= h >> 15;
+    h *= 0x85EBCA77u;
+    h ^= h >> 13;
+    return min(lo + (int)(((uint64_t)h * (uint32_t)max(1, hi - lo)) >> 32), n - 1);
+}
+
+__device__ __forceinline__ uint64_t depth_pair(uint32_t key, uint32_t val) { return ((uint64_t)key << 32) | val; }
+
+// A workgroup ranks kSplitRanked samples against all: a sixty-fourth of them per
+// quarter of a wave, keys read from LDS four at a time, the same for a quarter's
+// lanes.  Every fourth sample in order is a bin's lower bound.
+constexpr int kSplitRanked = 16;
+__global__ void __launch_bounds__(kSplitThreads) k_depth_bounds(const uint32_t* __restrict__ keys, uint32_t val0, int n,
+                                                                int lg_bins, uint64_t* __restrict__ bounds) {
+    __shared__ __align__(16) uint32_t s_keys[kSplitOver * kSplitMaxBins];
+    __shared__ uint32_t s_rank[kSplitThreads / 64][kSplitRanked];
+    const int lg = lg_bins + 2, S = 1 << lg;  // (kSplitOver = 4)
+    keys += (size_t)blockIdx.y * n;
+    bounds += (size_t)blockIdx.y << lg_bins;
+    for (int j = threadIdx.x; j < S; j += kSplitThreads) s_keys[j] = keys[sample_place(j, n, lg)];
+    __syncthreads();
+    const int lane = __lane_id(), w = (int)threadIdx.x >> 6;
+    const int i0 = (int)blockIdx.x * kSplitRanked, i = i0 + lane % kSplitRanked;
+    const uint32_t key = s_keys[i];
+    const int per = S / 64, j0 = (w * 4 + lane / kSplitRanked) * per, j1 = j0 + per;  // (multiples of four)
+    uint32_t r = 0u;
+    // samples lie in id order: equal keys of lower index come before
+#pragma unroll 4
+    for (int j = j0; j < min(j1, i0); j += 4) {
+        const uint4 k = *reinterpret_cast<const uint4*>(&s_keys[j]);
+        r += (k.x <= key ? 1u : 0u) + (k.y <= key ? 1u : 0u) + (k.z <= key ? 1u : 0u) + (k.w <= key ? 1u : 0u);
+    }
+    for (int j = max(j0, i0); j < min(j1, i0 + kSplitRanked); ++j) {
+        const uint32_t k = s_keys[j];
+        r += (k < key || (k == key && j < i)) ? 1u : 0u;
+    }
+#pragma unroll 4
+    for (int j = max(j0, i0 + kSplitRanked); j < j1; j += 4) {
+        const uint4 k = *reinterpret_cast<const uint4*>(&s_keys[j]);
+        r += (k.x < key ? 1u : 0u) + (k.y < key ? 1u : 0u) + (k.z < key ? 1u : 0u) + (k.w < key ? 1u : 0u);
+    }
+    r += __shfl_xor(r, 16);
+    r += __shfl_xor(r, 32);
+    if (lane < kSplitRanked) s_rank[w][lane] = r;
+    __syncthreads();
+    if (threadIdx.x < kSplitRanked) {
+        uint32_t at = 0u;
+#pragma unroll
+        for (int q = 0; q < kSplitThreads / 64; ++q) at += s_rank[q][lane];
+        if (at > 0u && at % kSplitOver == 0u)
+            bounds[at / kSplitOver - 1] = depth_pair(key, val0 + (uint32_t)sample_place(i, n, lg));
+    }
+}
+
+// Counts of a workgroup's keys per bin (a row of 2^lg_bins), and each key's bin.
+template <int ITEMS>
+__global__ void __launch_bounds__(kSplitThreads) k_depth_count(const uint32_t* __restrict__ keys, uint32_t val0, int n,
+                                                               int lg_bins, const uint64_t* __restrict__ bounds,
+                                                               uint16_t* __restrict__ key_bin,
+                                                               uint32_t* __restrict__ rows) {
+    __shared__ uint64_t s_bound[kSplitMaxBins];
+    __shared__ uint32_t s_count[kSplitMaxBins];
+    const int tid = threadIdx.x, bins = 1 << lg_bins;
+    const size_t seg = (size_t)blockIdx.y * n;
+    const int begin = (int)blockIdx.x * (kSplitThreads * ITEMS);
+    bounds += (size_t)blockIdx.y << lg_bins;
+    uint64_t x[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = begin + k * kSplitThreads + tid;
+        x[k] = depth_pair(i < n ? keys[seg + i] : 0u, val0 + (uint32_t)i);
+    }
+    for (int d = tid; d < bins; d += kSplitThreads) {
+        s_bound[d] = d < bins - 1 ? bounds[d] : ~0ull;
+        s_count[d] = 0u;
+    }
+    __syncthreads();
+    int at[ITEMS];  // bounds at or below the key
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) at[k] = 0;
+    for (int step = bins >> 1; step > 0; step >>= 1) {
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) at[k] += s_bound[at[k] + step - 1] <= x[k] ? step : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = begin + k * kSplitThreads + tid;
+        if (i < n) {
+            key_bin[seg + i] = (uint16_t)at[k];
+            atomicAdd(&s_count[at[k]], 1u);
+        }
+    }
+    __syncthreads();
+    rows += ((size_t)blockIdx.y * gridDim.x + blockIdx.x) << lg_bins;
+    for (int d = tid; d < bins; d += kSplitThreads) rows[d] = s_count[d];
+}
+
+// Exclusive scan of the rows down each bin's column, in place, and the totals: a
+// workgroup takes 64 bins, each of its sixteen waves a sixteenth of the rows.
+__global__ void __launch_bounds__(kSplitThreads) k_depth_columns(uint32_t* __restrict__ rows, int blocks, int lg_bins,
+                                                                 uint32_t* __restrict__ totals) {
+    __shared__ uint32_t s_sum[kSplitThreads / 64][64];
+    const int lane = __lane_id(), w = (int)threadIdx.x >> 6, d = (int)blockIdx.x * 64 + lane;
+    uint32_t* col = rows + (((size_t)blockIdx.y * blocks) << lg_bins) + d;
+    const int per = (blocks + kSplitThreads / 64 - 1) / (kSplitThreads / 64);
+    const int b0 = min(blocks, w * per), b1 = min(blocks, b0 + per);
+    uint32_t sum = 0u;
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) sum += col[(size_t)b << lg_bins];
+    s_sum[w][lane] = sum;
+    __syncthreads();
+    uint32_t run = 0u, total = 0u;
+#pragma unroll
+    for (int q = 0; q < kSplitThreads / 64; ++q) {
+        const uint32_t v = s_sum[q][lane];
+        run += q < w ? v : 0u;
+        total += v;
+    }
+    for (int b = b0; b < b1; b += 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = b + q < b1 ? col[(size_t)(b + q) << lg_bins] : 0u;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            if (b + q < b1) col[(size_t)(b + q) << lg_bins] = run;
+            run += v[q];
+        }
+    }
+    if (w == 0) totals[((size_t)blockIdx.y << lg_bins) + d] = total;
+}
+
+// In-place exclusive scan of s[0 .. n), n <= 2048, by 1024 threads.
+__device__ inline void block_scan_1024(uint32_t* s, int n, uint32_t* s_buf) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int per = n > kSplitThreads ? 2 : 1, d = tid * per;
+    const uint32_t v0 = d < n ? s[d] : 0u, v1 = per == 2 ? s[d + 1] : 0u;
+    uint32_t incl = v0 + v1;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off);
+        if (lane >= off) incl += y;
+    }
+    if (lane == 63) s_buf[w] = incl;
+    __syncthreads();
+    uint32_t run = incl - v0 - v1;
+    for (int k = 0; k < w; ++k) run += s_buf[k];
+    if (d < n) s[d] = run;
+    if (per == 2) s[d + 1] = run + v0;
+    __syncthreads();
+}
+
+// Keys to their bins (in any order inside), as pairs, through LDS so that a
+// workgroup's keys of one bin are written together.
+template <int ITEMS>
+__global__ void __launch_bounds__(kSplitThreads) k_depth_scatter(const uint32_t* __restrict__ keys, uint32_t val0, int n,
+                                                                 int lg_bins, const uint16_t* __restrict__ key_bin,
+                                                                 const uint32_t* __restrict__ rows, int direct,
+                                                                 const uint32_t* __restrict__ totals,
+                                                                 uint32_t* __restrict__ starts,
+                                                                 uint64_t* __restrict__ pairs) {
+    constexpr int T = kSplitThreads * ITEMS;
+    __shared__ uint64_t s_pair[T];
+    __shared__ uint16_t s_bin[T];
+    __shared__ uint32_t s_base[kSplitMaxBins], s_first[kSplitMaxBins];
+    __shared__ uint32_t s_buf[kSplitThreads / 64];
+    const int tid = threadIdx.x, bins = 1 << lg_bins, blocks = gridDim.x;
+    const size_t seg = (size_t)blockIdx.y * n;
+    const int begin = (int)blockIdx.x * T;
+    uint32_t key[ITEMS];
+    int bin[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = begin + k * kSplitThreads + tid;
+        key[k] = i < n ? keys[seg + i] : 0u;
+        bin[k] = i < n ? (int)key_bin[seg + i] : -1;
+    }
+    rows += ((size_t)blockIdx.y * blocks) << lg_bins;
+    uint32_t before[kSplitMaxBins / kSplitThreads];
+#pragma unroll
+    for (int q = 0; q < kSplitMaxBins / kSplitThreads; ++q) {
+        const int d = q * kSplitThreads + tid;
+        before[q] = 0u;
+        if (d >= bins) continue;
+        uint32_t total = 0u;
+        if (direct) {
+            for (int b = 0; b < blocks; b += 16) {
+                uint32_t v[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) v[u] = b + u < blocks ? rows[((size_t)(b + u) << lg_bins) + d] : 0u;
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    total += v[u];
+                    before[q] += b + u < (int)blockIdx.x ? v[u] : 0u;
+                }
+            }
+        } else {
+            total = totals[((size_t)blockIdx.y << lg_bins) + d];
+            before[q] = rows[((size_t)blockIdx.x << lg_bins) + d];
+        }
+        s_base[d] = total;
+        s_first[d] = 0u;
+    }
+    __syncthreads();
+    uint32_t rank[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) rank[k] = bin[k] >= 0 ? atomicAdd(&s_first[bin[k]], 1u) : 0u;
+    block_scan_1024(s_base, bins, s_buf);  // (its barriers also order the counts)
+    block_scan_1024(s_first, bins, s_buf);
+#pragma unroll
+    for (int q = 0; q < kSplitMaxBins / kSplitThreads; ++q) {
+        const int d = q * kSplitThreads + tid;
+        if (d >= bins) continue;
+        if (blockIdx.x == 0) starts[((size_t)blockIdx.y << lg_bins) + d] = s_base[d];
+        s_base[d] += before[q] - s_first[d];
+    }
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        if (bin[k] < 0) continue;
+        const uint32_t p = s_first[bin[k]] + rank[k];
+        s_pair[p] = depth_pair(key[k], val0 + (uint32_t)(begin + k * kSplitThreads + tid));
+        s_bin[p] = (uint16_t)bin[k];
+    }
+    __syncthreads();
+    const int cnt = min(T, n - begin);
+    for (int p = tid; p < cnt; p += kSplitThreads) pairs[seg + (uint32_t)(s_base[s_bin[p]] + (uint32_t)p)] = s_pair[p];
+}
+
+// The value of lane ^ J (14 of the 21 exchanges of a 64-lane sort stay in the
+// vector unit).
+template <int J>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t x) {
+    if constexpr (J == 1 || J == 2 || J == 8) {
+        constexpr int ctrl = J == 1 ? 0xB1 : J == 2 ? 0x4E : 0x128;  // quad_perm 1032, 2301; row_ror 8
+        const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)x, ctrl, 0xF, 0xF, true);
+        const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(x >> 32), ctrl, 0xF, 0xF, true);
+        return depth_pair(hi, lo);
+    } else {
+        return __shfl_xor((unsigned long long)x, J);
+    }
+}
+template <int K, int J>
+__device__ __forceinline__ void lane_merge(uint64_t& x, int lane) {
+    const uint64_t y = lane_xor<J>(x);
+    const bool low = ((lane & J) == 0) == ((lane & K) == 0);
+    x = (y < x) == low ? y : x;
+    if constexpr (J > 1) lane_merge<K, J / 2>(x, lane);
+}
+
+// Runs of 64 of a block of m <= kBinKeys keys, each ordered among the lanes of one
+// wave (padded with keys above all).
+__device__ inline void bin_runs(const uint64_t* __restrict__ pairs, int m, uint64_t* s_run) {
+    const int lane = __lane_id(), w = (int)threadIdx.x >> 6;
+    for (int c = w; c * 64 < m; c += kBinWaves) {
+        const int e = c * 64 + lane;
+        uint64_t x = e < m ? pairs[e] : ~0ull;
+        lane_merge<2, 1>(x, lane);
+        lane_merge<4, 2>(x, lane);
+        lane_merge<8, 4>(x, lane);
+        lane_merge<16, 8>(x, lane);
+        lane_merge<32, 16>(x, lane);
+        lane_merge<64, 32>(x, lane);
+        s_run[e] = x;
+    }
+}
+
+// Keys below x in the runs [c0, c1).
+__device__ __forceinline__ uint32_t runs_below(const uint64_t* s_run, int c0, int c1, uint64_t x) {
+    uint32_t r = 0u;
+#pragma unroll 4
+    for (int c = c0; c < c1; ++c) {
+        const uint64_t* run = s_run + c * 64;
+        uint32_t at = 0u;
+#pragma unroll
+        for (int step = 32; step > 0; step >>= 1) at += run[at + step - 1] < x ? step : 0;
+        r += at + (run[at] < x ? 1u : 0u);
+    }
+    return r;
+}
+
+// One bin in order: a key's place is its place in its run plus the keys below it in
+// every other run.  A bin of more than kBinKeys keys goes block against block.
+__global__ void __launch_bounds__(64 * kBinWaves) k_depth_bins(const uint64_t* __restrict__ pairs, int n, int lg_bins,
+                                                    const uint32_t* __restrict__ starts, uint32_t* __restrict__ vals_out) {
+    __shared__ uint64_t s_run[kBinKeys];
+    const int bin = blockIdx.x, tid = threadIdx.x, lane = __lane_id(), w = tid >> 6;
+    starts += (size_t)blockIdx.y << lg_bins;
+    const int begin = (int)starts[bin], m = (bin + 1 < (1 << lg_bins) ? (int)starts[bin + 1] : n) - begin;
+    pairs += (size_t)blockIdx.y * n + begin;
+    vals_out += (size_t)blockIdx.y * n + begin;
+    if (m <= kBinKeys) {
+        bin_runs(pairs, m, s_run);
+        __syncthreads();
+        const int runs = (m + 63) / 64;
+        for (int c = w; c < runs; c += kBinWaves) {
+            const uint64_t x = s_run[c * 64 + lane];
+            const uint32_t r = lane + runs_below(s_run, 0, c, x) + runs_below(s_run, c + 1, runs, x);
+            if (c * 64 + lane < m) vals_out[r] = (uint32_t)x;
+        }
+        return;
+    }
+    constexpr int PER = kBinKeys / (64 * kBinWaves);
+    for (int e0 = 0; e0 < m; e0 += kBinKeys) {
+        uint64_t x[PER];
+        uint32_t r[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int e = e0 + k * (64 * kBinWaves) + tid;
+            x[k] = e < m ? pairs[e] : 0ull;
+            r[k] = 0u;
+        }
+        for (int b = 0; b < m; b += kBinKeys) {
+            const int mb = min(kBinKeys, m - b);
+            __syncthreads();
+            bin_runs(pairs + b, mb, s_run);
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < PER; ++k) r[k] += runs_below(s_run, 0, (mb + 63) / 64, x[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (e0 + k * (64 * kBinWaves) + tid < m) vals_out[r[k]] = (uint32_t)x[k];
+    }
+}
+
+bool launch_depth_sort(uint32_t* keys, uint32_t val0, uint32_t* vals_out, int n, int n_seg, bool ranks,
+                       uint64_t* pairs, uint32_t* work, size_t work_words, uint32_t* totals, size_t totals_words,
+                       hipStream_t st) {
+    if (n <= 0 || n_seg <= 0) return true;
+    if (ranks) {
+        k_rank_sort<<<dim3((unsigned)((n + 63) / 64), (unsigned)n_seg), 64 * kRankWaves, 0, st>>>(keys, val0, vals_out, n);
+        return true;
+    }
+    const DepthPlan p = depth_plan(n, n_seg);
+    if (p.words > work_words) return false;
+    if (p.radix) {
+        uint32_t* keys2 = reinterpret_cast<uint32_t*>(pairs);
+        uint32_t* vals2 = keys2 + (size_t)n * n_seg;
+        static_assert(32 % (2 * kDepthDigitBits) == 0, "the last pass ends in vals_out");
+        for (int shift = 0; shift < 32; shift += kDepthDigitBits) {
+            const bool odd = shift / kDepthDigitBits % 2 != 0;
+            if (!launch_radix_pass(odd ? keys2 : keys, shift == 0 ? nullptr : odd ? vals2 : vals_out, odd ? keys : keys2,
+                                   odd ? vals_out : vals2, nullptr, (uint64_t)n, (uint64_t)n, shift, kDepthDigitBits,
+                                   work, work_words, totals, totals_words, nullptr, st, n_seg, (uint64_t)n, nullptr, 0,
+                                   nullptr, 0, nullptr, nullptr, val0))
+                return false;
+        }
+        return true;
+    }
+    const size_t bins = (size_t)1 << p.lg_bins;
+    uint64_t* bounds = reinterpret_cast<uint64_t*>(work);
+    uint32_t* counts = work + 2 * bins * n_seg;
+    uint32_t* starts = counts + bins * n_seg;
+    uint32_t* rows = starts + bins * n_seg;
+    uint16_t* key_bin = reinterpret_cast<uint16_t*>(vals_out);  // (until the bins are in order)
+    const int direct = p.blocks <= kSplitDirect ? 1 : 0;
+    const unsigned segs = (unsigned)n_seg;
+    const dim3 grid((unsigned)p.blocks, segs);
+    k_depth_bounds<<<dim3((unsigned)(kSplitOver * bins / kSplitRanked), segs), kSplitThreads, 0, st>>>(keys, val0, n, p.lg_bins,
+                                                                                          bounds);
+    if (p.items == 4)
+        k_depth_count<4><<<grid, kSplitThreads, 0, st>>>(keys, val0, n, p.lg_bins, bounds, key_bin, rows);
+    else
+        k_depth_count<8><<<grid, kSplitThreads, 0, st>>>(keys, val0, n, p.lg_bins, bounds, key_bin, rows);
+    if (!direct)
+        k_depth_columns<<<dim3((unsigned)(bins / 64), segs), kSplitThreads, 0, st>>>(rows, p.blocks, p.lg_bins, counts);
+    if (p.items == 4)
+        k_depth_scatter<4><<<grid, kSplitThreads, 0, st>>>(keys, val0, n, p.lg_bins, key_bin, rows, direct, counts, starts,
+                                                         pairs);
+    else
+        k_depth_scatter<8><<<grid, kSplitThreads, 0, st>>>(keys, val0, n, p.lg_bins, key_bin, rows, direct, counts, starts,
+                                                         pairs);
+    k_depth_bins<<<dim3((unsigned)bins, segs), 64 * kBinWaves, 0, st>>>(pairs, n, p.lg_bins, starts, vals_out);
+    return true;
 }
 
 // ---------------------------------------------------------------------------

@@ -63,3 +63,31 @@ def test_depth_order(h4d, n):
     want = seen[np.argsort(rec["depth"][seen], kind="stable")]
     assert ranges.cpu().numpy().tolist() == [[0, len(want)]]
     assert np.array_equal(ids.cpu().numpy()[:len(want)], want)
+
+
+@pytest.mark.parametrize("depths", ["spread", "equal", "skewed"])
+@pytest.mark.parametrize("n", [13000, 13001, 65537, 262145, 524288, 524289, 1048577])
+def test_long_depth_order(h4d, n, depths):
+    """Sorts by bins of sampled keys, from the ranks' longest segment to the radix
+    sort's shortest (beyond 2^18 keys the workgroups' counts are scanned by a launch
+    of their own, beyond 2^19 a workgroup takes 8192 keys, not 4096): a whole-image
+    tile's list is the stable depth order, also when most depths are equal or nearly
+    so."""
+    print(f"[long depth order] n={n} {depths}", flush=True)
+    rng = np.random.default_rng(n)
+    W = H = 16
+    rec = sg.synthetic_records(n, W, H, seed=32, max_radius=40)
+    rec["u"][:], rec["v"][:], rec["radius"][:] = 8.0, 8.0, 30
+    rec["visible"] = (rng.uniform(size=n) > 0.3).astype(np.uint8)
+    if depths == "spread":
+        rec["depth"] = (0.5 + rng.integers(0, n // 7, size=n) / 64.0).astype(np.float32)
+    elif depths == "equal":
+        rec["depth"] = np.full(n, 2.5, np.float32)
+    else:
+        rec["depth"] = np.exp2(60.0 * rng.uniform(size=n) ** 9).astype(np.float32)
+    rast = h4d.Rasterizer(tile=16, chunk=64, pair_capacity=1 << 21, cull=False)
+    _, _, ids, ranges = h4d.rasterize_splats(rast, rec, W, H)
+    seen = np.nonzero(rec["visible"])[0]
+    want = seen[np.argsort(rec["depth"][seen], kind="stable")]
+    assert ranges.cpu().numpy().tolist() == [[0, len(want)]]
+    assert np.array_equal(ids.cpu().numpy()[:len(want)], want)
