@@ -51,6 +51,32 @@ def test_time_colour_forward_and_backward(h4d, degree, period):
         assert np.all(np.abs(g - r) <= 1e-3 * np.abs(r) + 1e-3 * rms)
 
 
+@pytest.mark.parametrize("degree,batched", [(1, False), (2, True)])
+def test_time_colour_over_several_views(h4d, degree, batched):
+    """Gradient rows of the time coefficients: written by the first view that shows a
+    Gaussian, added to by later ones, zero where none does (NaN before the call)."""
+    print(f"[time colour, three views] degree {degree}, batched {batched}", flush=True)
+    scene = sg.with_time_colour(sg.tiny_scene(n3=100, n4=500, seed=95, box=2.5), degree=degree, period=0.9, seed=96)
+    views = [scene.views[0].with_time(0.1), sg.look_at((1.5, 0.0, -2.0), (0.0, 0.0, 0.0), 80, 61, t=0.4),
+             scene.views[0].with_time(0.8)]
+    rast = h4d.Rasterizer(time_period=0.9, batched=batched)
+    g3, g4 = h4d.to_device(scene.g3), h4d.to_device(scene.g4)
+    refs = [oracle.render(scene, v) for v in views]
+    dls = [mask_flagged(d, r["amb"]) for d, r in zip(sg.upstream_grads(views, seed=97), refs)]
+    junk = [torch.full((1 << 20,), float("nan"), device="cuda") for _ in range(4)]
+    del junk
+    h = rast.forward(g3, g4, views)
+    gr3, gr4 = rast.backward(h, g3, g4, [torch.as_tensor(d, device="cuda") for d in dls])
+    torch.cuda.synchronize()
+    r3, r4 = oracle.render_bwd(scene, views, dls)
+    check_grads(scene, gr3, gr4, r3, r4, np.zeros(scene.n3 + scene.n4, bool))
+    g = gr4["sh_t"].cpu().numpy().astype(np.float64)
+    r = r4["sh_t"]
+    assert np.any(np.all(r == 0, axis=0)) and np.linalg.norm(r) > 0
+    assert np.all(g[:, np.all(r == 0, axis=0)] == 0)
+    assert np.all(np.abs(g - r) <= 1e-3 * np.abs(r) + 1e-3 * np.sqrt(np.mean(r * r)))
+
+
 def test_conversion_and_densification_carry_time_coefficients(h4d):
     rng = np.random.default_rng(94)
     g4 = sg.draw_4d(rng, 3000, 2.0, static_fraction=0.4, tau=0.5)
