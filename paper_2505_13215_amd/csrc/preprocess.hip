@@ -173,6 +173,14 @@ struct ProjF {
     double dir[3], en;
 };
 
+// Direction from the camera centre to mu, and the distance.
+__device__ inline void view_dir(const ViewParams& V, const double mu[3], double dir[3], double& en) {
+    const double e[3] = {mu[0] - V.campos[0], mu[1] - V.campos[1], mu[2] - V.campos[2]};
+    en = sqrt(e[0] * e[0] + e[1] * e[1] + e[2] * e[2]);
+    const double ie = 1.0 / en;
+    for (int k = 0; k < 3; ++k) dir[k] = e[k] * ie;
+}
+
 __device__ inline void project(const ViewParams& V, const WorldF& w, ProjF& p) {
     p.culled = true;
     p.covered = false;
@@ -213,10 +221,7 @@ __device__ inline void project(const ViewParams& V, const WorldF& w, ProjF& p) {
     p.y1 = min(V.H - 1, (int)floor(p.v + p.r - 0.5));
     p.culled = false;
     p.covered = p.x0 <= p.x1 && p.y0 <= p.y1;
-    double e[3] = {w.mu[0] - V.campos[0], w.mu[1] - V.campos[1], w.mu[2] - V.campos[2]};
-    p.en = sqrt(e[0] * e[0] + e[1] * e[1] + e[2] * e[2]);
-    const double ie = 1.0 / p.en;
-    for (int k = 0; k < 3; ++k) p.dir[k] = e[k] * ie;
+    view_dir(V, w.mu, p.dir, p.en);
 }
 
 // raw (unclamped) colour of channel ch: 0.5 + sum_k sh[k][ch] Y_k
@@ -242,20 +247,16 @@ __device__ inline void time_weights(const G4Ptr& g, int i, double time, double w
     }
 }
 
-// Channel ch's SH coefficients of 4D Gaussian i at the time of the weights w.  All
-// loops have fixed bounds, so that a degree's sixteen loads are in flight together
-// and the weights stay in registers (one coefficient at a time: 0.030 ms,
-// together 0.010, for 20k Gaussians, 6k of them 4D; their adjoint 0.081 -> 0.047).
-__device__ __forceinline__ void coefs_at(const G4Ptr& g, int i, int ch, const double w[kMaxTimeDeg], double c[16]) {
+// Adds the time terms of channel ch's SH coefficients of 4D Gaussian i at the time of
+// the weights w.  All loops have fixed bounds, so that a degree's sixteen loads are in
+// flight together and the weights stay in registers (20k Gaussians, 6k of them 4D: one
+// coefficient at a time 0.030 ms, together 0.010; the adjoint 0.081 -> 0.047).
+__device__ __forceinline__ void add_time(const G4Ptr& g, int i, int ch, const double w[kMaxTimeDeg], double c[16]) {
     const size_t n = (size_t)g.n;
-    float v[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = g.sh[(size_t)(k * 3 + ch) * n + i];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) c[k] = (double)v[k];
 #pragma unroll
     for (int kk = 0; kk < kMaxTimeDeg; ++kk) {
         if (kk >= g.sh_t_deg) break;
+        float v[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k) v[k] = g.sh_t[((size_t)kk * 48 + k * 3 + ch) * n + i];
 #pragma unroll
@@ -268,7 +269,6 @@ __device__ __forceinline__ void coefs_at(const G4Ptr& g, int i, int ch, const do
 // gradient rows of sh_t (accumulated over the views, written by the first).
 struct TimeColour {
     const G4Ptr* g;
-    int i;
     bool first;
     double w[kMaxTimeDeg], dw[kMaxTimeDeg];
     float* gsht;
@@ -334,7 +334,8 @@ __global__ void __launch_bounds__(256) k_preprocess(G3Ptr g3, G4Ptr g4, const Vi
             time_weights(g4, g, V.time, tw, tdw);
             for (int ch = 0; ch < 3; ++ch) {
                 double acc = kShOffset, c[16];
-                coefs_at(g4, g, ch, tw, c);
+                for (int k = 0; k < 16; ++k) c[k] = (double)g4.sh[(size_t)(k * 3 + ch) * g4.n + g];
+                add_time(g4, g, ch, tw, c);
                 for (int k = 0; k < 16; ++k) acc += c[k] * Y[k];
                 raw[ch] = acc;
             }
@@ -380,53 +381,49 @@ __global__ void __launch_bounds__(256) k_preprocess(G3Ptr g3, G4Ptr g4, const Vi
 // part of Sigma4-bar, which is summed over views so that the covariance and
 // rotation adjoints run once per Gaussian.
 // ---------------------------------------------------------------------------
-// TIME: tc holds the Gaussian's time coefficients; their gradient rows are
-// accumulated and gmt receives mean_t's share through the time weights (a
-// separate instantiation, so that sets without them compile as plain SH).
-template <bool TIME, class E>
-__device__ inline void proj_bwd(const ViewParams& V, const WorldF& w, const ProjF& p, const float* shp, int shn,
-                                int shi, const E& e, double gmu[3], double Sb[3][3],
-                                double& gop, float* gsh, const TimeColour* tc = nullptr, double* gmt = nullptr) {
-    // the blending adjoint sums the centre and conic terms without their
-    // constant factors and the effective opacity: du, dv take -op / log2 e,
-    // dQ00, dQ11 -op / 2, dQ01 -op
-    const double ku = -kLn2 * w.op, kq = -0.5 * w.op;
-    const double gu = ku * e.at(0), gv = ku * e.at(1), gQa = kq * e.at(2), gQb = -w.op * e.at(3), gQc = kq * e.at(4);
-    gop = e.at(5);
-    const double grgb[3] = {e.at(6), e.at(7), e.at(8)};
-    // colour
-    double Y[16], raw[3];
-    sh_eval(p.dir[0], p.dir[1], p.dir[2], Y);
-    if constexpr (TIME) {
-        for (int ch = 0; ch < 3; ++ch) {
-            double acc = kShOffset, c[16];
-            coefs_at(*tc->g, tc->i, ch, tc->w, c);
-            for (int k = 0; k < 16; ++k) acc += c[k] * Y[k];
-            raw[ch] = acc;
+// Element i of row j of n: the row's address is the same for a wave, the element's
+// offset 32 bits wide (one register per lane for all rows).
+template <class T>
+__device__ __forceinline__ T* row_at(T* p, int j, int n, int i) {
+    using Bytes = std::conditional_t<std::is_const_v<T>, const char, char>;
+    return reinterpret_cast<T*>(reinterpret_cast<Bytes*>(p + (size_t)j * n) + (uint32_t)i * (uint32_t)sizeof(T));
+}
+
+// Colour of one view: gsh takes the coefficients' gradients, gmu the mean's share
+// through the view direction.  TIME: tc holds the Gaussian's time coefficients;
+// their gradient rows are accumulated and gmt receives mean_t's share through the
+// time weights (a separate instantiation, so that sets without them compile as
+// plain SH).
+template <bool TIME>
+__device__ inline void colour_bwd(const ViewParams& V, const double mu[3], const float sh[48], const double grgb[3],
+                                  double gmu[3], float gsh[48], const TimeColour* tc = nullptr, int i = 0,
+                                  double* gmt = nullptr) {
+    // (opaque: the rows' addresses are found for each view, not kept through them)
+    if constexpr (TIME) asm("" : "+v"(i));
+    double Y[16], wY[16], dir[3], en;
+    view_dir(V, mu, dir, en);
+    sh_eval(dir[0], dir[1], dir[2], Y);
+    for (int k = 0; k < 16; ++k) wY[k] = 0.0;
+    double gm = 0.0;
+    // channel by channel, so that one's coefficients are held at a time
+    for (int ch = 0; ch < 3; ++ch) {
+        double raw = kShOffset, c[16];
+        for (int k = 0; k < 16; ++k) c[k] = (double)sh[k * 3 + ch];
+        if constexpr (TIME) add_time(*tc->g, i, ch, tc->w, c);
+        for (int k = 0; k < 16; ++k) raw += c[k] * Y[k];
+        const double gc = raw > 0.0 ? grgb[ch] : 0.0;
+        for (int k = 0; k < 16; ++k) {
+            gsh[k * 3 + ch] += (float)(gc * Y[k]);
+            wY[k] += gc * c[k];
         }
-    } else {
-        colour(shp, shn, shi, Y, raw);
-    }
-    double gc[3];
-    for (int ch = 0; ch < 3; ++ch) gc[ch] = raw[ch] > 0.0 ? grgb[ch] : 0.0;
-    double wY[16];
-    if constexpr (TIME) {
-        // dc_j / dsh_t[k][j] = w[k], dc_j / dmean_t = sum_k dw[k] sh_t[k][j]
-        // (a channel's loads before its stores, which they may not pass)
-        const size_t n = (size_t)tc->g->n;
-        double gm = 0.0;
-        for (int k = 0; k < 16; ++k) wY[k] = 0.0;
-        for (int ch = 0; ch < 3; ++ch) {
-            double c[16];
-            coefs_at(*tc->g, tc->i, ch, tc->w, c);
-            for (int k = 0; k < 16; ++k) {
-                gsh[k * 3 + ch] += (float)(gc[ch] * Y[k]);
-                wY[k] += gc[ch] * c[k];
-            }
+        if constexpr (TIME) {
+            // dc_j / dsh_t[k][j] = w[k], dc_j / dmean_t = sum_k dw[k] sh_t[k][j]
+            // (a channel's loads before its stores, which they may not pass)
+            const size_t n = (size_t)tc->g->n;
 #pragma unroll
             for (int kk = 0; kk < kMaxTimeDeg; ++kk) {
                 if (kk >= tc->g->sh_t_deg) break;
-                const size_t o = ((size_t)kk * 48 + ch) * n + tc->i;
+                const size_t o = ((size_t)kk * 48 + ch) * n + i;
                 float old[16], t[16];
 #pragma unroll
                 for (int k = 0; k < 16; ++k) t[k] = tc->g->sh_t[o + (size_t)(3 * k) * n];
@@ -434,28 +431,31 @@ __device__ inline void proj_bwd(const ViewParams& V, const WorldF& w, const Proj
                 for (int k = 0; k < 16; ++k) old[k] = tc->first ? 0.f : tc->gsht[o + (size_t)(3 * k) * n];
 #pragma unroll
                 for (int k = 0; k < 16; ++k) {
-                    const double gj = gc[ch] * Y[k];
+                    const double gj = gc * Y[k];
                     tc->gsht[o + (size_t)(3 * k) * n] = old[k] + (float)(tc->w[kk] * gj);
                     gm += gj * tc->dw[kk] * (double)t[k];
                 }
             }
         }
-        *gmt += gm;
-    } else {
-        for (int k = 0; k < 16; ++k) {
-            double acc = 0.0;
-            for (int ch = 0; ch < 3; ++ch) {
-                gsh[k * 3 + ch] += (float)(gc[ch] * Y[k]);
-                acc += gc[ch] * (double)shp[(size_t)(k * 3 + ch) * shn + shi];
-            }
-            wY[k] = acc;
-        }
     }
+    if constexpr (TIME) *gmt += gm;
     double gd[3];
-    sh_grad_dot(p.dir[0], p.dir[1], p.dir[2], wY, gd);
-    const double dd = p.dir[0] * gd[0] + p.dir[1] * gd[1] + p.dir[2] * gd[2];
-    const double ie = 1.0 / p.en;
-    for (int k = 0; k < 3; ++k) gmu[k] = (gd[k] - p.dir[k] * dd) * ie;
+    sh_grad_dot(dir[0], dir[1], dir[2], wY, gd);
+    const double dd = dir[0] * gd[0] + dir[1] * gd[1] + dir[2] * gd[2];
+    const double ie = 1.0 / en;
+    for (int k = 0; k < 3; ++k) gmu[k] = (gd[k] - dir[k] * dd) * ie;
+}
+
+// The projection's other values: e(k) the record's du dv dQ00 dQ01 dQ11 dop.
+template <class E>
+__device__ inline void proj_bwd(const ViewParams& V, const WorldF& w, const ProjF& p, const E& e, double gmu[3],
+                                double Sb[3][3], double& gop) {
+    // the blending adjoint sums the centre and conic terms without their
+    // constant factors and the effective opacity: du, dv take -op / log2 e,
+    // dQ00, dQ11 -op / 2, dQ01 -op
+    const double ku = -kLn2 * w.op, kq = -0.5 * w.op;
+    const double gu = ku * e(0), gv = ku * e(1), gQa = kq * e(2), gQb = -w.op * e(3), gQc = kq * e(4);
+    gop = e(5);
     // conic -> 2D covariance: S2bar = -Q Gbar Q, Gbar = [[gQa, gQb/2], [gQb/2, gQc]]
     const double iD = 1.0 / p.det;
     const double Q00 = p.d * iD, Q01 = -p.b * iD, Q11 = p.a * iD;
@@ -494,7 +494,7 @@ __device__ inline void proj_bwd(const ViewParams& V, const WorldF& w, const Proj
     pb0 = xb * iz;
     pb1 = yb * iz;
     pb2 += -(xb * p.pc[0] + yb * p.pc[1]) * iz2;
-    for (int k = 0; k < 3; ++k) gmu[k] += V.R[k] * pb0 + V.R[3 + k] * pb1 + V.R[6 + k] * pb2;
+    for (int k = 0; k < 3; ++k) gmu[k] = V.R[k] * pb0 + V.R[3 + k] * pb1 + V.R[6 + k] * pb2;
 }
 
 __device__ inline void unit_bwd(const double qh[4], double nrm, const double gqh[4], float* out, size_t stride) {
@@ -503,48 +503,122 @@ __device__ inline void unit_bwd(const double qh[4], double nrm, const double gqh
     for (int k = 0; k < 4; ++k) out[k * stride] = (float)((gqh[k] - qh[k] * dq) * in);
 }
 
-template <bool TIME, bool WIDE>
-__device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restrict__ views, int n_views, int N,
-                              const Rec* __restrict__ recs, const float* __restrict__ g2, const G4Grad& gr,
-                              const SetStats& st) {
+// A 4D Gaussian's view-independent values, as the adjoint needs them.
+struct Base4 {
+    double s[4], ql[4], qr[4], nl, nr, R[4][4], S4[4][4], b[3], c, ic, mu0[3], mt;
+};
+__device__ inline void base4(const G4Ptr& g4, int i, Base4& z) {
     const size_t n = (size_t)g4.n;
-    double s[4], ql[4], qr[4];
-    for (int k = 0; k < 4; ++k) s[k] = exp((double)g4.log_scale[k * n + i]);
-    const double nl = load_unit4(g4.quat_l, g4.n, i, ql);
-    const double nr = load_unit4(g4.quat_r, g4.n, i, qr);
-    double R[4][4];
+    for (int k = 0; k < 4; ++k) z.s[k] = exp((double)g4.log_scale[k * n + i]);
+    z.nl = load_unit4(g4.quat_l, g4.n, i, z.ql);
+    z.nr = load_unit4(g4.quat_r, g4.n, i, z.qr);
     {
         double L[4][4], Rr[4][4];
-        rot_left(ql, L);
-        rot_right(qr, Rr);
+        rot_left(z.ql, L);
+        rot_right(z.qr, Rr);
         for (int r = 0; r < 4; ++r)
             for (int c = 0; c < 4; ++c)
-                R[r][c] = L[r][0] * Rr[0][c] + L[r][1] * Rr[1][c] + L[r][2] * Rr[2][c] + L[r][3] * Rr[3][c];
+                z.R[r][c] = L[r][0] * Rr[0][c] + L[r][1] * Rr[1][c] + L[r][2] * Rr[2][c] + L[r][3] * Rr[3][c];
     }
-    double S4[4][4];
     for (int r = 0; r < 4; ++r)
         for (int c = r; c < 4; ++c) {
             double acc = 0;
-            for (int k = 0; k < 4; ++k) acc += R[r][k] * s[k] * s[k] * R[c][k];
-            S4[r][c] = acc;
-            S4[c][r] = acc;
+            for (int k = 0; k < 4; ++k) acc += z.R[r][k] * z.s[k] * z.s[k] * z.R[c][k];
+            z.S4[r][c] = acc;
+            z.S4[c][r] = acc;
         }
-    const double c = S4[3][3], ic = 1.0 / c;
-    const double b[3] = {S4[0][3], S4[1][3], S4[2][3]};
-    const double mu0[3] = {(double)g4.mean[i], (double)g4.mean[n + i], (double)g4.mean[2 * n + i]};
-    const double mt = (double)g4.mean_t[i];
+    z.c = z.S4[3][3];
+    z.ic = 1.0 / z.c;
+    for (int k = 0; k < 3; ++k) {
+        z.b[k] = z.S4[k][3];
+        z.mu0[k] = (double)g4.mean[k * n + i];
+    }
+    z.mt = (double)g4.mean_t[i];
+}
+
+// What the colour wave of a workgroup leaves for the other, per Gaussian: the sums
+// over the views of the mean's gradient through the view direction, of the same
+// times delta (4D), and mean_t's share through the time weights.
+struct ColourSums {
+    double gmu[3][64], gmd[3][64], gmt[64];
+};
+
+template <bool TIME, bool WIDE>
+__device__ inline void colour_4d(const G4Ptr& g4, int i, bool valid, const ViewParams* __restrict__ views, int n_views,
+                                 int N, const Rec* __restrict__ recs, const float* __restrict__ g2, const G4Grad& gr,
+                                 ColourSums& out) {
+    const size_t n = (size_t)g4.n;
+    Base4 z;
+    base4(g4, i, z);
+    double gmu[3] = {0, 0, 0}, gmd[3] = {0, 0, 0}, gmt = 0;
+    float sh[48], gsh[48];
+    for (int k = 0; k < 48; ++k) sh[k] = *row_at(g4.sh, k, g4.n, i);
+    for (int k = 0; k < 48; ++k) gsh[k] = 0.f;
+    [[maybe_unused]] bool first = true;
+    for (int v = 0; v < n_views; ++v) {
+        if (!valid || recs[(size_t)v * N + i].d.w == 0u) continue;  // covers no pixel in this view
+        const ViewParams& V = views[v];
+        const double delta = V.time - z.mt;
+        double mu[3], gmc[3];
+        for (int k = 0; k < 3; ++k) mu[k] = z.mu0[k] + z.b[k] * z.ic * delta;
+        const ScreenGrad<WIDE> e{g2 + ((size_t)v * N + i) * kG2Stride};
+        const double grgb[3] = {e.at(6), e.at(7), e.at(8)};
+        if constexpr (TIME) {
+            TimeColour tc;
+            tc.g = &g4;
+            tc.gsht = gr.sh_t;
+            tc.first = first;
+            first = false;
+            time_weights(g4, i, V.time, tc.w, tc.dw);
+            colour_bwd<true>(V, mu, sh, grgb, gmc, gsh, &tc, i, &gmt);
+        } else {
+            colour_bwd<false>(V, mu, sh, grgb, gmc, gsh);
+        }
+        for (int k = 0; k < 3; ++k) {
+            gmu[k] += gmc[k];
+            gmd[k] += gmc[k] * delta;
+        }
+    }
+    const int lane = __lane_id();
+    for (int k = 0; k < 3; ++k) {
+        out.gmu[k][lane] = gmu[k];
+        out.gmd[k][lane] = gmd[k];
+    }
+    out.gmt[lane] = gmt;
+    if (!valid) return;
+    for (int k = 0; k < 48; ++k) *row_at(gr.sh, k, (int)n, i) = gsh[k];
+    if constexpr (TIME)
+        if (first)  // covers no pixel in any view
+            for (int k = 0; k < 48 * g4.sh_t_deg; ++k) gr.sh_t[(size_t)k * n + i] = 0.f;
+}
+
+template <bool WIDE>
+__device__ inline void bwd_4d(const G4Ptr& g4, int i, bool valid, const ViewParams* __restrict__ views, int n_views,
+                              int N, const Rec* __restrict__ recs, const float* __restrict__ g2, const G4Grad& gr,
+                              const SetStats& st, const ColourSums& col) {
+    const size_t n = (size_t)g4.n;
+    double S4[4][4], b[3], mu0[3], ic, mt;
+    {
+        Base4 z;
+        base4(g4, i, z);
+        for (int r = 0; r < 4; ++r)
+            for (int k = 0; k < 4; ++k) S4[r][k] = z.S4[r][k];
+        for (int k = 0; k < 3; ++k) {
+            b[k] = z.b[k];
+            mu0[k] = z.mu0[k];
+        }
+        ic = z.ic;
+        mt = z.mt;
+    }
     const double sig = sigmoid((double)g4.opacity[i]);
     double gmu[3] = {0, 0, 0}, gmt = 0, gsig = 0;
     double Ss[4][4];  // accumulated Sigma4-bar + Sigma4-bar^T
     for (int r = 0; r < 4; ++r)
         for (int k = 0; k < 4; ++k) Ss[r][k] = 0.0;
-    float gsh[48];
-    for (int k = 0; k < 48; ++k) gsh[k] = 0.f;
-    [[maybe_unused]] bool first = true;
     double stat_g = 0.0;
     int stat_n = 0;
     for (int v = 0; v < n_views; ++v) {
-        if (recs[(size_t)v * N + i].d.w == 0u) continue;  // covers no pixel in this view
+        if (!valid || recs[(size_t)v * N + i].d.w == 0u) continue;  // covers no pixel in this view
         const ViewParams& V = views[v];
         const double delta = V.time - mt;
         const double pt = exp(-(delta * delta) * 0.5 * ic);
@@ -561,19 +635,7 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restri
         ProjF p;
         project(V, w, p);
         double gmc[3], Sb[3][3], gop;
-        if constexpr (TIME) {
-            TimeColour tc;
-            tc.g = &g4;
-            tc.i = i;
-            tc.gsht = gr.sh_t;
-            tc.first = first;
-            first = false;
-            time_weights(g4, i, V.time, tc.w, tc.dw);
-            proj_bwd<true>(V, w, p, g4.sh, g4.n, i, e, gmc, Sb, gop, gsh, &tc,
-                           &gmt);
-        } else {
-            proj_bwd<false>(V, w, p, g4.sh, g4.n, i, e, gmc, Sb, gop, gsh);
-        }
+        proj_bwd(V, w, p, [&](int k) { return e.at(k); }, gmc, Sb, gop);
         // effective opacity sigma * p(t); p(t) = exp(-delta^2 / (2 c))
         gsig += gop * pt;
         const double gpt = gop * sig;
@@ -596,6 +658,30 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restri
         for (int r = 0; r < 3; ++r)
             for (int k = 0; k < 3; ++k) Ss[r][k] += 2.0 * Sb[r][k];
     }
+    // the colour's share of the mean (the slicing adjoint is linear in it)
+    __syncthreads();
+    if (!valid) return;
+    {
+        const int lane = __lane_id();
+        double mub = 0.0, mud = 0.0;
+        for (int r = 0; r < 3; ++r) {
+            const double gm = col.gmu[r][lane], gd = col.gmd[r][lane];
+            gmu[r] += gm;
+            mub += gm * b[r];
+            mud += gd * b[r];
+            Ss[r][3] += gd * ic;
+            Ss[3][r] += gd * ic;
+        }
+        gmt += col.gmt[lane] - mub * ic;
+        Ss[3][3] -= 2.0 * mud * ic * ic;
+    }
+    // the rotation and scales again, rather than in registers all through the views
+    // (the index is made opaque, or the compiler would keep them)
+    asm("" : "+v"(i));
+    Base4 z;
+    base4(g4, i, z);
+    const auto& R = z.R;
+    const auto& s = z.s;
     // Sigma4 = Lm Lm^T, Lm = R diag(s): Lbar = Ss Lm, Rbar = Lbar diag(s), sbar_j = (R^T Lbar)_jj
     double Rb[4][4];
     for (int r = 0; r < 4; ++r)
@@ -613,7 +699,7 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restri
     double gl[4], grr[4];
     {
         double Rr[4][4];
-        rot_right(qr, Rr);
+        rot_right(z.qr, Rr);
         double Lb[4][4];
         for (int r = 0; r < 4; ++r)
             for (int c2 = 0; c2 < 4; ++c2)
@@ -625,7 +711,7 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restri
     }
     {
         double L[4][4];
-        rot_left(ql, L);
+        rot_left(z.ql, L);
         double Rrb[4][4];
         for (int r = 0; r < 4; ++r)
             for (int c2 = 0; c2 < 4; ++c2)
@@ -635,30 +721,76 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, const ViewParams* __restri
         grr[2] = -Rrb[0][2] - Rrb[1][3] + Rrb[2][0] + Rrb[3][1];
         grr[3] = -Rrb[0][3] + Rrb[1][2] - Rrb[2][1] + Rrb[3][0];
     }
-    unit_bwd(ql, nl, gl, gr.quat_l + i, n);
-    unit_bwd(qr, nr, grr, gr.quat_r + i, n);
+    unit_bwd(z.ql, z.nl, gl, gr.quat_l + i, n);
+    unit_bwd(z.qr, z.nr, grr, gr.quat_r + i, n);
     for (int k = 0; k < 3; ++k) gr.mean[k * n + i] = (float)gmu[k];
     gr.mean_t[i] = (float)gmt;
     gr.opacity[i] = (float)(gsig * sig * (1.0 - sig));
     write_stats(st, i, stat_g, stat_n);
-    for (int k = 0; k < 48; ++k) gr.sh[k * n + i] = gsh[k];
-    if constexpr (TIME)
-        if (first)  // covers no pixel in any view
-            for (int k = 0; k < 48 * g4.sh_t_deg; ++k) gr.sh_t[(size_t)k * n + i] = 0.f;
+}
+
+// Components [K0, K1) of a 3D record of view v: the record as it is for a view alone
+// or a group's sum already in it (direct), otherwise the group's members' summed here.
+template <bool WIDE, int K0, int K1>
+__device__ inline void group_grad(const ViewParams* __restrict__ views, int v, int N, int gidx,
+                                  const float* __restrict__ g2, bool direct, double out[K1 - K0]) {
+    using Sum = std::conditional_t<WIDE, double, float>;
+    constexpr int KS = WIDE || K1 < 9 ? K1 : kG2Slots;  // (the last component lies in four slots)
+    if (direct) {
+        const ScreenGrad<WIDE> e{g2 + ((size_t)v * N + gidx) * kG2Stride};
+        for (int k = K0; k < K1; ++k) out[k - K0] = e.at(k);
+        return;
+    }
+    Sum sum[KS - K0];
+    for (int k = K0; k < KS; ++k) sum[k - K0] = (Sum)0;
+    for (int u = v; u >= 0; u = views[u].static_next) {
+        const ScreenGrad<WIDE> e{g2 + ((size_t)u * N + gidx) * kG2Stride};
+        for (int k = K0; k < KS; ++k) {
+            if constexpr (WIDE) sum[k - K0] += e.at(k);
+            else sum[k - K0] += e.rec[k];
+        }
+    }
+    for (int k = K0; k < K1; ++k) out[k - K0] = (double)sum[k - K0];
+    if constexpr (KS > K1)
+        out[K1 - 1 - K0] = (double)sum[8 - K0] + sum[9 - K0] + sum[10 - K0] + sum[11 - K0];
 }
 
 template <bool WIDE>
-__device__ inline void bwd_3d(const G3Ptr& g3, int i, int gidx, const ViewParams* __restrict__ views, int n_views,
-                              int N, const Rec* __restrict__ recs, const float* __restrict__ g2, const G3Grad& gr,
-                              const SetStats& st, int static_rows) {
+__device__ inline void colour_3d(const G3Ptr& g3, int i, bool valid, int gidx, const ViewParams* __restrict__ views,
+                                 int n_views, int N, const Rec* __restrict__ recs, const float* __restrict__ g2,
+                                 const G3Grad& gr, int static_rows, ColourSums& out) {
+    const size_t n = (size_t)g3.n;
+    double mu[3], gmu[3] = {0, 0, 0};
+    for (int k = 0; k < 3; ++k) mu[k] = (double)g3.mean[(size_t)k * n + i];
+    float sh[48], gsh[48];
+    for (int k = 0; k < 48; ++k) sh[k] = *row_at(g3.sh, k, g3.n, i);
+    for (int k = 0; k < 48; ++k) gsh[k] = 0.f;
+    for (int v = 0; v < n_views; ++v) {
+        const ViewParams& V = views[v];
+        if (V.static_view != v) continue;
+        if (!valid || recs[(size_t)v * N + gidx].d.w == 0u) continue;
+        double grgb[3], gmc[3];
+        group_grad<WIDE, 6, 9>(views, v, N, gidx, g2, static_rows || V.static_next < 0, grgb);
+        colour_bwd<false>(V, mu, sh, grgb, gmc, gsh);
+        for (int k = 0; k < 3; ++k) gmu[k] += gmc[k];
+    }
+    for (int k = 0; k < 3; ++k) out.gmu[k][__lane_id()] = gmu[k];
+    if (!valid) return;
+    for (int k = 0; k < 48; ++k) *row_at(gr.sh, k, (int)n, i) = gsh[k];
+}
+
+template <bool WIDE>
+__device__ inline void bwd_3d(const G3Ptr& g3, int i, bool valid, int gidx, const ViewParams* __restrict__ views,
+                              int n_views, int N, const Rec* __restrict__ recs, const float* __restrict__ g2,
+                              const G3Grad& gr, const SetStats& st, int static_rows, const ColourSums& col) {
     const size_t n = (size_t)g3.n;
     WorldF w;
-    Cov3 z;
-    world3(g3, i, w, z);
+    {
+        Cov3 z0;
+        world3(g3, i, w, z0);
+    }
     double gmu[3] = {0, 0, 0}, gsig = 0;
     double Ss[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-    float gsh[48];
-    for (int k = 0; k < 48; ++k) gsh[k] = 0.f;
     double stat_g = 0.0;
     int stat_n = 0;
     // the views of a static group share one camera and one record: their
@@ -667,48 +799,32 @@ __device__ inline void bwd_3d(const G3Ptr& g3, int i, int gidx, const ViewParams
     for (int v = 0; v < n_views; ++v) {
         const ViewParams& V = views[v];
         if (V.static_view != v) continue;                  // summed into its group's leader below
-        if (recs[(size_t)v * N + gidx].d.w == 0u) continue;  // covers no pixel in this camera
-        // (a view alone, or the group's sum already in its record: that record
-        // as it is; otherwise the members' records summed here)
-        using Sum = std::conditional_t<WIDE, double, float>;
-        Sum e[kG2Slots];
-        for (int k = 0; k < kG2Slots; ++k) e[k] = (Sum)0;
+        if (!valid || recs[(size_t)v * N + gidx].d.w == 0u) continue;  // covers no pixel in this camera
         const bool direct = static_rows || V.static_next < 0;
-        const ScreenGrad<WIDE> own{g2 + ((size_t)v * N + gidx) * kG2Stride};
-        if (direct && (st.grad || st.vis || st.step_vis)) {
-            stat_g += ndc_grad_norm(own.at(0), own.at(1), kLn2 * w.op, V.W, V.H);
-            ++stat_n;
-        }
-        for (int u = direct ? -1 : v; u >= 0; u = views[u].static_next) {
-            const ScreenGrad<WIDE> g{g2 + ((size_t)u * N + gidx) * kG2Stride};
-            if (st.grad || st.vis || st.step_vis) {
+        if (st.grad || st.vis || st.step_vis)
+            for (int u = v; u >= 0; u = direct ? -1 : views[u].static_next) {
+                const ScreenGrad<WIDE> g{g2 + ((size_t)u * N + gidx) * kG2Stride};
                 stat_g += ndc_grad_norm(g.at(0), g.at(1), kLn2 * w.op, views[u].W, views[u].H);
                 ++stat_n;
             }
-            if constexpr (WIDE)
-                for (int k = 0; k < 9; ++k) e[k] += g.at(k);
-            else
-                for (int k = 0; k < kG2Slots; ++k) e[k] += g.rec[k];
-        }
+        double e[6];
+        group_grad<WIDE, 0, 6>(views, v, N, gidx, g2, direct, e);
         ProjF p;
         project(V, w, p);
         double gmc[3], Sb[3][3], gop;
-        if constexpr (WIDE) {
-            struct {
-                const double* e;
-                const ScreenGrad<true>* own;
-                __device__ double at(int k) const { return own ? own->at(k) : e[k]; }
-            } src{e, direct ? &own : nullptr};
-            proj_bwd<false>(V, w, p, g3.sh, g3.n, i, src, gmc, Sb, gop, gsh);
-        } else {
-            proj_bwd<false>(V, w, p, g3.sh, g3.n, i, ScreenGrad<false>{direct ? own.rec : e}, gmc, Sb, gop, gsh);
-        }
+        proj_bwd(V, w, p, [&](int k) { return e[k]; }, gmc, Sb, gop);
         gsig += gop;
         for (int r = 0; r < 3; ++r) {
             gmu[r] += gmc[r];
             for (int k = 0; k < 3; ++k) Ss[r][k] += 2.0 * Sb[r][k];
         }
     }
+    __syncthreads();
+    if (!valid) return;
+    for (int r = 0; r < 3; ++r) gmu[r] += col.gmu[r][__lane_id()];
+    asm("" : "+v"(i));  // (as bwd_4d)
+    Cov3 z;
+    world3(g3, i, w, z);
     double Rb[3][3];
     for (int r = 0; r < 3; ++r)
         for (int j = 0; j < 3; ++j) {
@@ -734,28 +850,40 @@ __device__ inline void bwd_3d(const G3Ptr& g3, int i, int gidx, const ViewParams
     for (int k = 0; k < 3; ++k) gr.mean[k * n + i] = (float)gmu[k];
     gr.opacity[i] = (float)(gsig * z.sig * (1.0 - z.sig));
     write_stats(st, i, stat_g, stat_n);
-    for (int k = 0; k < 48; ++k) gr.sh[k * n + i] = gsh[k];
 }
 
 // One launch for both sets: workgroups [0, nb4) take the 4D Gaussians (the
-// longer threads, started first), the rest the 3D ones.  Both paths hold one
-// wave per SIMD (FP64 state of 400+ registers), so sharing the launch costs no
-// occupancy and lets the two sets fill the machine together.
+// longer threads, started first), the rest the 3D ones.  A workgroup takes 64
+// Gaussians with two waves: one differentiates their colour, the other the rest,
+// and adds the colour's share of the mean's gradient.  One thread for both held 400+
+// registers of FP64 state, one wave per SIMD, which left it waiting for its
+// loads and its own results: 2M Gaussians and four views 0.714 -> 0.479 ms (1.2 GB),
+// 500k and eight 0.201 -> 0.170, 250k and one 0.044 -> 0.040, 20k with time terms
+// 0.047 -> 0.025.  The colour's coefficients stay in registers through the views
+// (read again for each: 0.714 -> 1.81 ms).
 // TIME: the 4D set carries time coefficients of its colour.
 template <bool TIME, bool WIDE>
-__global__ void __launch_bounds__(128) k_preprocess_bwd(G3Ptr g3, G4Ptr g4, int nb4, const ViewParams* __restrict__ views,
-                                                        int n_views, const Rec* __restrict__ recs,
-                                                        const float* __restrict__ g2, G3Grad gr3, G4Grad gr4,
-                                                        SetStats st3, SetStats st4, int static_rows,
-                                                        Status* status) {
+__global__ void __launch_bounds__(128, 2) k_preprocess_bwd(G3Ptr g3, G4Ptr g4, int nb4,
+                                                           const ViewParams* __restrict__ views, int n_views,
+                                                           const Rec* __restrict__ recs, const float* __restrict__ g2,
+                                                           G3Grad gr3, G4Grad gr4, SetStats st3, SetStats st4,
+                                                           int static_rows, Status* status) {
+    __shared__ ColourSums s_col;
     const int N = g3.n + g4.n;
+    const bool colour = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) != 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) status->g2_dirty = 1ull;  // (read by the next backward's prologue)
-    if ((int)blockIdx.x < nb4) {
-        const int g = blockIdx.x * blockDim.x + threadIdx.x;
-        if (g < g4.n) bwd_4d<TIME, WIDE>(g4, g, views, n_views, N, recs, g2, gr4, st4);
+    const bool four = (int)blockIdx.x < nb4;
+    const int n = four ? g4.n : g3.n;
+    if (n == 0) return;  // (uniform: an empty call's workgroup)
+    const int at = ((int)blockIdx.x - (four ? 0 : nb4)) * 64 + __lane_id(), i = min(at, n - 1);
+    const bool valid = at < n;
+    if (colour) {
+        if (four) colour_4d<TIME, WIDE>(g4, i, valid, views, n_views, N, recs, g2, gr4, s_col);
+        else colour_3d<WIDE>(g3, i, valid, g4.n + i, views, n_views, N, recs, g2, gr3, static_rows, s_col);
+        __syncthreads();
     } else {
-        const int i = (blockIdx.x - nb4) * blockDim.x + threadIdx.x;
-        if (i < g3.n) bwd_3d<WIDE>(g3, i, g4.n + i, views, n_views, N, recs, g2, gr3, st3, static_rows);
+        if (four) bwd_4d<WIDE>(g4, i, valid, views, n_views, N, recs, g2, gr4, st4, s_col);
+        else bwd_3d<WIDE>(g3, i, valid, g4.n + i, views, n_views, N, recs, g2, gr3, st3, static_rows, s_col);
     }
 }
 
@@ -833,7 +961,7 @@ void launch_preprocess_bwd(const G3Ptr& g3, const G4Ptr& g4, const ViewParams* v
                            const float* g2, int wide, const G3Grad& gr3, const G4Grad& gr4, const SetStats& st3,
                            const SetStats& st4, int static_rows, Status* status, hipStream_t st) {
     const int N = g3.n + g4.n;
-    const int nb4 = ceil_div(g4.n, 128), nb3 = ceil_div(g3.n, 128);
+    const int nb4 = ceil_div(g4.n, 64), nb3 = ceil_div(g3.n, 64);
     const int nb = std::max(1, nb4 + nb3);  // (one workgroup at least: it marks the records used)
     const auto run = [&](auto kernel) {
         kernel<<<nb, 128, 0, st>>>(g3, g4, nb4, views, n_views, recs, g2, gr3, gr4, st3, st4, static_rows, status);
