@@ -206,6 +206,7 @@ bool launch_bwd_prologue(float* g2, size_t n_g2, const unsigned long long* dirty
                          const uint32_t* thist, const PassTiles& passes, const OrderSort& sort, uint32_t* order,
                          hipStream_t st);
 void launch_fill_u64(unsigned long long* p, size_t n, unsigned long long val, hipStream_t st);
+void launch_copy_words(const uint32_t* src, uint32_t* dst, int n, hipStream_t st);
 void launch_fill_f32(float* p, size_t n, float val, hipStream_t st);
 
 // composite.hip

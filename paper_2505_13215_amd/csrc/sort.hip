@@ -2039,6 +2039,14 @@ void launch_fill_u64(unsigned long long* p, size_t n, unsigned long long val, hi
     const int nb = (int)std::min<size_t>(4096, (n + 255) / 256);
     k_fill_u64<<<nb, 256, 0, st>>>(p, n, val);
 }
+// (n <= 64; dst may be pinned host memory)
+__global__ void k_copy_words(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, int n) {
+    if ((int)threadIdx.x < n) dst[threadIdx.x] = src[threadIdx.x];
+}
+void launch_copy_words(const uint32_t* src, uint32_t* dst, int n, hipStream_t st) {
+    if (n > 0 && n <= 64) k_copy_words<<<1, 64, 0, st>>>(src, dst, n);
+}
+
 void launch_fill_f32(float* p, size_t n, float val, hipStream_t st) {
     if (n == 0) return;
     const int nb = (int)std::min<size_t>(8192, (n + 255) / 256);

@@ -17,7 +17,8 @@ G4_KEYS = ("mean", "mean_t", "log_scale", "quat_l", "quat_r", "opacity", "sh")
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # (the stream's handle without a Stream object: three or four calls per step)
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _ptr(t):
