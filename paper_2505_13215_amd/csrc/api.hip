@@ -1503,11 +1503,22 @@ h4d_status h4dgs_l1_loss_grad(h4d_ctx* ctx, int32_t n_views, const float* const*
     hipStream_t st = static_cast<hipStream_t>(stream);
     StageScope sc(ctx, st, H4D_STAGE_LOSS);
     if (loss) launch_fill_f32(loss, 1, 0.f, st);  // a fill kernel: safe under graph capture
+    L1Views t;
+    std::memset(&t, 0, sizeof(t));
     for (int v = 0; v < n_views; ++v) {
-        const size_t n = (size_t)3 * views[v].width * views[v].height;
-        const float scale = (float)(1.0 / ((double)n * n_views));
-        launch_l1_loss_grad(images[v], targets[v], dl_dimages[v], n, scale, loss, st);
+        t.n[v] = (size_t)3 * views[v].width * views[v].height;
+        t.scale[v] = (float)(1.0 / ((double)t.n[v] * n_views));
+        t.img[v] = images[v];
+        t.target[v] = targets[v];
+        t.dl[v] = dl_dimages[v];
     }
+    // outputs that lie in another view's buffers are written view after view
+    const auto meet = [&](int v, const float* p, int u) { return t.dl[v] < p + t.n[u] && p < t.dl[v] + t.n[v]; };
+    bool apart = true;
+    for (int v = 0; v < n_views; ++v)
+        for (int u = 0; u < n_views; ++u)
+            apart = apart && (u == v || !(meet(v, t.dl[u], u) || meet(v, t.img[u], u) || meet(v, t.target[u], u)));
+    for (int v = 0; v < n_views; v += apart ? n_views : 1) launch_l1_loss_grad(t, v, apart ? n_views : 1, loss, st);
     return hip_check(ctx, "l1_loss_grad");
 }
 

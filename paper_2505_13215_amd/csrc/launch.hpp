@@ -252,8 +252,15 @@ void launch_walk_lists(int tile, const Rec* recs, int N, const CoarseLists& list
                        unsigned long long* offsets, unsigned long long* partials, uint32_t* out, uint64_t out_cap,
                        int64_t* ranges, hipStream_t st);
 // L1 loss gradient (loss.hip)
-void launch_l1_loss_grad(const float* img, const float* target, float* dl, size_t n, float scale, float* loss,
-                         hipStream_t st);
+struct L1Views {
+    const float* img[kMaxViews];
+    const float* target[kMaxViews];
+    float* dl[kMaxViews];
+    size_t n[kMaxViews];  // floats
+    float scale[kMaxViews];
+};
+// the views [v0, v0 + n_views)
+void launch_l1_loss_grad(const L1Views& views, int v0, int n_views, float* loss, hipStream_t st);
 
 // densify.hip
 // Densification limits as the kernels take them (see h4d_densify_params).

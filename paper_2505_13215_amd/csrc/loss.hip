@@ -1,5 +1,7 @@
 // L1 photometric loss and its gradient (elementwise, HBM-bound: 12 bytes per
 // pixel channel).  Each thread keeps four 16-byte loads of each input in flight.
+// One launch takes all views (eight of 1352 x 1014, each as long as a launch's
+// start and end: 0.098 -> 0.069 ms).
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -17,8 +19,13 @@ __device__ __forceinline__ float block_sum_256(float v) {
 
 // n4 float4 groups (images are 16-byte aligned); the last n - 4 n4 scalars are
 // handled by block 0.
-__global__ void __launch_bounds__(256) k_l1_loss_grad(const float* __restrict__ img, const float* __restrict__ target,
-                                                      float* __restrict__ dl, size_t n, float scale, float* loss) {
+__global__ void __launch_bounds__(256) k_l1_loss_grad(L1Views views, int v0, float* loss) {
+    const int view = v0 + (int)blockIdx.y;
+    const float* __restrict__ img = views.img[view];
+    const float* __restrict__ target = views.target[view];
+    float* __restrict__ dl = views.dl[view];
+    const size_t n = views.n[view];
+    const float scale = views.scale[view];
     const size_t n4 = n / 4;
     const float4* __restrict__ a4 = reinterpret_cast<const float4*>(img);
     const float4* __restrict__ b4 = reinterpret_cast<const float4*>(target);
@@ -60,14 +67,15 @@ __global__ void __launch_bounds__(256) k_l1_loss_grad(const float* __restrict__ 
     }
 }
 
-void launch_l1_loss_grad(const float* img, const float* target, float* dl, size_t n, float scale, float* loss,
-                         hipStream_t st) {
+void launch_l1_loss_grad(const L1Views& views, int v0, int n_views, float* loss, hipStream_t st) {
+    size_t n = 0;
+    for (int v = v0; v < v0 + n_views; ++v) n = std::max(n, views.n[v]);
     if (n == 0) return;
     const size_t n4 = n / 4;
-    // one block per compute unit at most: the blocks end with an atomic on one
-    // word, which serialises
+    // one block per compute unit and view at most: the blocks end with an atomic on
+    // one word, which serialises
     const int nb = (int)std::max<size_t>(1, std::min<size_t>(256, (n4 + 4 * 256 - 1) / (4 * 256)));
-    k_l1_loss_grad<<<nb, 256, 0, st>>>(img, target, dl, n, scale, loss);
+    k_l1_loss_grad<<<dim3(nb, n_views), 256, 0, st>>>(views, v0, loss);
 }
 
 }  // namespace h4d
