@@ -380,7 +380,7 @@ __global__ void __launch_bounds__(64 * kRankWaves) k_rank_sort(const uint32_t* _
 // to their bins, and one workgroup per bin orders it.  The keys are read twice and
 // moved once (an 8-bit radix sort reads them eight times and moves them four), in
 // four or five launches instead of twelve: 18,000 keys 0.054 -> 0.023 ms, 250,000
-// 0.065 -> 0.041, 500,000 0.079 -> 0.053, eight segments of 500,000 0.212 -> 0.177.
+// 0.065 -> 0.040, 500,000 0.079 -> 0.052, eight segments of 500,000 0.212 -> 0.150.
 // Short segments are bound by the launches and one trip through memory in each,
 // long ones by the searches in LDS (k_depth_bins, 19 ns per 1000 keys).
 constexpr int kSplitThreads = 1024;
@@ -389,23 +389,27 @@ constexpr int kSplitMaxBins = 2048;
 // Up to here a scatter workgroup sums the counting workgroups' rows itself, a load
 // per row; beyond, a launch scans them first.
 constexpr int kSplitDirect = 64;
+// From this many samples on a launch gathers them once: one segment of 1M (8192
+// samples) 0.087 -> 0.075 ms, eight of 500,000 0.176 -> 0.150; 250,000 (4096) even.
+constexpr size_t kSplitGather = 8192;
 constexpr int kBinWaves = 8;
 constexpr int kBinKeys = 4096;  // a bin's keys held in LDS (32 KB)
 
-// The radix sort takes the segments whose bounds cost more than its passes: 1M keys
-// 0.089 ms here against 0.100, 2M 0.154 against 0.125 (four segments of 1M take the
-// radix sort 0.206 ms).
+// The radix sort takes the longest segments, whose bins and runs grow: 1M keys 0.075
+// ms here against 0.100, four segments of 1M 0.169 against 0.208, 2M 0.154 against
+// 0.125.
 DepthPlan depth_plan(int n, int n_seg) {
     DepthPlan p;
     const bool large = n > (1 << 19);
-    p.radix = large && (int64_t)n * n_seg > (1 << 20);
+    p.radix = n > (1 << 20);
     p.lg_bins = 6;
     while (p.lg_bins < (large ? 11 : 10) && ((int64_t)256 << p.lg_bins) < n) ++p.lg_bins;
     p.items = large ? 8 : 4;
     p.blocks = (int)(((int64_t)n + kSplitThreads * p.items - 1) / (kSplitThreads * p.items));
-    // per segment and bin: the bound (64 bits), total, start, and a row per workgroup
+    // per segment and bin: the bound (64 bits), total, start, four samples, and a row
+    // per workgroup
     p.words = p.radix ? radix_hist_words((uint64_t)n, n_seg, kDepthDigitBits, kSortItems)
-                      : ((size_t)n_seg << p.lg_bins) * (4 + (size_t)p.blocks);
+                      : ((size_t)n_seg << p.lg_bins) * (4 + kSplitOver + (size_t)p.blocks);
     return p;
 }
 
@@ -421,38 +425,60 @@ __device__ __forceinline__ int sample_place(int j, int n, int lg) {
 
 __device__ __forceinline__ uint64_t depth_pair(uint32_t key, uint32_t val) { return ((uint64_t)key << 32) | val; }
 
-// A workgroup ranks kSplitRanked samples against all: a sixty-fourth of them per
-// quarter of a wave, keys read from LDS four at a time, the same for a quarter's
-// lanes.  Every fourth sample in order is a bin's lower bound.
+// The samples' keys, for k_depth_bounds' workgroups to read side by side.
+__global__ void __launch_bounds__(256) k_depth_samples(const uint32_t* __restrict__ keys, int n, int lg,
+                                                       uint32_t* __restrict__ samples) {
+    const int j = (int)(blockIdx.x * 256 + threadIdx.x);
+    samples[((size_t)blockIdx.y << lg) + j] = keys[(size_t)blockIdx.y * n + sample_place(j, n, lg)];
+}
+
+// A workgroup ranks kSplitRanked samples against all: a sixteenth of them per wave,
+// four at a time from LDS, the quarters of a wave side by side.  Every fourth sample
+// in order is a bin's lower bound.  samples: their keys (null: read from keys by
+// every workgroup).
 constexpr int kSplitRanked = 16;
 __global__ void __launch_bounds__(kSplitThreads) k_depth_bounds(const uint32_t* __restrict__ keys, uint32_t val0, int n,
-                                                                int lg_bins, uint64_t* __restrict__ bounds) {
+                                                                int lg_bins, const uint32_t* __restrict__ samples,
+                                                                uint64_t* __restrict__ bounds) {
     __shared__ __align__(16) uint32_t s_keys[kSplitOver * kSplitMaxBins];
     __shared__ uint32_t s_rank[kSplitThreads / 64][kSplitRanked];
     const int lg = lg_bins + 2, S = 1 << lg;  // (kSplitOver = 4)
     keys += (size_t)blockIdx.y * n;
     bounds += (size_t)blockIdx.y << lg_bins;
-    for (int j = threadIdx.x; j < S; j += kSplitThreads) s_keys[j] = keys[sample_place(j, n, lg)];
+    if (samples) {
+        const uint4* from = reinterpret_cast<const uint4*>(samples + ((size_t)blockIdx.y << lg));
+        for (int j = threadIdx.x; j < S / 4; j += kSplitThreads) reinterpret_cast<uint4*>(s_keys)[j] = from[j];
+    } else {
+        for (int j = threadIdx.x; j < S; j += kSplitThreads) s_keys[j] = keys[sample_place(j, n, lg)];
+    }
     __syncthreads();
-    const int lane = __lane_id(), w = (int)threadIdx.x >> 6;
+    const int lane = __lane_id(), w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int i0 = (int)blockIdx.x * kSplitRanked, i = i0 + lane % kSplitRanked;
     const uint32_t key = s_keys[i];
-    const int per = S / 64, j0 = (w * 4 + lane / kSplitRanked) * per, j1 = j0 + per;  // (multiples of four)
+    const int j0 = w * (S / 16), j1 = j0 + S / 16;  // (multiples of 16)
+    const int q = 4 * (lane / kSplitRanked);
     uint32_t r = 0u;
+    const auto four = [&](int j) { return *reinterpret_cast<const uint4*>(&s_keys[j + q]); };
     // samples lie in id order: equal keys of lower index come before
+    if (j1 <= i0) {
 #pragma unroll 4
-    for (int j = j0; j < min(j1, i0); j += 4) {
-        const uint4 k = *reinterpret_cast<const uint4*>(&s_keys[j]);
-        r += (k.x <= key ? 1u : 0u) + (k.y <= key ? 1u : 0u) + (k.z <= key ? 1u : 0u) + (k.w <= key ? 1u : 0u);
-    }
-    for (int j = max(j0, i0); j < min(j1, i0 + kSplitRanked); ++j) {
-        const uint32_t k = s_keys[j];
-        r += (k < key || (k == key && j < i)) ? 1u : 0u;
-    }
+        for (int j = j0; j < j1; j += 16) {
+            const uint4 k = four(j);
+            r += (k.x <= key ? 1u : 0u) + (k.y <= key ? 1u : 0u) + (k.z <= key ? 1u : 0u) + (k.w <= key ? 1u : 0u);
+        }
+    } else if (j0 >= i0 + kSplitRanked) {
 #pragma unroll 4
-    for (int j = max(j0, i0 + kSplitRanked); j < j1; j += 4) {
-        const uint4 k = *reinterpret_cast<const uint4*>(&s_keys[j]);
-        r += (k.x < key ? 1u : 0u) + (k.y < key ? 1u : 0u) + (k.z < key ? 1u : 0u) + (k.w < key ? 1u : 0u);
+        for (int j = j0; j < j1; j += 16) {
+            const uint4 k = four(j);
+            r += (k.x < key ? 1u : 0u) + (k.y < key ? 1u : 0u) + (k.z < key ? 1u : 0u) + (k.w < key ? 1u : 0u);
+        }
+    } else {
+        for (int j = j0; j < j1; j += 16) {
+            const uint4 k = four(j);
+            const int at = j + q;
+            r += (k.x < key || (k.x == key && at < i) ? 1u : 0u) + (k.y < key || (k.y == key && at + 1 < i) ? 1u : 0u) +
+                 (k.z < key || (k.z == key && at + 2 < i) ? 1u : 0u) + (k.w < key || (k.w == key && at + 3 < i) ? 1u : 0u);
+        }
     }
     r += __shfl_xor(r, 16);
     r += __shfl_xor(r, 32);
@@ -461,7 +487,7 @@ __global__ void __launch_bounds__(kSplitThreads) k_depth_bounds(const uint32_t* 
     if (threadIdx.x < kSplitRanked) {
         uint32_t at = 0u;
 #pragma unroll
-        for (int q = 0; q < kSplitThreads / 64; ++q) at += s_rank[q][lane];
+        for (int u = 0; u < kSplitThreads / 64; ++u) at += s_rank[u][lane];
         if (at > 0u && at % kSplitOver == 0u)
             bounds[at / kSplitOver - 1] = depth_pair(key, val0 + (uint32_t)sample_place(i, n, lg));
     }
@@ -764,13 +790,18 @@ bool launch_depth_sort(uint32_t* keys, uint32_t val0, uint32_t* vals_out, int n,
     uint64_t* bounds = reinterpret_cast<uint64_t*>(work);
     uint32_t* counts = work + 2 * bins * n_seg;
     uint32_t* starts = counts + bins * n_seg;
-    uint32_t* rows = starts + bins * n_seg;
+    uint32_t* samples = starts + bins * n_seg;
+    uint32_t* rows = samples + kSplitOver * bins * n_seg;
     uint16_t* key_bin = reinterpret_cast<uint16_t*>(vals_out);  // (until the bins are in order)
     const int direct = p.blocks <= kSplitDirect ? 1 : 0;
     const unsigned segs = (unsigned)n_seg;
     const dim3 grid((unsigned)p.blocks, segs);
-    k_depth_bounds<<<dim3((unsigned)(kSplitOver * bins / kSplitRanked), segs), kSplitThreads, 0, st>>>(keys, val0, n, p.lg_bins,
-                                                                                          bounds);
+    // (not by every workgroup that ranks some)
+    const bool gather = kSplitOver * bins * n_seg >= kSplitGather;
+    if (gather)
+        k_depth_samples<<<dim3((unsigned)(kSplitOver * bins / 256), segs), 256, 0, st>>>(keys, n, p.lg_bins + 2, samples);
+    k_depth_bounds<<<dim3((unsigned)(kSplitOver * bins / kSplitRanked), segs), kSplitThreads, 0, st>>>(
+        keys, val0, n, p.lg_bins, gather ? samples : nullptr, bounds);
     if (p.items == 4)
         k_depth_count<4><<<grid, kSplitThreads, 0, st>>>(keys, val0, n, p.lg_bins, bounds, key_bin, rows);
     else

@@ -70,7 +70,8 @@ def test_depth_order(h4d, n):
 def test_long_depth_order(h4d, n, depths):
     """Sorts by bins of sampled keys, from the ranks' longest segment to the radix
     sort's shortest (beyond 2^18 keys the workgroups' counts are scanned by a launch
-    of their own, beyond 2^19 a workgroup takes 8192 keys, not 4096): a whole-image
+    of their own, beyond 2^19 a workgroup takes 8192 keys, not 4096, and the samples are gathered
+    first): a whole-image
     tile's list is the stable depth order, also when most depths are equal or nearly
     so."""
     print(f"[long depth order] n={n} {depths}", flush=True)
