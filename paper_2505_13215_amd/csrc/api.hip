@@ -425,7 +425,7 @@ Layout make_layout(int N, int n3, const h4d_view* views, int V, const h4d_config
         cbits = std::max(cbits, coarse_max_bits(bits_for(L.pass(k).supers)));
     // the depth sort's segments: a pass's views (all Gaussians, or the 4D ones
     // when shared) and the static groups (3D ones)
-    // (words for 256 counts per 512 keys: five eighths suffice, and the ranked
+    // (words for 256 counts per 512 keys: three quarters suffice, and the ranked
     // binning's scratch extends over them)
     size_t dwords = radix_hist_words(n, max_views, kDepthDigitBits, 2);
     if (L.shared)
