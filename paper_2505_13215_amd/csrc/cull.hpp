@@ -82,13 +82,16 @@ __host__ __device__ inline CullShape cull_shape(const Rec& rec) {
 // evaluates a test decides alike.)
 // First pixel whose centre lies at or past centre + x, and last at or before it
 // (i: integer part of the centre, f: fractional part; an undefined x keeps all).
+// The sum of the two whole numbers is exact wherever it lies near the image,
+// however far off the centre is and the ellipse reaches (each is a multiple of its
+// own unit in the last place); beyond, only its side counts.
 __host__ __device__ __forceinline__ int first_pixel(float i, float f, float x) {
 #pragma clang fp contract(off)
-    return (int)i + (int)fminf(fmaxf(ceilf(x + f - 0.5f), -1e6f), 1e6f);
+    return (int)fminf(fmaxf(i + ceilf(x + f - 0.5f), -1e9f), 1e9f);
 }
 __host__ __device__ __forceinline__ int last_pixel(float i, float f, float x) {
 #pragma clang fp contract(off)
-    return (int)i + (int)fmaxf(fminf(floorf(x + f - 0.5f), 1e6f), -1e6f);
+    return (int)fmaxf(fminf(i + floorf(x + f - 0.5f), 1e9f), -1e9f);
 }
 // The tile that holds pixel p (rounded down for pixels left of the image).
 template <int TILE>

@@ -1,0 +1,30 @@
+"""Vast splats whose centre lies far off the image (GPU): images do not depend on
+culling or the tile size, and hold what the splats blend."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("distance", [1e4, 3e6, 1e8])
+def test_images_do_not_depend_on_culling(distance):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_13215_amd as h4d
+    print(f"[far splats] distance {distance:g}", flush=True)
+    n, W, H = 24, 203, 131
+    rng = np.random.default_rng(3)
+    th = rng.uniform(0, 2 * np.pi, n)
+    s = distance * rng.uniform(0.4, 1.5, n)  # round splats
+    f = lambda x: np.asarray(x, np.float32)
+    sp = dict(u=f(distance * np.cos(th)), v=f(distance * np.sin(th)), conic=f(np.stack([s ** -2.0, 0 * s, s ** -2.0])),
+              opacity=f(np.full(n, 0.3)), rgb=f(rng.uniform(0, 1, (3, n))), radius=np.ceil(3 * s).astype(np.int32),
+              depth=f(rng.uniform(1, 5, n)), visible=np.ones(n, np.uint8))
+    want = h4d.rasterize_splats(h4d.Rasterizer(tile=8, cull=False), sp, W, H)[:2]
+    # (0.3 exp(-0.5 / 0.4^2) = 0.013 at the least, where 1/255 suffices)
+    assert float(want[1].max()) < 0.9
+    for tile in (8, 16, 32):
+        for cull in (False, True):
+            got = h4d.rasterize_splats(h4d.Rasterizer(tile=tile, cull=cull), sp, W, H)[:2]
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (tile, cull)
