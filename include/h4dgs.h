@@ -147,8 +147,8 @@ const char *h4dgs_version(void);
  * inference render needs only a leading part of the state (no gradient
  * records: N x n_views x 64 bytes less).  Calls of at most 2048 tiles of 16 x
  * 16 pixels include 29 KiB per tile for the adjoint's checkpoints, without which
- * (a smaller state) they run slower; render_bwd takes the state_bytes of its
- * render_fwd. */
+ * (a smaller state) they run slower; so does a render_bwd whose state_bytes has
+ * room for them where its render_fwd's had not, or the other way round. */
 h4d_status h4dgs_workspace_size(h4d_ctx *ctx, int32_t n3, int32_t n4, const h4d_view *views, int32_t n_views,
                                 const h4d_config *cfg, size_t *state_bytes, size_t *scratch_bytes);
 

@@ -250,6 +250,8 @@ struct Layout {
     size_t scratch_bytes;
 
     int n_passes() const { return n_pass; }
+    // entries of each tile's list head (quad: the state has room for the checkpoints)
+    int tile_ids(bool quad) const { return quad ? kQuadIds : kTileIds; }
     Pass pass(int k) const { return passes[k]; }
     // depth-ordered entries of a pass and their segment layout
     SegLayout segs(const Pass& P) const {
@@ -753,7 +755,7 @@ void blend_pass(h4d_ctx* c, const Layout& L, int k, int tile, int chunk, void* s
                          keep ? at<float>(state, L.st_T) : nullptr, keep ? at<uint32_t>(state, L.st_nc) : nullptr,
                          keep ? at<float>(state, L.st_C) : nullptr, keep ? at<uint32_t>(state, L.st_tcost) : nullptr,
                          keep ? at<uint32_t>(state, L.st_thist) + (size_t)kCostBuckets * k : nullptr,
-                         keep ? at<uint32_t>(state, L.st_tids) : nullptr, quad ? kQuadIds : kTileIds,
+                         keep ? at<uint32_t>(state, L.st_tids) : nullptr, L.tile_ids(quad),
                          keep && quad ? at<float4>(state, L.st_chk) : nullptr, at<Status>(state, L.st_status),
                          keep ? stat_counters(c, state, L) : nullptr,
                          st, km.a, km.b);
@@ -847,7 +849,7 @@ static h4d_status render_forward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d*
     const G4Ptr p4 = to_ptr(g4);
     ViewParams* vp = at<ViewParams>(state, L.st_views);
     launch_init_state(view_table(views, n_views, cfg->tile, L), vp, at<Status>(state, L.st_status),
-                      at<unsigned long long>(state, L.st_pair_base), at<unsigned long long>(state, L.st_cranges),
+                      keep ? L.tile_ids(quad) : 0, at<unsigned long long>(state, L.st_pair_base), at<unsigned long long>(state, L.st_cranges),
                       range_words(L), st);
     PtrTable tab;
     std::memset(&tab, 0, sizeof(tab));
@@ -939,7 +941,7 @@ static h4d_status render_backward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d
     if ((s = check_layout(ctx, L, cfg)) != H4D_OK) return s;
     if (!state || state_bytes < L.min_state_bytes)
         return fail(ctx, H4D_ERR_INVALID_ARG, "state too small (%zu < %zu)", state_bytes, L.min_state_bytes);
-    const bool quad = L.quad && state_bytes >= L.state_bytes;  // (as the forward on this state)
+    const bool quad = L.quad && state_bytes >= L.state_bytes;
     if (!scratch || scratch_bytes < L.bwd_bytes)
         return fail(ctx, H4D_ERR_INVALID_ARG, "scratch too small (%zu < %zu)", scratch_bytes, L.bwd_bytes);
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -980,7 +982,7 @@ static h4d_status render_backward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d
                                  L.shared, static_rows, vp, P.v0, P.v1, P.tiles, border + pt.tile0[k], tab,
                                  at<float>(stt, L.st_T),
                                  at<uint32_t>(stt, L.st_nc), at<float>(stt, L.st_C), at<uint32_t>(stt, L.st_tcost),
-                                 at<uint32_t>(stt, L.st_tids), quad ? kQuadIds : kTileIds,
+                                 at<uint32_t>(stt, L.st_tids), L.tile_ids(quad),
                                  quad ? at<float4>(stt, L.st_chk) : nullptr, wide, status, g2,
                                  stat_counters(ctx, stt, L),
                                  st, km.a, km.b);
@@ -1059,9 +1061,10 @@ h4d_status h4dgs_rasterize_splats(h4d_ctx* ctx, int32_t n, const float* u, const
     if (!state || state_bytes < L.min_state_bytes) return fail(ctx, H4D_ERR_INVALID_ARG, "state too small");
     if (!scratch || scratch_bytes < L.fwd_bytes) return fail(ctx, H4D_ERR_INVALID_ARG, "scratch too small");
     if (!plan_fits(L)) return fail(ctx, H4D_ERR_UNSUPPORTED, "internal: radix buffers of the layout too small");
+    const bool quad = L.quad && state_bytes >= L.state_bytes;
     hipStream_t st = static_cast<hipStream_t>(stream);
     launch_init_state(view_table(&view, 1, cfg->tile, L), at<ViewParams>(state, L.st_views),
-                      at<Status>(state, L.st_status), at<unsigned long long>(state, L.st_pair_base),
+                      at<Status>(state, L.st_status), L.tile_ids(quad), at<unsigned long long>(state, L.st_pair_base),
                       at<unsigned long long>(state, L.st_cranges), range_words(L), st);
     Rec* recs = at<Rec>(state, L.st_recs);
     launch_splats_to_records(n, u, v, conic, opacity, rgb, radius, depth, visible, width, height, recs,
@@ -1071,7 +1074,7 @@ h4d_status h4dgs_rasterize_splats(h4d_ctx* ctx, int32_t n, const float* u, const
     tab.p[0] = image;
     if (!bin_pass(ctx, L, L.pass(0), cfg->tile, cfg->cull, state, scratch, st, true))
         return fail(ctx, H4D_ERR_UNSUPPORTED, "internal: a radix pass did not fit its buffers");
-    blend_pass(ctx, L, 0, cfg->tile, cfg->chunk, state, tab, st, true, L.quad && state_bytes >= L.state_bytes);
+    blend_pass(ctx, L, 0, cfg->tile, cfg->chunk, state, tab, st, true, quad);
     const size_t hw = (size_t)width * height;
     if (T_final) (void)hipMemcpyAsync(T_final, at<float>(state, L.st_T), 4 * hw, hipMemcpyDeviceToDevice, st);
     if (sorted_ids && ranges)

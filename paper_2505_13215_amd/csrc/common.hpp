@@ -157,7 +157,10 @@ struct Status {
     // counters of the counting variants (h4dgs_stats): blend evaluations and
     // blends of the forward and the adjoint, tile-list entries, traversed
     // entries (each tile's last contributor) and on-screen records
-    unsigned long long pad[12];
+    unsigned long long pad[11];
+    // entries per tile in the list heads that the forward kept (0: none), which a
+    // backward reads only if it has them at the same places
+    unsigned long long list_heads;
     // nonzero once a forward has left the quadrant kernels' checkpoints
     unsigned long long checkpoints;
     // nonzero once a backward has accumulated into the screen-space gradient

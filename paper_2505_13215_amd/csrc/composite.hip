@@ -700,6 +700,11 @@ struct QuadSegs {
     const float4* chk;      // checkpoints
     const Status* status;
 };
+// Entries of each tile's list that the adjoint finds in the kept heads: tile_ids of
+// them, or none where the forward's state had another size and they lie elsewhere.
+__device__ __forceinline__ uint32_t held_ids(const Status* status, int tile_ids) {
+    return status->list_heads == (unsigned long long)tile_ids ? (uint32_t)tile_ids : 0u;
+}
 // The (tile, segment) of this workgroup and the list entries [first, end) it
 // takes; false: none.  The last segment goes on to the list's end; without
 // checkpoints (status->checkpoints: a counting forward leaves none) the first
@@ -834,12 +839,13 @@ __global__ void __launch_bounds__(Shape<B>::NT, 5) k_composite_bwd(
     const int tid = (int)threadIdx.x;
     // the forward kept the list's head: a tile whose contributors all lie in
     // it reads them from there, any other walks its list again
-    bool kept = SEG ? true : total <= (uint32_t)tile_ids;
+    const uint32_t held = held_ids(segs.status, tile_ids);
+    bool kept = SEG ? true : total <= held;
     const uint32_t* __restrict__ head = tids + (size_t)gt * tile_ids;
     for (uint32_t rel0 = first; rel0 < total;) {
         __syncthreads();  // the previous chunk's LDS is no longer read
         int cnt;
-        if (SEG && kept && rel0 >= (uint32_t)tile_ids) {  // past the head: walk to here
+        if (SEG && kept && rel0 >= held) {  // past the head: walk to here
             uint32_t id;
             for (uint32_t r = 0; r < rel0; r += 64) (void)walk.next(64, s_q, id);
             kept = false;
@@ -1030,10 +1036,11 @@ __global__ void __launch_bounds__(256) k_composite_bwd_quad(
     const int comp = lr == 0 ? comp0 : (lr == 8 ? 4 + comp0 : 8 + row);
     TileWalk<MERGE> walk;
     walk.init(lists, V, view, recs, N, super_factor(16), tx, ty);
+    const uint32_t held = held_ids(segs.status, kQuadIds);
     bool walking = false;  // past the kept head: the list is walked again
     for (uint32_t rel0 = first; rel0 < end;) {
         int cnt = (int)min((uint32_t)kQuadChunk, end - rel0);
-        if (rel0 + (uint32_t)cnt > (uint32_t)kQuadIds) {  // uniform
+        if (rel0 + (uint32_t)cnt > held) {  // uniform
             if (w == 0) {
                 uint32_t id = 0u;
                 for (uint32_t r = 0; !walking && r < rel0; r += kQuadChunk) (void)walk.next(kQuadChunk, s_q, id);
@@ -1197,7 +1204,7 @@ static void bwd_t(const Rec* recs, int N, const CoarseLists& lists, bool merge, 
     launch_timed(merge ? (stats ? k_composite_bwd<B, C, true, true> : k_composite_bwd<B, C, false, true>)
                        : (stats ? k_composite_bwd<B, C, true, false> : k_composite_bwd<B, C, false, false>),
                  n_tiles, NT, st, e0, e1, recs, N, lists, static_rows, views, v0, v1, order, dls, Tfin, ncontrib,
-                 Cout, tids, tile_ids, g2, counters, QuadSegs{});
+                 Cout, tids, tile_ids, g2, counters, QuadSegs{n_tiles, tcost, nullptr, status});
 }
 
 // Tile lists written out (for inspection): one wave per tile walks the list as

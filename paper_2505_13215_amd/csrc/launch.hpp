@@ -26,9 +26,11 @@ struct ViewTableIn {
 };
 
 // preprocess.hip
-// The view table, cleared status / list-slot bases and empty tile ranges.
-void launch_init_state(const ViewTableIn& in, ViewParams* views, Status* status, unsigned long long* pair_base,
-                       unsigned long long* ranges, size_t n_range_words, hipStream_t st);
+// The view table, cleared status / list-slot bases and empty tile ranges;
+// list_heads: what the forward will keep of each tile's list (Status).
+void launch_init_state(const ViewTableIn& in, ViewParams* views, Status* status, int list_heads,
+                       unsigned long long* pair_base, unsigned long long* ranges, size_t n_range_words,
+                       hipStream_t st);
 // Counting variant: the on-screen (view, Gaussian) records of views [v0, v0 +
 // nv) (3D Gaussians read from each view's static_view), added to *counter.
 void launch_count_onscreen(const Rec* recs, int N, int n4, const ViewParams* views, int v0, int nv,
@@ -221,7 +223,8 @@ bool composite_supported(int tile, int chunk);
 // contributor into tcost[global tile] and counts the launch's tiles per
 // cost_bucket into thist[kCostBuckets] (zero on entry) and keeps the first
 // tile_ids entries of each tile's list in tids[global tile][tile_ids] (may be
-// null), which the adjoint reads for tiles whose contributors all lie there.
+// null), which the adjoint reads for tiles whose contributors all lie there,
+// where the forward kept as many (status->list_heads).
 // chk (may be null; launches of at most kQuadTiles 16 x 16 tiles, tile_ids =
 // kQuadIds): the pixels' transmittance and colour at the starts of the list's
 // segments after the first, [global tile][kQuadSegs - 1][256]; status: where

@@ -931,11 +931,13 @@ __device__ void write_views(const ViewTableIn& in, ViewParams* out) {
 // Start of a forward call: the view table, cleared status and list-slot bases,
 // and empty tile ranges, in one launch.
 __global__ void __launch_bounds__(256) k_init_state(ViewTableIn in, ViewParams* views, Status* status,
-                                                    unsigned long long* pair_base,
+                                                    int list_heads, unsigned long long* pair_base,
                                                     unsigned long long* ranges, size_t n_range_words) {
     if (blockIdx.x == 0) {
         if (threadIdx.x == 0) write_views(in, views);
-        if (threadIdx.x < sizeof(Status) / 8) (&status->flags)[threadIdx.x] = 0ull;
+        constexpr unsigned heads = offsetof(Status, list_heads) / 8;
+        if (threadIdx.x < sizeof(Status) / 8)
+            (&status->flags)[threadIdx.x] = threadIdx.x == heads ? (unsigned long long)list_heads : 0ull;
         for (int v = threadIdx.x; v <= in.n; v += blockDim.x) pair_base[v] = 0ull;
     }
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_range_words;
@@ -943,10 +945,11 @@ __global__ void __launch_bounds__(256) k_init_state(ViewTableIn in, ViewParams* 
         ranges[i] = 0ull;
 }
 
-void launch_init_state(const ViewTableIn& in, ViewParams* views, Status* status, unsigned long long* pair_base,
-                       unsigned long long* ranges, size_t n_range_words, hipStream_t st) {
+void launch_init_state(const ViewTableIn& in, ViewParams* views, Status* status, int list_heads,
+                       unsigned long long* pair_base, unsigned long long* ranges, size_t n_range_words,
+                       hipStream_t st) {
     const int nb = (int)std::max<size_t>(1, std::min<size_t>(1024, (n_range_words + 255) / 256));
-    k_init_state<<<nb, 256, 0, st>>>(in, views, status, pair_base, ranges, n_range_words);
+    k_init_state<<<nb, 256, 0, st>>>(in, views, status, list_heads, pair_base, ranges, n_range_words);
 }
 
 void launch_preprocess(const G3Ptr& g3, const G4Ptr& g4, const ViewParams* views, int v0, int nv, int shared,
