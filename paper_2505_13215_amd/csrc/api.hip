@@ -155,7 +155,15 @@ h4d_status read_back(h4d_ctx* c, void* dst, const void* src, size_t bytes, hipSt
             return hip_check(c, where);
         return H4D_OK;
     }
-    launch_copy_words(static_cast<const uint32_t*>(src), static_cast<uint32_t*>(pin), (int)(bytes / 4), st);
+    // (the block holds an earlier read-back's words: a copy that was not enqueued
+    // must not pass for this one's)
+    const hipError_t e =
+        launch_copy_words(static_cast<const uint32_t*>(src), static_cast<uint32_t*>(pin), (int)(bytes / 4), st);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        c->give_pin(pin);
+        return fail(c, H4D_ERR_HIP, "%s: %s", where, hipGetErrorString(e));
+    }
     // (a block whose kernel may still run is not handed out again)
     if (hipStreamSynchronize(st) != hipSuccess) return hip_check(c, where);
     std::memcpy(dst, pin, bytes);

@@ -208,7 +208,8 @@ bool launch_bwd_prologue(float* g2, size_t n_g2, const unsigned long long* dirty
                          const uint32_t* thist, const PassTiles& passes, const OrderSort& sort, uint32_t* order,
                          hipStream_t st);
 void launch_fill_u64(unsigned long long* p, size_t n, unsigned long long val, hipStream_t st);
-void launch_copy_words(const uint32_t* src, uint32_t* dst, int n, hipStream_t st);
+// n <= 64 words; returns whether it was enqueued
+hipError_t launch_copy_words(const uint32_t* src, uint32_t* dst, int n, hipStream_t st);
 void launch_fill_f32(float* p, size_t n, float val, hipStream_t st);
 
 // composite.hip

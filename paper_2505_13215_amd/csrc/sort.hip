@@ -2074,8 +2074,10 @@ void launch_fill_u64(unsigned long long* p, size_t n, unsigned long long val, hi
 __global__ void k_copy_words(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, int n) {
     if ((int)threadIdx.x < n) dst[threadIdx.x] = src[threadIdx.x];
 }
-void launch_copy_words(const uint32_t* src, uint32_t* dst, int n, hipStream_t st) {
-    if (n > 0 && n <= 64) k_copy_words<<<1, 64, 0, st>>>(src, dst, n);
+hipError_t launch_copy_words(const uint32_t* src, uint32_t* dst, int n, hipStream_t st) {
+    if (n < 0 || n > 64) return hipErrorInvalidValue;
+    void* args[] = {&src, &dst, &n};
+    return hipLaunchKernel((const void*)k_copy_words, dim3(1), dim3(64), args, 0, st);
 }
 
 void launch_fill_f32(float* p, size_t n, float val, hipStream_t st) {
