@@ -143,15 +143,27 @@ h4d_status hip_check(h4d_ctx* c, const char* where) {
     return H4D_OK;
 }
 
+// Whether p lies on the device that work on `st` runs on.
+bool on_device_of(const void* p, hipStream_t st) {
+    int of_p = -1, of_st = -1;
+    if (hipPointerGetAttribute(&of_p, HIP_POINTER_ATTRIBUTE_DEVICE_ORDINAL, const_cast<void*>(p)) != hipSuccess ||
+        hipStreamGetDevice(st, &of_st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return of_p == of_st;
+}
+
 // Copies a few 32-bit words behind the work enqueued on `st` to the host
 // (synchronises once).  A kernel stores them to pinned memory: a copy into pageable
 // memory costs a staging copy and its wait (a render of 2,000 Gaussians with its
-// check 0.113 -> 0.103 ms, densification of 250k 0.237 -> 0.208).
-h4d_status read_back(h4d_ctx* c, void* dst, const void* src, size_t bytes, hipStream_t st, const char* where) {
-    void* pin = bytes <= h4d_ctx::kPinBytes ? c->take_pin() : nullptr;
+// check 0.113 -> 0.103 ms, densification of 250k 0.237 -> 0.208).  here: src lies on
+// the stream's device; a kernel there may not reach another's memory.
+h4d_status read_back(h4d_ctx* c, void* dst, const void* src, size_t bytes, hipStream_t st, bool here,
+                     const char* where) {
+    void* pin = here && bytes <= h4d_ctx::kPinBytes ? c->take_pin() : nullptr;
     if (!pin) {
-        if (hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess)
+        if (hipStreamSynchronize(st) != hipSuccess || hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost) != hipSuccess)
             return hip_check(c, where);
         return H4D_OK;
     }
@@ -1036,7 +1048,8 @@ h4d_status h4dgs_check(h4d_ctx* ctx, const void* state, size_t state_bytes, int6
     hipStream_t st = static_cast<hipStream_t>(stream);
     unsigned long long hs[2];  // flags, pairs_needed
     static_assert(offsetof(Status, flags) == 0 && offsetof(Status, pairs_needed) == 8, "");
-    if (const h4d_status s = read_back(ctx, hs, state, sizeof(hs), st, "check: status copy"); s != H4D_OK) return s;
+    if (const h4d_status s = read_back(ctx, hs, state, sizeof(hs), st, on_device_of(state, st), "check: status copy");
+        s != H4D_OK) return s;
     if (pairs_needed) *pairs_needed = (int64_t)hs[1];
     if (hs[0] & kFlagOverflow)
         return fail(ctx, H4D_ERR_CAPACITY, "pair capacity exceeded: %llu pairs needed", hs[1]);
@@ -1153,7 +1166,8 @@ h4d_status convert_plan(h4d_ctx* ctx, const h4d_g4d* in4, int n3, float tau, int
     h4d_status s;
     if ((s = hip_check(ctx, "convert_static")) != H4D_OK) return s;
     unsigned long long conv = 0;
-    if ((s = read_back(ctx, &conv, partials + nb, sizeof(conv), st, "convert_static: count readback")) != H4D_OK) return s;
+    if ((s = read_back(ctx, &conv, partials + nb, sizeof(conv), st, true, "convert_static: count readback")) != H4D_OK)
+        return s;
     *n4_out = in4->n - (int32_t)conv;
     *n3_out = n3 + (int32_t)conv;
     return H4D_OK;
@@ -1268,7 +1282,7 @@ h4d_status densify_plan(h4d_ctx* ctx, const h4d_g3d* in3, const h4d_g4d* in4, co
     h4d_status s;
     if ((s = hip_check(ctx, "densify")) != H4D_OK) return s;
     unsigned long long h[6];
-    if ((s = read_back(ctx, h, d.s[0].totals, sizeof(h), st, "densify: count readback")) != H4D_OK) return s;
+    if ((s = read_back(ctx, h, d.s[0].totals, sizeof(h), st, true, "densify: count readback")) != H4D_OK) return s;
     for (int q = 0; q < 6; ++q) counts[q] = (int32_t)h[q];
     return H4D_OK;
 }

@@ -40,3 +40,27 @@ ctx.close()
 got = [c[0] for c in calls()]
 assert got.count("malloc") == 1 == got.count("free"), got
 """)
+
+
+def test_a_state_of_another_device_is_copied(stub):
+    """A kernel on the stream's device may have no access to another device's
+    memory: such a state is read by a copy."""
+    hip_record.run(stub, STATE + """
+calls()
+R.record_set(0, 0, 1, 0)  # the state on device 1, the stream on device 0
+state[0], state[1] = 0, 11
+assert check() == L.H4D_OK and need.value == 11
+assert calls() == [["sync"], ["memcpy"]]
+R.record_set(0, 0, 1, 1)
+state[1] = 12
+assert check() == L.H4D_OK and need.value == 12
+assert [c[0] for c in calls()] == ["launch", "sync"]
+""")
+
+
+def test_without_pinned_memory(stub):
+    hip_record.run(stub, """
+R.record_set(0, 2, 0, 0)  # (out of memory)
+""" + STATE + """
+assert not kernels(calls())
+""")
