@@ -36,31 +36,41 @@ struct h4d_ctx {
         return e;
     }
     // Pinned words that read-backs land in: a block per read-back in flight, kept
-    // for the next (as many as threads have read back at the same time).
-    static constexpr size_t kPinBytes = 64;
+    // for the next (as many as threads have read back at the same time).  The lists
+    // run through the blocks, so that keeping one allocates nothing that could throw.
+    struct Pin {
+        uint32_t words[16];
+        Pin *older, *next_free;
+    };
     std::mutex pin_lock;
-    std::vector<void*> pins, free_pins;
-    void* take_pin() {
+    Pin *pins = nullptr, *free_pins = nullptr;
+    Pin* take_pin() {
         const std::lock_guard<std::mutex> g(pin_lock);
-        if (!free_pins.empty()) {
-            void* p = free_pins.back();
-            free_pins.pop_back();
+        Pin* p = free_pins;
+        if (p) {
+            free_pins = p->next_free;
             return p;
         }
-        void* p = nullptr;
-        if (hipHostMalloc(&p, kPinBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        void* mem = nullptr;
+        if (hipHostMalloc(&mem, sizeof(Pin), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
             (void)hipGetLastError();
             return nullptr;
         }
-        pins.push_back(p);
+        p = static_cast<Pin*>(mem);
+        p->older = pins;
+        pins = p;
         return p;
     }
-    void give_pin(void* p) {
+    void give_pin(Pin* p) {
         const std::lock_guard<std::mutex> g(pin_lock);
-        free_pins.push_back(p);
+        p->next_free = free_pins;
+        free_pins = p;
     }
     ~h4d_ctx() {
-        for (void* p : pins) (void)hipHostFree(p);
+        while (Pin* p = pins) {
+            pins = p->older;
+            (void)hipHostFree(p);
+        }
         for (auto& m : marks) {
             if (m.a) (void)hipEventDestroy(m.a);
             if (m.b) (void)hipEventDestroy(m.b);
@@ -161,7 +171,7 @@ bool on_device_of(const void* p, hipStream_t st) {
 // the stream's device; a kernel there may not reach another's memory.
 h4d_status read_back(h4d_ctx* c, void* dst, const void* src, size_t bytes, hipStream_t st, bool here,
                      const char* where) {
-    void* pin = here && bytes <= h4d_ctx::kPinBytes ? c->take_pin() : nullptr;
+    h4d_ctx::Pin* pin = here && bytes <= sizeof(pin->words) ? c->take_pin() : nullptr;
     if (!pin) {
         if (hipStreamSynchronize(st) != hipSuccess || hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost) != hipSuccess)
             return hip_check(c, where);
@@ -170,7 +180,7 @@ h4d_status read_back(h4d_ctx* c, void* dst, const void* src, size_t bytes, hipSt
     // (the block holds an earlier read-back's words: a copy that was not enqueued
     // must not pass for this one's)
     const hipError_t e =
-        launch_copy_words(static_cast<const uint32_t*>(src), static_cast<uint32_t*>(pin), (int)(bytes / 4), st);
+        launch_copy_words(static_cast<const uint32_t*>(src), pin->words, (int)(bytes / 4), st);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         c->give_pin(pin);
@@ -178,7 +188,7 @@ h4d_status read_back(h4d_ctx* c, void* dst, const void* src, size_t bytes, hipSt
     }
     // (a block whose kernel may still run is not handed out again)
     if (hipStreamSynchronize(st) != hipSuccess) return hip_check(c, where);
-    std::memcpy(dst, pin, bytes);
+    std::memcpy(dst, pin->words, bytes);
     c->give_pin(pin);
     return H4D_OK;
 }

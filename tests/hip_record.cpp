@@ -7,7 +7,25 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
+
+namespace {
+// The library's allocations fail on request (not those made here).
+bool new_fails = false;
+int inside = 0;
+struct Inside {
+    Inside() { ++inside; }
+    ~Inside() { --inside; }
+};
+}  // namespace
+
+void* operator new(std::size_t n) {
+    if (new_fails && inside == 0) throw std::bad_alloc();
+    return std::malloc(n ? n : 1);
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
 
 namespace {
 struct Dim {
@@ -20,11 +38,16 @@ Dim g_grid, g_block;
 size_t g_shared;
 void* g_stream;
 
+void note(const char* what) {
+    const Inside in;
+    calls += what;
+}
 int set(int e) {
     if (e) last_error = e;
     return e;
 }
 int launch(const void* f, Dim g, Dim b, void** args) {
+    const Inside in;
     const std::string& name = names[f];
     char line[256];
     std::snprintf(line, sizeof line, "launch %s %u %u %u %u\n", name.c_str(), g.x, g.y, g.z, b.x);
@@ -42,6 +65,7 @@ int launch(const void* f, Dim g, Dim b, void** args) {
 extern "C" {
 const char* record_calls() { return calls.c_str(); }
 void record_clear() { calls.clear(); }
+void record_new_fails(int on) { new_fails = on != 0; }
 void record_set(int launch_e, int malloc_e, int pointer_dev, int stream_dev) {
     launch_error = launch_e;
     malloc_error = malloc_e;
@@ -84,28 +108,28 @@ int hipGetLastError() {
 }
 const char* hipGetErrorString(int) { return "recorded error"; }
 int hipHostMalloc(void** p, size_t n, unsigned) {
-    calls += "malloc\n";
+    note("malloc\n");
     if (malloc_error) return set(malloc_error);
     *p = std::calloc(1, n);
     return 0;
 }
 int hipHostFree(void* p) {
-    calls += "free\n";
+    note("free\n");
     std::free(p);
     return 0;
 }
 int hipMemcpy(void* dst, const void* src, size_t n, int) {
-    calls += "memcpy\n";
+    note("memcpy\n");
     std::memcpy(dst, src, n);
     return 0;
 }
 int hipMemcpyAsync(void* dst, const void* src, size_t n, int, void*) {
-    calls += "memcpy_async\n";
+    note("memcpy_async\n");
     std::memcpy(dst, src, n);
     return 0;
 }
 int hipStreamSynchronize(void*) {
-    calls += "sync\n";
+    note("sync\n");
     return 0;
 }
 int hipGetDevice(int* d) {

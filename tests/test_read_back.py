@@ -64,3 +64,13 @@ R.record_set(0, 2, 0, 0)  # (out of memory)
 """ + STATE + """
 assert not kernels(calls())
 """)
+
+
+def test_nothing_is_thrown(stub):
+    """A context keeps its pinned blocks without host allocations that could throw
+    across the C entry."""
+    hip_record.run(stub, """
+R.record_new_fails(1)
+""" + STATE.replace("state[0], state[1] = 1, 9", "state[1] = 9").replace("H4D_ERR_CAPACITY", "H4D_OK") + """
+R.record_new_fails(0)
+""")
