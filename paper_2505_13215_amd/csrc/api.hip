@@ -171,6 +171,14 @@ bool on_device_of(const void* p, hipStream_t st) {
 // the stream's device; a kernel there may not reach another's memory.
 h4d_status read_back(h4d_ctx* c, void* dst, const void* src, size_t bytes, hipStream_t st, bool here,
                      const char* where) {
+    // (under capture the wait below fails; a block would be lost to a copy that the
+    // graph may hold)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        capture = hipStreamCaptureStatusActive;
+    }
+    here = here && capture == hipStreamCaptureStatusNone;
     h4d_ctx::Pin* pin = here && bytes <= sizeof(pin->words) ? c->take_pin() : nullptr;
     if (!pin) {
         if (hipStreamSynchronize(st) != hipSuccess || hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost) != hipSuccess)

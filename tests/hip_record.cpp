@@ -33,7 +33,7 @@ struct Dim {
 };
 std::map<const void*, std::string> names;
 std::string calls;
-int last_error = 0, launch_error = 0, malloc_error = 0, pointer_device = 0, stream_device = 0;
+int last_error = 0, launch_error = 0, malloc_error = 0, pointer_device = 0, stream_device = 0, capturing = 0;
 Dim g_grid, g_block;
 size_t g_shared;
 void* g_stream;
@@ -65,6 +65,7 @@ int launch(const void* f, Dim g, Dim b, void** args) {
 extern "C" {
 const char* record_calls() { return calls.c_str(); }
 void record_clear() { calls.clear(); }
+void record_capturing(int on) { capturing = on; }
 void record_new_fails(int on) { new_fails = on != 0; }
 void record_set(int launch_e, int malloc_e, int pointer_dev, int stream_dev) {
     launch_error = launch_e;
@@ -130,6 +131,10 @@ int hipMemcpyAsync(void* dst, const void* src, size_t n, int, void*) {
 }
 int hipStreamSynchronize(void*) {
     note("sync\n");
+    return set(capturing ? 900 : 0);
+}
+int hipStreamIsCapturing(void*, int* status) {
+    *status = capturing;
     return 0;
 }
 int hipGetDevice(int* d) {

@@ -74,3 +74,17 @@ R.record_new_fails(1)
 """ + STATE.replace("state[0], state[1] = 1, 9", "state[1] = 9").replace("H4D_ERR_CAPACITY", "H4D_OK") + """
 R.record_new_fails(0)
 """)
+
+
+def test_under_capture(stub):
+    """Refused before anything is recorded into the graph or kept for it."""
+    hip_record.run(stub, STATE + """
+calls()
+R.record_capturing(1)
+for _ in range(3):
+    assert check() == L.H4D_ERR_HIP
+assert calls() == [["sync"]] * 3
+R.record_capturing(0)
+assert check() == L.H4D_ERR_CAPACITY
+assert [c[0] for c in calls()] == ["launch", "sync"]
+""")
