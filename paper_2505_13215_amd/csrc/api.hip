@@ -319,6 +319,37 @@ bool same_camera(const h4d_view& a, const h4d_view& b) {
            a.fy == b.fy && a.cx == b.cx && a.cy == b.cy && a.width == b.width && a.height == b.height;
 }
 
+// Depth sorts of a pass: segments of equal length starting at `offset` in the
+// key arrays (the pass's views; with shared static binning, the views' 4D
+// Gaussians and the static groups' 3D Gaussians).
+struct DepthJob {
+    size_t offset;
+    int n_seg;
+    int len;
+    uint32_t id0;  // id of a segment's first Gaussian
+};
+// Whether a job's segments are short enough to rank by counting pairs of keys.
+// A workgroup places 64 keys against all of its segment's in 1.6 ns per key, one
+// workgroup on each of 256 CUs at a time: 2,000 keys 0.005 ms, 8,000 0.014 ms,
+// 16,000 0.026 ms.  Bins of sampled keys take 0.021 ms at 10,000 keys and 0.023 at
+// 18,000, and three launches more.  (32 segments of 1,024 keys take two rounds: no
+// segment as short as that goes to bins.)
+bool depth_ranks(const DepthJob& j) {
+    const int64_t rounds = ((int64_t)j.n_seg * ((j.len + 63) / 64) + 255) / 256;
+    return rounds * j.len <= 13000;
+}
+int depth_jobs(const Layout& L, const Pass& P, DepthJob* jobs) {
+    const int nv = P.v1 - P.v0;
+    int n = 0;
+    if (!L.shared) {
+        jobs[n++] = DepthJob{0, nv, L.N, 0u};
+        return n;
+    }
+    if (L.n4 > 0) jobs[n++] = DepthJob{0, nv, L.n4, 0u};
+    if (L.n3 > 0) jobs[n++] = DepthJob{(size_t)nv * L.n4, L.n_groups, L.n3, (uint32_t)L.n4};
+    return n;
+}
+
 Layout make_layout(int N, int n3, const h4d_view* views, int V, const h4d_config* cfg) {
     Layout L;
     L.N = N;
@@ -465,12 +496,18 @@ Layout make_layout(int N, int n3, const h4d_view* views, int V, const h4d_config
         cbits = std::max(cbits, coarse_max_bits(bits_for(L.pass(k).supers)));
     // the depth sort's segments: a pass's views (all Gaussians, or the 4D ones
     // when shared) and the static groups (3D ones)
-    // (words for 256 counts per 512 keys: three quarters suffice, and the ranked
-    // binning's scratch extends over them)
+    // (words for 256 counts per 512 keys, over which the ranked binning's scratch
+    // extends, and at least what the plans of the jobs that are not ranked take)
     size_t dwords = radix_hist_words(n, max_views, kDepthDigitBits, 2);
     if (L.shared)
         dwords = std::max(radix_hist_words((uint64_t)L.n4, V, kDepthDigitBits, 2),
                           radix_hist_words((uint64_t)L.n3, L.n_groups, kDepthDigitBits, 2));
+    for (int k = 0; k < L.n_passes(); ++k) {
+        DepthJob jobs[2];
+        const int nj = depth_jobs(L, L.pass(k), jobs);
+        for (int q = 0; q < nj; ++q)
+            if (!depth_ranks(jobs[q])) dwords = std::max(dwords, depth_plan(jobs[q].len, jobs[q].n_seg).words);
+    }
     L.hist_words = std::max(radix_hist_words(L.ccap, 1, cbits, kSortItems), dwords);
     L.totals_words = (size_t)kMaxRadix * (size_t)max_views;
     L.sc_hist = f.take(4 * L.hist_words);
@@ -502,47 +539,13 @@ Layout make_layout(int N, int n3, const h4d_view* views, int V, const h4d_config
 // Every radix pass the forward will launch fits the layout's histogram and
 // digit-total buffers (checked on the host before anything is enqueued; the
 // launcher checks each pass again).
-// Depth sorts of a pass: segments of equal length starting at `offset` in the
-// key arrays (the pass's views; with shared static binning, the views' 4D
-// Gaussians and the static groups' 3D Gaussians).
-struct DepthJob {
-    size_t offset;
-    int n_seg;
-    int len;
-    uint32_t id0;  // id of a segment's first Gaussian
-};
-// Whether a pass's segments are short enough to rank by counting pairs of keys.
-// A workgroup places 64 keys against all of its segment's in 1.6 ns per key, one
-// workgroup on each of 256 CUs at a time: 2,000 keys 0.005 ms, 8,000 0.014 ms,
-// 16,000 0.026 ms.  Bins of sampled keys take 0.021 ms at 10,000 keys and 0.023 at
-// 18,000, and three launches more.
-bool depth_ranks(const DepthJob* jobs, int n) {
-    int64_t keys = 0;
-    for (int q = 0; q < n; ++q) {
-        const int64_t rounds = ((int64_t)jobs[q].n_seg * ((jobs[q].len + 63) / 64) + 255) / 256;
-        keys += rounds * jobs[q].len;
-    }
-    return keys <= 13000;
-}
-int depth_jobs(const Layout& L, const Pass& P, DepthJob* jobs) {
-    const int nv = P.v1 - P.v0;
-    int n = 0;
-    if (!L.shared) {
-        jobs[n++] = DepthJob{0, nv, L.N, 0u};
-        return n;
-    }
-    if (L.n4 > 0) jobs[n++] = DepthJob{0, nv, L.n4, 0u};
-    if (L.n3 > 0) jobs[n++] = DepthJob{(size_t)nv * L.n4, L.n_groups, L.n3, (uint32_t)L.n4};
-    return n;
-}
-
 bool plan_fits(const Layout& L) {
     for (int k = 0; k < L.n_passes(); ++k) {
         const Pass P = L.pass(k);
         DepthJob jobs[2];
         const int nj = depth_jobs(L, P, jobs);
-        for (int q = 0; q < nj && !depth_ranks(jobs, nj); ++q)
-            if (depth_plan(jobs[q].len, jobs[q].n_seg).words > L.hist_words) return false;
+        for (int q = 0; q < nj; ++q)
+            if (!depth_ranks(jobs[q]) && depth_plan(jobs[q].len, jobs[q].n_seg).words > L.hist_words) return false;
         const int bits = bits_for(P.supers);
         const int cp = n_passes_for(bits, kMaxRadixBits);
         for (int p = 0, shift = 0; p < cp; ++p) {
@@ -693,11 +696,10 @@ bool bin_pass(h4d_ctx* c, const Layout& L, const Pass& P, int tile, int cull, vo
         StageScope sc(c, st, H4D_STAGE_DEPTH_SORT);
         DepthJob jobs[2];
         const int nj = depth_jobs(L, P, jobs);
-        const bool ranks = depth_ranks(jobs, nj);
         for (int q = 0; q < nj; ++q) {
             const size_t o = jobs[q].offset;
-            if (!launch_depth_sort(dk + o, jobs[q].id0, dv + o, jobs[q].len, jobs[q].n_seg, ranks, pairs + o, hist,
-                                   L.hist_words, totals, L.totals_words, st))
+            if (!launch_depth_sort(dk + o, jobs[q].id0, dv + o, jobs[q].len, jobs[q].n_seg, depth_ranks(jobs[q]),
+                                   pairs + o, hist, L.hist_words, totals, L.totals_words, st))
                 return false;
         }
     }
