@@ -1515,7 +1515,8 @@ __global__ void __launch_bounds__(256) k_bin_count(const uint32_t* __restrict__ 
 // In place: hist rows become, within each chunk of kBinChunk blocks of one
 // segment, the exclusive sums over the chunk's blocks before; chunk_sums[chunk]
 // [2 words] the chunk's totals.  Two 16-bit counts share a word: a chunk's
-// total is at most 64 x 256.  grid: (words / 64, chunks).
+// total is at most 64 x 256.  grid: a workgroup per chunk and 64 words, the chunk's
+// side by side (in x, where more than 65535 chunks fit as well).
 __global__ void __launch_bounds__(256) k_bin_chunks(uint32_t* __restrict__ hist, int words, SegLayout sg,
                                                     const unsigned long long* __restrict__ partials,
                                                     uint2* __restrict__ chunk_sums,
@@ -1523,7 +1524,7 @@ __global__ void __launch_bounds__(256) k_bin_chunks(uint32_t* __restrict__ hist,
     __shared__ uint32_t s_sum[4][64];
     const int nba = ceil_div(sg.la, kBinBlock), nbb = ceil_div(sg.lb, kBinBlock);
     const int nca = ceil_div(nba, kBinChunk), ncb = ceil_div(nbb, kBinChunk);
-    const int c = (int)blockIdx.y;
+    const int cols = ceil_div(words, 64), c = (int)blockIdx.x / cols, col0 = (int)blockIdx.x - c * cols;
     int b0, nb;  // the chunk's blocks
     if (c < sg.na * nca) {
         const int s = c / nca, k = c - s * nca;
@@ -1534,7 +1535,7 @@ __global__ void __launch_bounds__(256) k_bin_chunks(uint32_t* __restrict__ hist,
         b0 = sg.na * nba + s * nbb + k * kBinChunk;
         nb = min(kBinChunk, nbb - k * kBinChunk);
     }
-    const int col = (int)blockIdx.x * 64 + ((int)threadIdx.x & 63), rg = (int)threadIdx.x >> 6;
+    const int col = col0 * 64 + ((int)threadIdx.x & 63), rg = (int)threadIdx.x >> 6;
     constexpr int R = kBinChunk / 4;
     uint32_t v[R], sum = 0u;
     uint32_t* h = hist + (size_t)(b0 + rg * R) * words + col;
@@ -1558,7 +1559,7 @@ __global__ void __launch_bounds__(256) k_bin_chunks(uint32_t* __restrict__ hist,
         run += v[r];
     }
     if (rg == 0 && col < words) chunk_sums[(size_t)c * words + col] = make_uint2(total & 0xFFFFu, total >> 16);
-    if (blockIdx.x == 0 && threadIdx.x < 64) {
+    if (col0 == 0 && threadIdx.x < 64) {
         unsigned long long e = (int)threadIdx.x < nb ? partials[b0 + threadIdx.x] : 0ull;
         for (int off = 32; off > 0; off >>= 1) e += (unsigned long long)__shfl_xor((long long)e, off);
         if (threadIdx.x == 0) chunk_entries[c] = e;
@@ -1986,8 +1987,8 @@ void launch_bin_ranked(const BinPlan& p, void* work, const uint32_t* sorted_gid,
             chunk_sums = nullptr;                                                                                      \
             k_bin_top<true><<<p.n_seg, 1024, 0, st>>>(hist, partials, nullptr, words, sg, nullptr, lists, seg_entries); \
         } else {                                                                                                       \
-            k_bin_chunks<<<dim3((words + 63) / 64, (unsigned)p.chunks), 256, 0, st>>>(hist, words, sg, partials,       \
-                                                                                      chunk_sums, chunk_entries);      \
+            k_bin_chunks<<<(unsigned)(p.chunks * ceil_div(words, 64)), 256, 0, st>>>(hist, words, sg, partials,        \
+                                                                                     chunk_sums, chunk_entries);       \
             k_bin_top<false><<<p.n_seg, 1024, 0, st>>>(nullptr, nullptr, chunk_sums, words, sg, chunk_entries, lists,  \
                                                        seg_entries);                                                   \
         }                                                                                                              \

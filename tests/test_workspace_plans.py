@@ -39,3 +39,18 @@ for _ in range(4000):
     assert rc == L.H4D_OK, (n3, n4, V, W, H, cfg.tile, cfg.batched, cfg.cull, cfg.pair_capacity, error())
     R.record_clear()
 """)
+
+
+def test_grids_stay_within_the_launch_limits(stub):  # noqa: F811
+    """A batched call of more than 2^30 (view, Gaussian) pairs: no grid of more than
+    65535 in y or z, nor of 2^32 threads in x."""
+    hip_record.run(stub, """
+for n3, n4, same, cull in [(33600000, 0, False, 0), (1000, 33600000, True, 0), (33600000, 0, False, 1)]:
+    rc = render(n3, n4, cameras(32, 64, 64, same), 32, L.Config(16, 64, 1, cull, 1 << 22))
+    assert rc == L.H4D_OK, error()
+    got = calls()
+    assert any("k_bin_scatter" in k for k in kernels(got))
+    for c in got:
+        gx, gy, gz, bx = map(int, c[2:])
+        assert 0 < gx and gx * bx < 1 << 32 and 0 < gy <= 65535 and 0 < gz <= 65535, c
+""")
