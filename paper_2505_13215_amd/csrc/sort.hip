@@ -1418,9 +1418,8 @@ constexpr int kBinWide = 255;
 // shrunk rectangles, which the capacity counts.
 // Bound by instruction issue: each lane finds its four rows' spans with two
 // roots per row and integer ends (row_columns); stepping the ends to the exact
-// float comparisons tile by tile and setting the shapes up in FP64 throughout
-// took 0.044 instead of 0.021 ms (250k splats, 1352 x 1014) and 0.151 instead of
-// 0.063 ms (1M, 2704 x 2028).
+// float comparisons tile by tile took 0.044 instead of 0.023 ms (250k splats, 1352 x
+// 1014) and 0.151 instead of 0.067 ms (1M, 2704 x 2028).
 template <int TILE>
 __global__ void __launch_bounds__(256) k_bin_count(const uint32_t* __restrict__ sorted_gid, int N, SegLayout sg,
                                                    const Rec* __restrict__ recs, const ViewParams* __restrict__ views,
