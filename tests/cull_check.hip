@@ -2,8 +2,10 @@
 // run by test_cull_reach.py; no GPU is used).  For random splats of one kind it
 // goes through every pixel of the splat's square in every tile that tile_mask
 // leaves out and counts those that would blend: power <= 0 and opacity
-// exp(power) >= 1/255, evaluated in FP64 from the record's float32 values.  Prints
-// "kind K tile T dropped D blending B" per kind of splat and tile size.
+// exp(power) >= 1/255, evaluated in FP64 from the record's float32 values.  It also
+// counts the ellipses whose extents are not their FP64 values rounded to float32
+// (to a unit in the last place).  Prints "kind K tile T dropped D blending B rounded
+// R" per kind of splat and tile size.
 #include "../paper_2505_13215_amd/csrc/sort.hip"
 
 #include <algorithm>
@@ -48,7 +50,7 @@ static void check(const Kind& kind, int splats) {
     constexpr int S = super_factor(TILE);
     std::mt19937_64 g(20250513);
     const int W = kind.W, H = kind.H;
-    long dropped = 0, blending = 0;
+    long dropped = 0, blending = 0, rounded = 0;
     for (int it = 0; it < splats; ++it) {
         const Splat2 z = kind.draw(g, W, H);
         const double c = std::cos(z.angle), s = std::sin(z.angle);
@@ -66,6 +68,14 @@ static void check(const Kind& kind, int splats) {
         rec.c = make_float4(0.f, (float)fu, (float)fv, 1.f);
         rec.d = make_uint4((uint32_t)x0 | ((uint32_t)x1 << 16), (uint32_t)y0 | ((uint32_t)y1 << 16), 1u, 1u);
         const CullShape cs = cull_shape(rec);
+        if (cs.mode == 1) {
+            const double a = -(double)rec.a.z, b = rec.a.w, cc = -(double)rec.b.x, det4 = 4.0 * a * cc - b * b;
+            const double t = std::log2(255.0 * (double)rec.b.y) + kCullMargin;
+            const double y_full = std::sqrt(4.0 * a * t / det4), x_ext = std::sqrt(4.0 * cc * t / det4);
+            const auto off = [](float f, double x) { return std::fabs(f - x) > std::ldexp(std::fabs(x), -23); };
+            rounded += off(cs.y_full, y_full) || off(cs.four_at, 4.0 * a * t) || off(cs.inv2a, 0.5 / a) ||
+                       off(cs.y_ext, 0.5 * b * x_ext / cc);
+        }
         const uint32_t tx0 = x0 / TILE, tx1 = x1 / TILE, ty0 = y0 / TILE, ty1 = y1 / TILE;
         for (uint32_t ty = ty0; ty <= ty1; ++ty)
             for (uint32_t tx = tx0; tx <= tx1; ++tx) {
@@ -81,7 +91,7 @@ static void check(const Kind& kind, int splats) {
                     }
             }
     }
-    std::printf("kind %s tile %d dropped %ld blending %ld\n", kind.name, TILE, dropped, blending);
+    std::printf("kind %s tile %d dropped %ld blending %ld rounded %ld\n", kind.name, TILE, dropped, blending, rounded);
 }
 
 int main(int argc, char** argv) {

@@ -1,7 +1,8 @@
 """The tile test leaves out no pixel that would blend (host build of the kernels'
 helpers, no GPU): for random splats near the image, needles, and vast splats whose
 centre lies 10^4 to 10^9 pixels away, every pixel of the tiles that it drops is
-evaluated in FP64.  (Conservative culling, reading of Alg. 1's DuplicateWithKeys.)"""
+evaluated in FP64.  The ellipses' extents are
+set up in FP64.  (Conservative culling, reading of Alg. 1's DuplicateWithKeys.)"""
 import os
 import shutil
 import subprocess
@@ -27,3 +28,4 @@ def test_dropped_tiles_hold_no_blending_pixel(tmp_path):
     for r in rows:
         assert int(r[5]) > 1_000, out  # (the kind is dropped somewhere)
         assert int(r[7]) == 0, out
+        assert int(r[9]) == 0, out
