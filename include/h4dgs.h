@@ -432,8 +432,8 @@ h4d_status h4dgs_l1_loss_grad(h4d_ctx *ctx, int32_t n_views, const float *const 
  * host before launching anything (and the launcher again per pass); these two
  * calls expose that arithmetic so that it can be tested without a GPU.
  * h4dgs_radix_hist_words: histogram words one pass over `capacity` keys in
- * n_seg segments with nbits-bit digits and `items` keys per thread (8 or 2)
- * needs.  h4dgs_radix_pass_check: H4D_OK if such a pass fits histogram /
+ * n_seg segments with nbits-bit digits and `items` keys per thread (8, as the
+ * passes run, or 2) needs.  h4dgs_radix_pass_check: H4D_OK if such a pass fits histogram /
  * digit-total buffers of hist_words / totals_words 32-bit words, else
  * H4D_ERR_INVALID_ARG (also for nbits outside [1, 11] or other items). */
 size_t h4dgs_radix_hist_words(uint64_t capacity, int32_t n_seg, int32_t nbits, int32_t items);

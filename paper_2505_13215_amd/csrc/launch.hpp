@@ -67,8 +67,8 @@ int radix_blocks(uint64_t capacity, int items);
 size_t radix_hist_words(uint64_t capacity, int n_seg, int max_bits, int items);
 // Whether a pass fits histogram / digit-total buffers of the given sizes (in
 // 32-bit words): hist needs radix_hist_words(capacity, n_seg, nbits, items),
-// totals 2^nbits * n_seg; nbits in [1, 11], items kSortItems or 2 (8-bit
-// digits only).
+// totals 2^nbits * n_seg; nbits in [1, 11], items kSortItems, as the passes run, or
+// 2 (8-bit digits only; sizes alone).
 bool radix_pass_fits(uint64_t capacity, int n_seg, int nbits, int items, size_t hist_words, size_t totals_words);
 // One stable LSD pass over `nbits` (<= 11) bits at `shift`, independently on
 // n_seg segments that start seg_stride elements apart (all arrays).  Count

@@ -372,9 +372,10 @@ __global__ void __launch_bounds__(256) k_preprocess(G3Ptr g3, G4Ptr g4, const Vi
 // Backward kernel: one thread per Gaussian, looping over the views of the call
 // (no atomics: every view's contribution to a Gaussian lands in one lane).
 // g2: per (view, Gaussian) screen-space gradients from the blending adjoint,
-// layout [view][N][kG2Stride], in doubles when wide, else: du dv dQ00 dQ01 dQ11 dop dr dg, then db as
-// four parts (w.r.t. the unscaled conic entries, Q01 counted once; the first
-// five without their factors -op / log2 e, -op / log2 e, -op / 2, -op, -op / 2).
+// layout [view][N][kG2Stride]: du dv dQ00 dQ01 dQ11 dop dr dg, then db as four
+// parts, or, when wide (kG2Wide), the first six as doubles and dr dg db as floats
+// (w.r.t. the unscaled conic entries, Q01 counted once; the first five without
+// their factors -op / log2 e, -op / log2 e, -op / 2, -op, -op / 2).
 //
 // Per view the projection adjoint gives mu_c-bar, Sigma_c-bar and op-bar; the
 // slicing adjoint maps them to the spatial/temporal means and to the symmetric

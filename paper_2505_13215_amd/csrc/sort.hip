@@ -88,7 +88,7 @@ __device__ inline uint32_t block_scan_digits(uint32_t* s, int radix, uint32_t* s
 // MB: largest digit width the instantiation handles (LDS is sized for it).
 // skip_empty: keys whose upper 16 bits are zero (coarse entries with an empty
 // tile mask) are left out of the counts (and, in the downsweep, of the output).
-template <int MB, int ITEMS>
+template <int MB>
 __global__ void __launch_bounds__(kSortThreads) k_radix_upsweep(const uint32_t* __restrict__ keys,
                                                                 const unsigned long long* dcount, uint64_t hcount,
                                                                 int shift, int nbits, uint32_t* __restrict__ hist,
@@ -100,11 +100,11 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_upsweep(const uint32_t* 
     const uint32_t mask = (uint32_t)radix - 1u;
     const int tid = threadIdx.x, w = tid >> 6;
     const uint64_t n = read_count(dcount, hcount);
-    const uint64_t begin = (uint64_t)blockIdx.x * (kSortThreads * ITEMS);
+    const uint64_t begin = (uint64_t)blockIdx.x * kSortTile;
     if (begin >= n) return;  // blocks past the live count are never scanned (uniform)
     for (int d = tid; d < 4 * radix; d += kSortThreads) s_hist[d / radix][d % radix] = 0;
     __syncthreads();
-    for (int k = 0; k < ITEMS; ++k) {
+    for (int k = 0; k < kSortItems; ++k) {
         const uint64_t idx = begin + (uint64_t)k * kSortThreads + tid;
         if (idx < n) {
             const uint32_t key = keys[idx];
@@ -147,7 +147,7 @@ __global__ void __launch_bounds__(256) k_radix_digit_scan(uint32_t* __restrict__
     if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
-template <int MB, int ITEMS>
+template <int MB>
 __global__ void __launch_bounds__(kSortThreads) k_radix_downsweep(
     const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in, uint32_t* __restrict__ keys_out,
     uint32_t* __restrict__ vals_out, const unsigned long long* dcount, uint64_t hcount, int shift, int nbits,
@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_downsweep(
     __shared__ uint32_t s_dstart[1 << MB];
     __shared__ uint32_t s_gbase[1 << MB];
     __shared__ uint32_t s_buf[256];
-    constexpr int TILE = kSortThreads * ITEMS;
+    constexpr int ITEMS = kSortItems, TILE = kSortTile;
     __shared__ uint32_t s_keys[TILE];
     __shared__ uint32_t s_vals[TILE];
 
@@ -285,11 +285,11 @@ bool launch_radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, uint32_
     // the smallest instantiation that holds the digit (LDS is sized by it)
 #define H4D_RADIX_PASS(MB)                                                                                            \
     do {                                                                                                              \
-        k_radix_upsweep<MB, kSortItems><<<grid, kSortThreads, 0, st>>>(keys_in, dcount, hcount, shift, nbits, hist,   \
-                                                                      nb, seg_stride, skip_empty);                   \
+        k_radix_upsweep<MB><<<grid, kSortThreads, 0, st>>>(keys_in, dcount, hcount, shift, nbits, hist, nb,           \
+                                                          seg_stride, skip_empty);                                   \
         k_radix_digit_scan<<<dim3(1 << nbits, n_seg), 256, 0, st>>>(hist, nb, 1 << nbits, totals, dcount, hcount,     \
                                                                     kSortTile);                                      \
-        k_radix_downsweep<MB, kSortItems><<<grid, kSortThreads, 0, st>>>(                                            \
+        k_radix_downsweep<MB><<<grid, kSortThreads, 0, st>>>(                                                        \
             keys_in, vals_in, keys_out, vals_out, dcount, hcount, shift, nbits, hist, totals, nb, out_offset,         \
             seg_stride, digit_ranges, n_digit_ranges, val_map, skip_empty, out_count, pairs_out, val0);               \
     } while (0)
