@@ -468,7 +468,7 @@ __device__ __forceinline__ void quad_stage(const Rec& r, uint32_t gid, int n, in
     uint32_t q = 0u;  // quadrants, bit 2 row + column
     if (lane < n) {
         stage_splat(r, gid, ty * 16, ty * 16 + 15, s.sp[b][lane]);
-        const CullShape cs = cull_shape(r);
+        const CullShape cs = cull_shape<false>(r);
         if (cs.mode == 0) q = 0xFu;
         if (cs.mode == 1) {
             int r0, r1;

@@ -14,40 +14,75 @@ namespace h4d {
 // arithmetic has no pixel that the blending kernels would blend.
 constexpr double kCullMargin = 1e-3;
 
+// Root of a normal x > 0: on the device the hardware's reciprocal root and one
+// step on it, which gives sqrtf's bits (all 2^24 floats of [1, 4)) in a third of its
+// instructions (1M splats, 2704 x 2028: counting 0.073 -> 0.067 ms).
+__host__ __device__ __forceinline__ float cull_root(float x) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const float r = __builtin_amdgcn_rsqf(x), y = x * r;
+    return __builtin_fmaf(__builtin_fmaf(-y, y, x), 0.5f * r, y);
+#else
+    return sqrtf(x);
+#endif
+}
+// (the hardware's approximation, one ulp, on the device)
+__host__ __device__ __forceinline__ float cull_rcp(float x) {
+#ifdef __HIP_DEVICE_COMPILE__
+    return __builtin_amdgcn_rcpf(x);
+#else
+    return 1.f / x;
+#endif
+}
+constexpr float kRootLeast = 1.17549435e-38f;  // the smallest normal
+
 // The alpha >= 1/255 region of one splat as the tile test needs it:
 // -p2 = a dx^2 - b dx dy + c dy^2 <= t, with dx, dy offsets from the centre.
-// Set up in FP64 per splat; the per-row test runs in FP32 on intervals widened
-// by pad_x / pad_y: 2e-3 of the ellipse's half-extent plus 0.01 px, several times
-// the FP32 rounding of the extent (whose worst case, near the ellipse's top and
-// bottom, is about 5e-4 of the half-width).
+// Set up in FP64 once per splat by the binning; the per-row test runs in FP32 on
+// intervals widened by pad_x / pad_y: 2e-3 of the ellipse's half-extent plus 0.01 px,
+// several times the FP32 rounding of the extent (whose worst case, near the
+// ellipse's top and bottom, is about 5e-4 of the half-width).
+// FP64 = false: for the quadrant kernels, which pick their quadrants' splats from a
+// list that is already the tile's, once per tile and splat.  Only the determinant,
+// which cancels, is FP64; the rest is within a few roundings, far inside the pads
+// (1785 tiles, 73k Gaussians: forward and binning 0.132 ms against 0.146).
+template <bool FP64 = true>
 __host__ __device__ inline CullShape cull_shape(const Rec& rec) {
 #pragma clang fp contract(off)
     CullShape cs;
-    const double a = -(double)rec.a.z, b = rec.a.w, c = -(double)rec.b.x, op = rec.b.y;
+    const float a = -rec.a.z, b = rec.a.w, c = -rec.b.x, op = rec.b.y;
     cs.ui = rec.c.y; cs.uf = rec.a.x; cs.vi = rec.c.z; cs.vf = rec.a.y;
     cs.px0 = (int)(rec.d.x & 0xFFFFu); cs.px1 = (int)(rec.d.x >> 16);
     cs.py0 = (int)(rec.d.y & 0xFFFFu); cs.py1 = (int)(rec.d.y >> 16);
-    const double det4 = 4.0 * a * c - b * b;
+    const double ac4 = 4.0 * (double)a * (double)c, det4 = ac4 - (double)b * (double)b;
     cs.mode = 0;
     cs.b = cs.inv2a = cs.four_at = cs.det4 = cs.y_full = cs.y_ext = cs.pad_x = cs.pad_y = 0.f;
     // a proper ellipse only (of a size that float32 holds); otherwise keep every overlapped tile
-    if (a > 0.0 && c > 0.0 && det4 > 1e-12 * 4.0 * a * c && det4 > 1e-30 && det4 < 1e37 && op > 0.0) {
-        const double t = log2(255.0 * op) + kCullMargin;
-        if (t <= 0.0) {
-            cs.mode = 2;
-        } else {
-            cs.mode = 1;
-            const double ia = 0.5 / a, ic = 0.5 / c, t4 = 4.0 * t / det4;
-            const double y_full = sqrt(a * t4), x_ext = sqrt(c * t4);
-            cs.b = (float)b;
-            cs.inv2a = (float)ia;
-            cs.four_at = (float)(4.0 * a * t);
-            cs.det4 = (float)det4;
-            cs.y_full = (float)y_full;
-            cs.y_ext = (float)(b * x_ext * ic);
-            cs.pad_y = (float)(2e-3 * y_full + 1e-2);
-            cs.pad_x = (float)(2e-3 * (x_ext + fabs(b) * y_full * ia) + 1e-2);
-        }
+    if (!(a > 1e-30f && c > 1e-30f && det4 > 1e-12 * ac4 && det4 > 1e-30 && det4 < 1e37 && op > 0.f)) return cs;
+    cs.b = b;
+    cs.det4 = (float)det4;
+    if constexpr (FP64) {
+        const double t = log2(255.0 * (double)op) + kCullMargin;
+        cs.mode = t <= 0.0 ? 2 : 1;
+        if (cs.mode == 2) return cs;
+        const double ia = 0.5 / (double)a, ic = 0.5 / (double)c, t4 = 4.0 * t / det4;
+        const double y_full = sqrt((double)a * t4), x_ext = sqrt((double)c * t4);
+        cs.inv2a = (float)ia;
+        cs.four_at = (float)(4.0 * (double)a * t);
+        cs.y_full = (float)y_full;
+        cs.y_ext = (float)((double)b * x_ext * ic);
+        cs.pad_y = (float)(2e-3 * y_full + 1e-2);
+        cs.pad_x = (float)(2e-3 * (x_ext + fabs((double)b) * y_full * ia) + 1e-2);
+    } else {
+        const float t = log2f(255.f * op) + (float)kCullMargin;
+        cs.mode = t <= 0.f ? 2 : 1;
+        if (cs.mode == 2) return cs;
+        const float t4 = 4.f * t * cull_rcp(cs.det4), x_ext = cull_root(fmaxf(kRootLeast, c * t4));
+        cs.inv2a = 0.5f * cull_rcp(a);
+        cs.four_at = 4.f * a * t;
+        cs.y_full = cull_root(fmaxf(kRootLeast, a * t4));
+        cs.y_ext = 0.5f * b * x_ext * cull_rcp(c);
+        cs.pad_y = 2e-3f * cs.y_full + 1e-2f;
+        cs.pad_x = 2e-3f * (x_ext + fabsf(b) * cs.y_full * cs.inv2a) + 1e-2f;
     }
     return cs;
 }
@@ -99,17 +134,6 @@ __host__ __device__ __forceinline__ void slab_rows(const CullShape& cs, int ty0,
     r1 = min(ty1, tile_of<TILE>(hi));
     if (lo > cs.py1 || hi < cs.py0) r1 = r0 - 1;
 }
-// Root of a normal x > 0: on the device the hardware's reciprocal root and one
-// step on it, which gives sqrtf's bits (all 2^24 floats of [1, 4)) in a third of its
-// instructions (1M splats, 2704 x 2028: counting 0.073 -> 0.067 ms).
-__host__ __device__ __forceinline__ float cull_root(float x) {
-#ifdef __HIP_DEVICE_COMPILE__
-    const float r = __builtin_amdgcn_rsqf(x), y = x * r;
-    return __builtin_fmaf(__builtin_fmaf(-y, y, x), 0.5f * r, y);
-#else
-    return sqrtf(x);
-#endif
-}
 // The ellipse's x-extent [xl, xr] over tile row ty's slab (from its leftmost
 // and rightmost points clamped into the slab), widened by pad_x.
 template <int TILE>
@@ -117,8 +141,8 @@ __host__ __device__ __forceinline__ void row_extent(const CullShape& cs, int ty,
 #pragma clang fp contract(off)
     const float Y0 = row_y0<TILE>(cs, ty), Y1 = row_y1<TILE>(cs, ty);
     const float yr = fminf(fmaxf(cs.y_ext, Y0), Y1), yl = fminf(fmaxf(-cs.y_ext, Y0), Y1);
-    xr = (cs.b * yr + cull_root(fmaxf(1.17549435e-38f, cs.four_at - yr * yr * cs.det4))) * cs.inv2a + cs.pad_x;
-    xl = (cs.b * yl - cull_root(fmaxf(1.17549435e-38f, cs.four_at - yl * yl * cs.det4))) * cs.inv2a - cs.pad_x;
+    xr = (cs.b * yr + cull_root(fmaxf(kRootLeast, cs.four_at - yr * yr * cs.det4))) * cs.inv2a + cs.pad_x;
+    xl = (cs.b * yl - cull_root(fmaxf(kRootLeast, cs.four_at - yl * yl * cs.det4))) * cs.inv2a - cs.pad_x;
 }
 // The tile columns of tile row ty (one of slab_rows') that the test keeps, as
 // one word: first column | (last + 1) << 16 (0: none).

@@ -4,7 +4,7 @@
 // leaves out and counts those that would blend: power <= 0 and opacity
 // exp(power) >= 1/255, evaluated in FP64 from the record's float32 values.  It also
 // counts the ellipses whose extents are not their FP64 values rounded to float32
-// (to a unit in the last place).  Prints "kind K tile T dropped D blending B rounded
+// (to a unit in the last place; not for the quadrants' shapes).  Prints "kind K tile T dropped D blending B rounded
 // R" per kind of splat and tile size.
 #include "../paper_2505_13215_amd/csrc/sort.hip"
 
@@ -45,7 +45,8 @@ static Splat2 far_off(std::mt19937_64& g, int W, int H) {
             uni(g) * 3.141592653589793};
 }
 
-template <int TILE>
+// FP64: as the binning sets the shapes up; otherwise as the quadrant kernels do.
+template <int TILE, bool FP64 = true>
 static void check(const Kind& kind, int splats) {
     constexpr int S = super_factor(TILE);
     std::mt19937_64 g(20250513);
@@ -67,8 +68,8 @@ static void check(const Kind& kind, int splats) {
         rec.b = make_float4((float)(sa / det * k), (float)op, 0.f, 0.f);
         rec.c = make_float4(0.f, (float)fu, (float)fv, 1.f);
         rec.d = make_uint4((uint32_t)x0 | ((uint32_t)x1 << 16), (uint32_t)y0 | ((uint32_t)y1 << 16), 1u, 1u);
-        const CullShape cs = cull_shape(rec);
-        if (cs.mode == 1) {
+        const CullShape cs = cull_shape<FP64>(rec);
+        if (FP64 && cs.mode == 1) {
             const double a = -(double)rec.a.z, b = rec.a.w, cc = -(double)rec.b.x, det4 = 4.0 * a * cc - b * b;
             const double t = std::log2(255.0 * (double)rec.b.y) + kCullMargin;
             const double y_full = std::sqrt(4.0 * a * t / det4), x_ext = std::sqrt(4.0 * cc * t / det4);
@@ -91,7 +92,7 @@ static void check(const Kind& kind, int splats) {
                     }
             }
     }
-    std::printf("kind %s tile %d dropped %ld blending %ld rounded %ld\n", kind.name, TILE, dropped, blending, rounded);
+    std::printf("kind %s%s tile %d dropped %ld blending %ld rounded %ld\n", kind.name, FP64 ? "" : "-quadrants", TILE, dropped, blending, rounded);
 }
 
 int main(int argc, char** argv) {
@@ -103,6 +104,7 @@ int main(int argc, char** argv) {
         check<8>(k, splats);
         check<16>(k, splats);
         check<32>(k, splats);
+        check<8, false>(k, splats);
     }
     return 0;
 }

@@ -23,8 +23,8 @@ def test_dropped_tiles_hold_no_blending_pixel(tmp_path):
     subprocess.run(cmd, check=True, capture_output=True, timeout=600)
     out = subprocess.run([exe, "2000"], check=True, capture_output=True, text=True, timeout=600).stdout
     rows = [ln.split() for ln in out.splitlines() if ln.startswith("kind ")]
-    assert [(r[1], int(r[3])) for r in rows] == [(k, t) for k in ("near", "thin", "far4", "far6", "far7", "far8")
-                                                 for t in (8, 16, 32)]
+    assert [(r[1], int(r[3])) for r in rows] == [(k + q, t) for k in ("near", "thin", "far4", "far6", "far7", "far8")
+                                                 for q, t in (("", 8), ("", 16), ("", 32), ("-quadrants", 8))]
     for r in rows:
         assert int(r[5]) > 1_000, out  # (the kind is dropped somewhere)
         assert int(r[7]) == 0, out
