@@ -443,8 +443,8 @@ h4d_status h4dgs_radix_pass_check(uint64_t capacity, int32_t n_seg, int32_t nbit
 /* ---- instrumentation ---------------------------------------------------- */
 typedef enum {
     H4D_STAGE_PREPROCESS = 0,     /* per-Gaussian FP64 geometry, records, depth keys */
-    H4D_STAGE_DEPTH_SORT = 1,     /* radix sort of the depth keys */
-    H4D_STAGE_BINNING = 2,        /* pair offsets, emission, tile sort, tile ranges */
+    H4D_STAGE_DEPTH_SORT = 1,     /* depth order of the Gaussians */
+    H4D_STAGE_BINNING = 2,        /* super-tile lists and their ranges */
     H4D_STAGE_BLEND_FWD = 3,      /* front-to-back blending */
     H4D_STAGE_BLEND_BWD = 4,      /* blending adjoint */
     H4D_STAGE_PREPROCESS_BWD = 5, /* per-Gaussian FP64 adjoint */
