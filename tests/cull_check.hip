@@ -2,7 +2,8 @@
 // run by test_cull_reach.py; no GPU is used).  For random splats of one kind it
 // goes through every pixel of the splat's square in every tile that tile_mask
 // leaves out and counts those that would blend: power <= 0 and opacity
-// exp(power) >= 1/255, evaluated in FP64 from the record's float32 values.  It also
+// exp(power) >= 1/255, the power evaluated in FP64 from the record's float32 values
+// or as the kernels do in FP32.  It also
 // counts the ellipses whose extents are not their FP64 values rounded to float32
 // (to a unit in the last place; not for the quadrants' shapes).  Prints "kind K tile T dropped D blending B rounded
 // R" per kind of splat and tile size.
@@ -43,6 +44,14 @@ static Splat2 far_off(std::mt19937_64& g, int W, int H) {
     const double a = d * (0.4 + 3.0 * uni(g));
     return {0.5 * W + d * std::cos(th), 0.5 * H + d * std::sin(th), a * a, a * a * log_uni(g, 1e-2, 1.0),
             uni(g) * 3.141592653589793};
+}
+
+// The power as the blending kernels evaluate it (eval_col, eval_pix).
+static float kernel_power(const Rec& r, int px, int py) {
+#pragma clang fp contract(off)
+    const float dx = (((float)px + 0.5f) - r.c.y) - r.a.x, dy = (((float)py + 0.5f) - r.c.z) - r.a.y;
+    const float qadx = r.a.z * dx;
+    return std::fmaf(dy, std::fmaf(r.b.x, dy, r.a.w * dx), qadx * dx);
 }
 
 // FP64: as the binning sets the shapes up; otherwise as the quadrant kernels do.
@@ -88,7 +97,10 @@ static void check(const Kind& kind, int splats) {
                         const double dx = px + 0.5 - rec.c.y - (double)rec.a.x, dy = py + 0.5 - rec.c.z - (double)rec.a.y;
                         const double p2 = (double)rec.a.z * dx * dx + (double)rec.a.w * dx * dy + (double)rec.b.x * dy * dy;
                         ++dropped;
-                        if (p2 <= 0.0 && p2 + std::log2((double)rec.b.y) >= -std::log2(255.0)) ++blending;
+                        const auto blends = [&](double power) {
+                            return power <= 0.0 && power + std::log2((double)rec.b.y) >= -std::log2(255.0);
+                        };
+                        if (blends(p2) || blends(kernel_power(rec, px, py))) ++blending;
                     }
             }
     }

@@ -1,7 +1,7 @@
 """The tile test leaves out no pixel that would blend (host build of the kernels'
 helpers, no GPU): for random splats near the image, needles, and vast splats whose
 centre lies 10^4 to 10^9 pixels away, every pixel of the tiles that it drops is
-evaluated in FP64.  The ellipses' extents are
+evaluated in FP64 and in the kernels' FP32.  The ellipses' extents are
 set up in FP64.  (Conservative culling, reading of Alg. 1's DuplicateWithKeys.)"""
 import os
 import shutil
