@@ -73,6 +73,8 @@ __host__ __device__ inline CullShape cull_shape(const Rec& rec) {
         cs.pad_y = (float)(2e-3 * y_full + 1e-2);
         cs.pad_x = (float)(2e-3 * (x_ext + fabs((double)b) * y_full * ia) + 1e-2);
     } else {
+        // (a centre that is not a number fails no test of the blending's: keep it)
+        if (!(fabsf(cs.uf) <= 1.f && fabsf(cs.vf) <= 1.f)) return cs;
         const float t = log2f(255.f * op) + (float)kCullMargin;
         cs.mode = t <= 0.f ? 2 : 1;
         if (cs.mode == 2) return cs;

@@ -1,5 +1,5 @@
-"""Vast splats whose centre lies far off the image (GPU): images do not depend on
-culling or the tile size, and hold what the splats blend."""
+"""Vast splats whose centre lies far off the image, and splats without a centre (GPU):
+images do not depend on culling or the tile size, and hold what the splats blend."""
 import numpy as np
 import pytest
 
@@ -28,3 +28,22 @@ def test_images_do_not_depend_on_culling(distance):
         for cull in (False, True):
             got = h4d.rasterize_splats(h4d.Rasterizer(tile=tile, cull=cull), sp, W, H)[:2]
             assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (tile, cull)
+
+
+def test_splats_without_a_centre():
+    """A centre that is not a number: the pixels of the splat's square pass the power
+    test (no comparison fails), and the quadrants keep all of them as the other
+    kernels do."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_13215_amd as h4d
+    print("[far splats] no centre", flush=True)
+    n, W, H = 3, 40, 150
+    f = lambda x: np.asarray(x, np.float32)
+    sp = dict(u=f([np.nan, 20.0, 12.0]), v=f([70.0, np.nan, 40.0]), conic=f([[0.01] * n, [0.0] * n, [0.01] * n]),
+              opacity=f([0.5, 0.6, 0.7]), rgb=f(np.arange(9).reshape(3, 3) / 9.0), radius=np.full(n, 60, np.int32),
+              depth=f([1.0, 2.0, 3.0]), visible=np.ones(n, np.uint8))
+    want = h4d.rasterize_splats(h4d.Rasterizer(tile=8, cull=False), sp, W, H)[:2]
+    got = h4d.rasterize_splats(h4d.Rasterizer(tile=16, cull=False), sp, W, H)[:2]
+    assert torch.equal(got[0].nan_to_num(7.0), want[0].nan_to_num(7.0))
+    assert torch.equal(got[1].nan_to_num(7.0), want[1].nan_to_num(7.0))
