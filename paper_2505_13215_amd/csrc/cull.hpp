@@ -33,7 +33,7 @@ __host__ __device__ __forceinline__ float cull_rcp(float x) {
     return 1.f / x;
 #endif
 }
-constexpr float kRootLeast = 1.17549435e-38f;  // the smallest normal
+constexpr float kRootLeast = 1.17549435e-38f, kRootMost = 3.4e38f;  // the range of its argument
 
 // The alpha >= 1/255 region of one splat as the tile test needs it:
 // -p2 = a dx^2 - b dx dy + c dy^2 <= t, with dx, dy offsets from the centre.
@@ -56,8 +56,11 @@ __host__ __device__ inline CullShape cull_shape(const Rec& rec) {
     const double ac4 = 4.0 * (double)a * (double)c, det4 = ac4 - (double)b * (double)b;
     cs.mode = 0;
     cs.b = cs.inv2a = cs.four_at = cs.det4 = cs.y_full = cs.y_ext = cs.pad_x = cs.pad_y = 0.f;
-    // a proper ellipse only (of a size that float32 holds); otherwise keep every overlapped tile
-    if (!(a > 1e-30f && c > 1e-30f && det4 > 1e-12 * ac4 && det4 > 1e-30 && det4 < 1e37 && op > 0.f)) return cs;
+    // a proper ellipse only (of a size whose products float32 holds); otherwise keep
+    // every overlapped tile
+    if (!(fminf(a, c) > 1e-30f && fmaxf(a, c) < 1e25f && det4 > 1e-12 * ac4 && det4 > 1e-30 && det4 < 1e37 &&
+          op > 0.f && op < 1e30f))
+        return cs;
     cs.b = b;
     cs.det4 = (float)det4;
     if constexpr (FP64) {
@@ -78,10 +81,10 @@ __host__ __device__ inline CullShape cull_shape(const Rec& rec) {
         const float t = log2f(255.f * op) + (float)kCullMargin;
         cs.mode = t <= 0.f ? 2 : 1;
         if (cs.mode == 2) return cs;
-        const float t4 = 4.f * t * cull_rcp(cs.det4), x_ext = cull_root(fmaxf(kRootLeast, c * t4));
+        const float t4 = 4.f * t * cull_rcp(cs.det4), x_ext = cull_root(fminf(fmaxf(kRootLeast, c * t4), kRootMost));
         cs.inv2a = 0.5f * cull_rcp(a);
         cs.four_at = 4.f * a * t;
-        cs.y_full = cull_root(fmaxf(kRootLeast, a * t4));
+        cs.y_full = cull_root(fminf(fmaxf(kRootLeast, a * t4), kRootMost));
         cs.y_ext = 0.5f * b * x_ext * cull_rcp(c);
         cs.pad_y = 2e-3f * cs.y_full + 1e-2f;
         cs.pad_x = 2e-3f * (x_ext + fabsf(b) * cs.y_full * cs.inv2a) + 1e-2f;
@@ -95,19 +98,22 @@ __host__ __device__ inline CullShape cull_shape(const Rec& rec) {
 // the splat's fractional offset, so both ends become integer pixels once per
 // row and the rest is integer arithmetic.  (No contraction: every kernel that
 // evaluates a test decides alike.)
-// First pixel whose centre lies at or past centre + x, and last at or before it
-// (i: integer part of the centre, f: fractional part; an undefined x keeps all).
+// First pixel whose centre lies at or past centre + x, and last at or before it,
+// as whole numbers (i: integer part of the centre, f: fractional part).
 // The sum of the two whole numbers is exact wherever it lies near the image,
 // however far off the centre is and the ellipse reaches (each is a multiple of its
 // own unit in the last place); beyond, only its side counts.
-__host__ __device__ __forceinline__ int first_pixel(float i, float f, float x) {
+__host__ __device__ __forceinline__ float first_pixel(float i, float f, float x) {
 #pragma clang fp contract(off)
-    return (int)fminf(fmaxf(i + ceilf(x + f - 0.5f), -1e9f), 1e9f);
+    return i + ceilf(x + f - 0.5f);
 }
-__host__ __device__ __forceinline__ int last_pixel(float i, float f, float x) {
+__host__ __device__ __forceinline__ float last_pixel(float i, float f, float x) {
 #pragma clang fp contract(off)
-    return (int)fmaxf(fminf(i + floorf(x + f - 0.5f), 1e9f), -1e9f);
+    return i + floorf(x + f - 0.5f);
 }
+// Such a number as an integer; what is not a number counts as far right (left).
+__host__ __device__ __forceinline__ int to_right(float p) { return (int)fmaxf(fminf(p, 1e9f), -1e9f); }
+__host__ __device__ __forceinline__ int to_left(float p) { return (int)fminf(fmaxf(p, -1e9f), 1e9f); }
 // The tile that holds pixel p (rounded down for pixels left of the image).
 template <int TILE>
 __host__ __device__ __forceinline__ int tile_of(int p) {
@@ -126,12 +132,13 @@ __host__ __device__ __forceinline__ float row_y1(const CullShape& cs, int ty) {
     return ((float)min(ty * TILE + TILE - 1, cs.py1) + 0.5f - cs.vi) - cs.vf;
 }
 // The tile rows [r0, r1] of [ty0, ty1] whose slab of pixel centres meets the
-// ellipse's height, widened by pad_y (r1 < r0: none).
+// ellipse's height, widened by pad_y (r1 < r0: none; all for a height or a centre that
+// is not a number).
 template <int TILE>
 __host__ __device__ __forceinline__ void slab_rows(const CullShape& cs, int ty0, int ty1, int& r0, int& r1) {
 #pragma clang fp contract(off)
     const float h = cs.y_full + cs.pad_y;
-    const int lo = first_pixel(cs.vi, cs.vf, -h), hi = last_pixel(cs.vi, cs.vf, h);
+    const int lo = to_left(first_pixel(cs.vi, cs.vf, -h)), hi = to_right(last_pixel(cs.vi, cs.vf, h));
     r0 = max(ty0, tile_of<TILE>(lo));
     r1 = min(ty1, tile_of<TILE>(hi));
     if (lo > cs.py1 || hi < cs.py0) r1 = r0 - 1;
@@ -147,12 +154,13 @@ __host__ __device__ __forceinline__ void row_extent(const CullShape& cs, int ty,
     xl = (cs.b * yl - cull_root(fmaxf(kRootLeast, cs.four_at - yl * yl * cs.det4))) * cs.inv2a - cs.pad_x;
 }
 // The tile columns of tile row ty (one of slab_rows') that the test keeps, as
-// one word: first column | (last + 1) << 16 (0: none).
+// one word: first column | (last + 1) << 16 (0: none, also for an extent or a centre
+// that is not a number).
 template <int TILE>
 __host__ __device__ __forceinline__ uint32_t row_columns(const CullShape& cs, int ty, int tx0, int tx1) {
     float xl, xr;
     row_extent<TILE>(cs, ty, xl, xr);
-    const int lo = first_pixel(cs.ui, cs.uf, xl), hi = last_pixel(cs.ui, cs.uf, xr);
+    const int lo = to_right(first_pixel(cs.ui, cs.uf, xl)), hi = to_left(last_pixel(cs.ui, cs.uf, xr));
     const int cl = max(tx0, tile_of<TILE>(lo)), cr = min(tx1, tile_of<TILE>(hi));
     return lo <= cs.px1 && hi >= cs.px0 && cl <= cr ? (uint32_t)cl | ((uint32_t)(cr + 1) << 16) : 0u;
 }

@@ -43,7 +43,12 @@ def test_splats_without_a_centre():
     sp = dict(u=f([np.nan, 20.0, 12.0]), v=f([70.0, np.nan, 40.0]), conic=f([[0.01] * n, [0.0] * n, [0.01] * n]),
               opacity=f([0.5, 0.6, 0.7]), rgb=f(np.arange(9).reshape(3, 3) / 9.0), radius=np.full(n, 60, np.int32),
               depth=f([1.0, 2.0, 3.0]), visible=np.ones(n, np.uint8))
-    want = h4d.rasterize_splats(h4d.Rasterizer(tile=8, cull=False), sp, W, H)[:2]
-    got = h4d.rasterize_splats(h4d.Rasterizer(tile=16, cull=False), sp, W, H)[:2]
-    assert torch.equal(got[0].nan_to_num(7.0), want[0].nan_to_num(7.0))
-    assert torch.equal(got[1].nan_to_num(7.0), want[1].nan_to_num(7.0))
+    def render(tile, cull, some=slice(None)):
+        return torch.cat([x.reshape(-1, H, W) for x in h4d.rasterize_splats(
+            h4d.Rasterizer(tile=tile, cull=cull), {k: v[..., some] for k, v in sp.items()}, W, H)[:2]]).nan_to_num(7.0)
+
+    assert torch.equal(render(16, False), render(8, False))
+    # culling leaves a splat without a column out of every tile
+    for tile in (8, 16, 32):
+        assert torch.equal(render(tile, True), render(tile, True, slice(1, None)))
+        assert not torch.equal(render(tile, True), render(tile, True, slice(2, None)))
