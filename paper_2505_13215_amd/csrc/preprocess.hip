@@ -618,8 +618,10 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, bool valid, const ViewPara
         for (int k = 0; k < 4; ++k) Ss[r][k] = 0.0;
     double stat_g = 0.0;
     int stat_n = 0;
+    bool seen = false;
     for (int v = 0; v < n_views; ++v) {
         if (!valid || recs[(size_t)v * N + i].d.w == 0u) continue;  // covers no pixel in this view
+        seen = true;
         const ViewParams& V = views[v];
         const double delta = V.time - mt;
         const double pt = exp(-(delta * delta) * 0.5 * ic);
@@ -659,10 +661,11 @@ __device__ inline void bwd_4d(const G4Ptr& g4, int i, bool valid, const ViewPara
         for (int r = 0; r < 3; ++r)
             for (int k = 0; k < 3; ++k) Ss[r][k] += 2.0 * Sb[r][k];
     }
-    // the colour's share of the mean (the slicing adjoint is linear in it)
+    // the colour's share of the mean (the slicing adjoint is linear in it; no view
+    // adds none, also where the covariance is not finite)
     __syncthreads();
     if (!valid) return;
-    {
+    if (seen) {
         const int lane = __lane_id();
         double mub = 0.0, mud = 0.0;
         for (int r = 0; r < 3; ++r) {

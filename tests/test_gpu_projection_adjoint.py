@@ -38,3 +38,18 @@ def test_set_sizes(h4d, n3, n4, times, batched):
     torch.cuda.synchronize()
     r3, r4 = oracle.render_bwd(scene, views, dls)
     check_grads(scene, gr3, gr4, r3, r4, np.zeros(n3 + n4, bool))
+
+
+def test_unseen_rows_of_infinite_extent(h4d):
+    """A 4D Gaussian that no view sees takes no gradient of its times, however its
+    covariance came to be infinite."""
+    print("[projection adjoint] unseen, infinite extent", flush=True)
+    scene = sg.tiny_scene(n3=10, n4=70, seed=103)
+    scene.g4["opacity"][5:60:7] = -30.0  # below 1/255 in every view
+    scene.g4["log_scale"][3, 5:60:7] = np.inf
+    rast = h4d.Rasterizer()
+    g3, g4 = h4d.to_device(scene.g3), h4d.to_device(scene.g4)
+    h = rast.forward(g3, g4, scene.views)
+    _, gr4 = rast.backward(h, g3, g4, [torch.ones_like(im) for im in h.images])
+    for k in ("mean", "mean_t", "opacity", "sh"):
+        assert float(gr4[k][..., 5:60:7].abs().max()) == 0.0, k
