@@ -187,8 +187,7 @@ h4d_status read_back(h4d_ctx* c, void* dst, const void* src, size_t bytes, hipSt
     }
     // (the block holds an earlier read-back's words: a copy that was not enqueued
     // must not pass for this one's)
-    const hipError_t e =
-        launch_copy_words(static_cast<const uint32_t*>(src), pin->words, (int)(bytes / 4), st);
+    const hipError_t e = launch_copy_words(static_cast<const uint32_t*>(src), pin->words, (int)(bytes / 4), st);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         c->give_pin(pin);
@@ -889,8 +888,8 @@ static h4d_status render_forward(h4d_ctx* ctx, const h4d_g3d* g3, const h4d_g4d*
     const G4Ptr p4 = to_ptr(g4);
     ViewParams* vp = at<ViewParams>(state, L.st_views);
     launch_init_state(view_table(views, n_views, cfg->tile, L), vp, at<Status>(state, L.st_status),
-                      keep ? L.tile_ids(quad) : 0, at<unsigned long long>(state, L.st_pair_base), at<unsigned long long>(state, L.st_cranges),
-                      range_words(L), st);
+                      keep ? L.tile_ids(quad) : 0, at<unsigned long long>(state, L.st_pair_base),
+                      at<unsigned long long>(state, L.st_cranges), range_words(L), st);
     PtrTable tab;
     std::memset(&tab, 0, sizeof(tab));
     for (int v = 0; v < n_views; ++v) tab.p[v] = images[v];

@@ -3,10 +3,10 @@
 // goes through every pixel of the splat's square in every tile that tile_mask
 // leaves out and counts those that would blend: power <= 0 and opacity
 // exp(power) >= 1/255, the power evaluated in FP64 from the record's float32 values
-// or as the kernels do in FP32.  It also
-// counts the ellipses whose extents are not their FP64 values rounded to float32
-// (to a unit in the last place; not for the quadrants' shapes).  Prints "kind K tile T dropped D blending B rounded
-// R" per kind of splat and tile size.
+// or as the kernels do in FP32.  It also counts the ellipses whose extents are not
+// their FP64 values rounded to float32 (to a unit in the last place; not for the
+// quadrants' shapes).  Prints "kind K tile T dropped D blending B rounded R" per kind
+// of splat and tile size.
 #include "../paper_2505_13215_amd/csrc/sort.hip"
 
 #include <algorithm>

@@ -21,11 +21,11 @@ def test_dropped_tiles_hold_no_blending_pixel(tmp_path):
     cmd = [hipcc, "--offload-arch=gfx950", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "include"),
            "-Wno-unused-command-line-argument", os.path.join(HERE, "cull_check.hip"), "-o", exe]
     subprocess.run(cmd, check=True, capture_output=True, timeout=600)
-    out = subprocess.run([exe, "2000"], check=True, capture_output=True, text=True, timeout=600).stdout
+    out = subprocess.run([exe, "1000"], check=True, capture_output=True, text=True, timeout=600).stdout
     rows = [ln.split() for ln in out.splitlines() if ln.startswith("kind ")]
     assert [(r[1], int(r[3])) for r in rows] == [(k + q, t) for k in ("near", "thin", "far4", "far6", "far7", "far8")
                                                  for q, t in (("", 8), ("", 16), ("", 32), ("-quadrants", 8))]
     for r in rows:
-        assert int(r[5]) > 1_000, out  # (the kind is dropped somewhere)
+        assert int(r[5]) > 500, out  # (the kind is dropped somewhere)
         assert int(r[7]) == 0, out
         assert int(r[9]) == 0, out
